@@ -475,146 +475,424 @@ __global__ void k_write(const int32_t *__restrict__ leaves, const int32_t *__res
 
 constexpr int MODE_THREADS = 256;
 
+// Leaves whose points lie within NEAR_EXTENT mm per axis and radii of at most
+// NEAR_RADIUS mm take the tiled search: coordinates relative to the leaf's
+// minimum then fit 16 bits together with the padding points at NEAR_PAD
+// (farther than any radius from every point), squared distances 32 bits, and
+// a squared distance up to the link radius's square (below 2^22) packs above a
+// 10-bit point index. Rooms and radii of 5-10 cm are far inside; anything else
+// takes the plain search over all pairs.
+constexpr int NEAR_EXTENT = 28000, NEAR_RADIUS = 2000, NEAR_PAD = -4000;
+constexpr uint32_t D2_CAP = (1u << 22) - 1u;
+static_assert(MAX_R <= 1024, "a point index takes 10 bits");
+static_assert(NEAR_EXTENT - NEAR_PAD <= 32767 && -NEAR_PAD > NEAR_RADIUS, "padding points are far and fit 16 bits");
+static_assert((int64_t)NEAR_RADIUS * NEAR_RADIUS < (int64_t)D2_CAP, "a link distance packs above the index");
+
 struct ModeParams {
     int32_t R, M, minc, rd, rl, reg;
 };
 
-// dynamic LDS of the mode kernel: 7 int32 arrays of `cap` points
-static inline size_t mode_smem(int cap) { return (size_t)7 * 4 * (cap > 0 ? cap : 1); }
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-// One workgroup per leaf. Density and parent searches are exact integer
-// comparisons on LDS-resident points; clusters are the trees of the parent
-// forest (roots by pointer jumping); clusters of at least `minc` points are
-// ranked by (size descending, root ascending) and the first M become modes.
-__device__ void leaf_modes(const Entry *__restrict__ pts, int n, int n_total, int cap, const ModeParams mp,
-                           Mode *__restrict__ out, uint32_t *__restrict__ rgb_out, int rgb_len,
-                           int32_t *__restrict__ n_out, char *smem)
+// One leaf in LDS. The search holds the points in Morton order, relative to
+// the leaf's minimum ({x | y << 16, z, index << 22, order}; points come before
+// one another by density, then by index: order = (2047 - density) << 10 |
+// index), and the bounds of every 8 consecutive ones. Afterwards the points'
+// space holds the clusters' sizes and candidate roots.
+struct __align__(16) ModeLds {
+    u32x4_t pt[MAX_R];
+    int32_t par[MAX_R];      // sort exchange; then parent by original index, then root (-1: a root)
+    uint4 box[MAX_R / 8];    // lo xy, hi xy, lo z, hi z (16-bit halves)
+    int32_t red[MODE_THREADS / 64][6];
+    int32_t n_cand;
+    uint32_t next;
+};
+
+// dynamic LDS of the mode kernels: M accumulators of 13 sums
+static inline size_t mode_smem(int M) { return (size_t)13 * 8 * M; }
+
+__device__ __forceinline__ uint32_t spread3(uint32_t v)   // 7 bits, two zeros after each
 {
-    int32_t *X = (int32_t *)smem;
-    int32_t *Y = X + cap;
-    int32_t *Z = Y + cap;
-    int32_t *rho = Z + cap;
-    int32_t *par = rho + cap;
-    int32_t *size = par + cap;
-    uint32_t *col = (uint32_t *)(size + cap);
-    __shared__ int32_t cand_root[MAX_R];
-    __shared__ int32_t n_cand;
-    __shared__ unsigned long long acc[MAX_M][13];
-    __shared__ int32_t n_modes;
-    const int tid = threadIdx.x;
-    for (int i = tid; i < n; i += MODE_THREADS) {
-        Entry e = pts[i];
-        X[i] = e.x; Y[i] = e.y; Z[i] = e.z; col[i] = e.rgb;
-        size[i] = 0;
+    v = (v | (v << 8)) & 0x0000F00Fu;
+    v = (v | (v << 4)) & 0x000C30C3u;
+    return (v | (v << 2)) & 0x00249249u;
+}
+
+__device__ __forceinline__ i16x2 as_i16x2(uint32_t v) { return __builtin_bit_cast(i16x2, v); }
+__device__ __forceinline__ uint32_t as_u32(i16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+
+// squared distance of two points given as (xy, z)
+__device__ __forceinline__ uint32_t near_d2(uint32_t axy, uint32_t az, uint32_t bxy, uint32_t bz)
+{
+    const i16x2 d = as_i16x2(axy) - as_i16x2(bxy);
+    const int32_t dz = (int32_t)(az - bz);
+    return (uint32_t)__builtin_amdgcn_sdot2(d, d, __mul24(dz, dz), false);
+}
+
+// squared gap between two bounds (lo xy, hi xy, lo z, hi z)
+__device__ __forceinline__ uint32_t box_gap2(uint4 a, uint4 b)
+{
+    const i16x2 zero = {0, 0};
+    const i16x2 g = __builtin_elementwise_max(
+        __builtin_elementwise_max(as_i16x2(a.x) - as_i16x2(b.y), as_i16x2(b.x) - as_i16x2(a.y)), zero);
+    const i16x2 h = __builtin_elementwise_max(
+        __builtin_elementwise_max(as_i16x2(a.z) - as_i16x2(b.w), as_i16x2(b.z) - as_i16x2(a.w)), zero);
+    return (uint32_t)__builtin_amdgcn_sdot2(g, g, __builtin_amdgcn_sdot2(h, h, 0, false), false);
+}
+
+// one bitonic step at distance 4 M keys (lane ^ M) over a thread's four keys
+// (key i = 4 tid + e in register e), for the merge of size k
+template <int M>
+__device__ __forceinline__ void mode_sort_lanes(uint32_t v[4], int tid, int k)
+{
+    const bool lower = ((tid & M) == 0) == (((4 * tid) & k) == 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t o = xor_lane<M>(v[e]);
+        v[e] = lower ? min(v[e], o) : max(v[e], o);
     }
-    if (tid == 0) n_cand = 0;
-    for (int i = tid; i < MAX_M * 13; i += MODE_THREADS) acc[i / 13][i % 13] = 0ull;
+}
+
+__device__ __forceinline__ void mode_sort_pair(uint32_t &a, uint32_t &b, bool asc)
+{
+    const uint32_t lo = min(a, b), hi = max(a, b);
+    a = asc ? lo : hi;
+    b = asc ? hi : lo;
+}
+
+// ascending bitonic sort of the first `len` keys (a power of two, 4 at
+// least), key i = 4 tid + e in register e; distances of 256 keys and more go
+// through `ex` between barriers
+__device__ __forceinline__ void mode_sort(uint32_t v[4], int len, int tid, uint32_t *ex)
+{
+    {
+        const bool asc = (tid & 1) == 0;   // bit 4 of the key index
+        mode_sort_pair(v[0], v[1], true);
+        mode_sort_pair(v[2], v[3], false);
+        mode_sort_pair(v[0], v[2], asc);
+        mode_sort_pair(v[1], v[3], asc);
+        mode_sort_pair(v[0], v[1], asc);
+        mode_sort_pair(v[2], v[3], asc);
+    }
+    for (int k = 8; k <= len; k <<= 1) {
+        for (int j = k >> 1; j >= 256; j >>= 1) {
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ex[4 * tid + e] = v[e];
+            __syncthreads();
+            const bool lower = (((4 * tid) & j) == 0) == (((4 * tid) & k) == 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t o = ex[(4 * tid + e) ^ j];
+                v[e] = lower ? min(v[e], o) : max(v[e], o);
+            }
+        }
+        if (k >= 256) mode_sort_lanes<32>(v, tid, k);
+        if (k >= 128) mode_sort_lanes<16>(v, tid, k);
+        if (k >= 64) mode_sort_lanes<8>(v, tid, k);
+        if (k >= 32) mode_sort_lanes<4>(v, tid, k);
+        if (k >= 16) mode_sort_lanes<2>(v, tid, k);
+        mode_sort_lanes<1>(v, tid, k);
+        const bool asc = ((4 * tid) & k) == 0;
+        mode_sort_pair(v[0], v[2], asc);
+        mode_sort_pair(v[1], v[3], asc);
+        mode_sort_pair(v[0], v[1], asc);
+        mode_sort_pair(v[2], v[3], asc);
+    }
+}
+
+// Density and parent of every point by the tiled search: the points are
+// sorted along a Morton curve, a wavefront takes 64 consecutive points (one a
+// lane) and meets only those groups of 8 whose bounds come within the radius
+// of its own, whose points it reads from LDS at one address for all lanes. On
+// a full-size forest a third of all pairs is left (5 % are within 5 cm, 11 %
+// within 10 cm), at 6 (density) and 9 (parent) VALU instructions a pair
+// against about 33 for the branching plain search: k_modes of the 200-frame
+// full-size forest took 64.5 ms with that and takes 7.3 ms with this.
+// Groups of 16 leave 6 % more pairs; tiles of 32 points would leave a quarter
+// but need two lists a wavefront. x0, y0, z0: the leaf's minimum; shift: cells
+// of 2^shift mm, 128 an axis at most.
+__device__ __forceinline__ void near_search(ModeLds &S, const Entry (&mine)[4], int n, const ModeParams mp, int x0, int y0, int z0,
+                            int shift)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n64 = (n + 63) & ~63, nt = (n + 7) >> 3;
+    {
+        uint32_t v[4];
+        u32x4_t p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 4 * tid + e;
+            const uint32_t x = (uint32_t)(mine[e].x - x0), y = (uint32_t)(mine[e].y - y0),
+                           z = (uint32_t)(mine[e].z - z0);
+            p[e] = u32x4_t{x | (y << 16), z, (uint32_t)i << 22, 0u};
+            v[e] = i < n ? ((spread3(x >> shift) << 2 | spread3(y >> shift) << 1 | spread3(z >> shift)) << 10) |
+                               (uint32_t)i
+                         : 0xFFFFFFFFu;
+            if (i < n) S.pt[i] = p[e];
+        }
+        // up to 64 points are one tile: their order does not matter
+        if (n > 64) {
+            int len = 128;
+            while (len < n) len <<= 1;
+            mode_sort(v, len, tid, (uint32_t *)S.par);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (4 * tid + e < n) p[e] = S.pt[v[e] & 1023u];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 4 * tid + e;
+            if (i < n) S.pt[i] = p[e];
+            else if (i < n64)
+                S.pt[i] = u32x4_t{(uint32_t)(NEAR_PAD & 0xFFFF) * 0x10001u, (uint32_t)NEAR_PAD, 0u, 0u};
+        }
+    }
     __syncthreads();
+    if (tid < nt) {
+        i16x2 lo, hi, lz, hz;
+        for (int q = 0; q < 8; ++q) {
+            const int i = 8 * tid + q;
+            const u32x2_t p = *(const u32x2_t *)&S.pt[i < n ? i : n - 1];
+            const i16x2 xy = as_i16x2(p.x), z = as_i16x2(p.y);
+            lo = q ? __builtin_elementwise_min(lo, xy) : xy;
+            hi = q ? __builtin_elementwise_max(hi, xy) : xy;
+            lz = q ? __builtin_elementwise_min(lz, z) : z;
+            hz = q ? __builtin_elementwise_max(hz, z) : z;
+        }
+        S.box[tid] = make_uint4(as_u32(lo), as_u32(hi), as_u32(lz), as_u32(hz));
+    }
+    __syncthreads();
+    const uint32_t rd2 = (uint32_t)(mp.rd * mp.rd), rl2 = (uint32_t)(mp.rl * mp.rl);
+    for (int pass = 0; pass < 2; ++pass) {
+        const uint32_t r2 = pass ? rl2 : rd2;
+        for (int b = 64 * wave; b < n; b += MODE_THREADS) {
+            uint4 tb = S.box[b >> 3];
+            for (int q = 1; q < 8 && (b >> 3) + q < nt; ++q) {
+                const uint4 o = S.box[(b >> 3) + q];
+                tb.x = as_u32(__builtin_elementwise_min(as_i16x2(tb.x), as_i16x2(o.x)));
+                tb.y = as_u32(__builtin_elementwise_max(as_i16x2(tb.y), as_i16x2(o.y)));
+                tb.z = as_u32(__builtin_elementwise_min(as_i16x2(tb.z), as_i16x2(o.z)));
+                tb.w = as_u32(__builtin_elementwise_max(as_i16x2(tb.w), as_i16x2(o.w)));
+            }
+            const u32x4_t me = S.pt[b + lane];
+            uint32_t cnt = 0u, best = (rl2 + 1u) << 10;
+            for (int g = 0; g < nt; g += 64) {
+                uint64_t m = __ballot(g + lane < nt && box_gap2(tb, S.box[min(g + lane, nt - 1)]) <= r2);
+                while (m) {
+                    const u32x4_t *pp = S.pt + 8 * (g + __builtin_ctzll(m));
+                    m &= m - 1;
+                    if (!pass) {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            const u32x2_t w = *(const u32x2_t *)(pp + q);
+                            cnt += near_d2(me.x, me.y, w.x, w.y) <= rd2 ? 1u : 0u;
+                        }
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            const u32x4_t w = pp[q];
+                            // d2 << 10 | index: the nearest, then the lowest index
+                            const uint32_t c =
+                                __builtin_amdgcn_alignbit(min(near_d2(me.x, me.y, w.x, w.y), D2_CAP), w.z, 22);
+                            best = min(best, w.w < me.w ? c : 0xFFFFFFFFu);
+                        }
+                    }
+                }
+            }
+            const uint32_t i = me.z >> 22;
+            if (!pass) {
+                // the padding comes before no point; other wavefronts only read x, y and z in this pass
+                ((uint32_t *)&S.pt[b + lane])[3] = b + lane < n ? ((2047u - cnt) << 10) | i : 0xFFFFFFFFu;
+            } else if (b + lane < n) {
+                S.par[i] = best < ((rl2 + 1u) << 10) ? (int32_t)(best & 1023u) : -1;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// the same over all pairs, for any coordinates and radii
+__device__ __forceinline__ void plain_search(ModeLds &S, const Entry *__restrict__ pts, int n, const ModeParams mp)
+{
+    int32_t *rho = (int32_t *)S.pt;
     const int rd = mp.rd, rl = mp.rl;
     const int rd2 = rd * rd, rl2 = rl * rl;
-    for (int i = tid; i < n; i += MODE_THREADS) {
-        int xi = X[i], yi = Y[i], zi = Z[i], cnt = 0;
+    for (int i = threadIdx.x; i < n; i += MODE_THREADS) {
+        const int xi = pts[i].x, yi = pts[i].y, zi = pts[i].z;
+        int cnt = 0;
         for (int j = 0; j < n; ++j) {
-            int dx = X[j] - xi, dy = Y[j] - yi, dz = Z[j] - zi;
+            const int dx = pts[j].x - xi, dy = pts[j].y - yi, dz = pts[j].z - zi;
             if (abs(dx) <= rd && abs(dy) <= rd && abs(dz) <= rd && dx * dx + dy * dy + dz * dz <= rd2) cnt++;
         }
         rho[i] = cnt;
     }
     __syncthreads();
-    for (int i = tid; i < n; i += MODE_THREADS) {
-        int xi = X[i], yi = Y[i], zi = Z[i], ri = rho[i];
+    for (int i = threadIdx.x; i < n; i += MODE_THREADS) {
+        const int xi = pts[i].x, yi = pts[i].y, zi = pts[i].z, ri = rho[i];
         int best = -1, bd = 0;
         for (int j = 0; j < n; ++j) {
-            int dx = X[j] - xi, dy = Y[j] - yi, dz = Z[j] - zi;
+            const int dx = pts[j].x - xi, dy = pts[j].y - yi, dz = pts[j].z - zi;
             if (abs(dx) > rl || abs(dy) > rl || abs(dz) > rl) continue;
-            int d2 = dx * dx + dy * dy + dz * dz;
+            const int d2 = dx * dx + dy * dy + dz * dz;
             if (d2 > rl2 || j == i) continue;
-            int rj = rho[j];
+            const int rj = rho[j];
             if (!(rj > ri || (rj == ri && j < i))) continue;
             if (best < 0 || d2 < bd || (d2 == bd && j < best)) {
                 best = j;
                 bd = d2;
             }
         }
-        par[i] = best;
+        S.par[i] = best;
     }
     __syncthreads();
+}
+
+// One workgroup per leaf. Density and parent are exact integer comparisons
+// (near_search or plain_search); clusters are the trees of the parent forest
+// (roots by pointer jumping); clusters of at least `minc` points are ranked by
+// (size descending, root ascending) and the first M become modes. Sums are
+// exact integers relative to the leaf's minimum (modulo 2^64, as the
+// covariance's numerator is), so their order does not matter.
+__device__ __forceinline__ void leaf_modes(const Entry *__restrict__ pts, int n, const ModeParams mp, Mode *__restrict__ out,
+                           uint32_t *__restrict__ rgb_out, int rgb_len, int32_t *__restrict__ n_out, ModeLds &S,
+                           unsigned long long (*acc)[13])
+{
+    const int tid = threadIdx.x;
+    if (n < mp.minc) {   // too few points for any cluster to be kept
+        if (rgb_out && tid < rgb_len) rgb_out[tid] = RGB_NONE;
+        if (tid == 0) *n_out = 0;
+        return;
+    }
+    Entry mine[4];       // points 4 tid .. + 3
+    int lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = 4 * tid + e;
+        mine[e] = i < n ? pts[i] : Entry{0, 0, 0, 0u};
+        if (i < n) {
+            lo[0] = min(lo[0], mine[e].x); hi[0] = max(hi[0], mine[e].x);
+            lo[1] = min(lo[1], mine[e].y); hi[1] = max(hi[1], mine[e].y);
+            lo[2] = min(lo[2], mine[e].z); hi[2] = max(hi[2], mine[e].z);
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        for (int o = 32; o >= 1; o >>= 1) {
+            lo[a] = min(lo[a], __shfl_xor(lo[a], o, 64));
+            hi[a] = max(hi[a], __shfl_xor(hi[a], o, 64));
+        }
+        if ((tid & 63) == 0) {
+            S.red[tid >> 6][a] = lo[a];
+            S.red[tid >> 6][3 + a] = hi[a];
+        }
+    }
+    if (tid == 0) S.n_cand = 0;
+    for (int i = tid; i < mp.M * 13; i += MODE_THREADS) acc[i / 13][i % 13] = 0ull;
+    __syncthreads();
+    int64_t ext = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = S.red[0][a];
+        hi[a] = S.red[0][3 + a];
+        for (int w = 1; w < MODE_THREADS / 64; ++w) {
+            lo[a] = min(lo[a], S.red[w][a]);
+            hi[a] = max(hi[a], S.red[w][3 + a]);
+        }
+        ext = max(ext, (int64_t)hi[a] - (int64_t)lo[a]);
+    }
+    if (ext <= NEAR_EXTENT && mp.rd <= NEAR_RADIUS && mp.rl <= NEAR_RADIUS) {
+        int shift = 4;
+        while ((ext >> shift) > 127) ++shift;
+        near_search(S, mine, n, mp, lo[0], lo[1], lo[2], shift);
+    } else {
+        plain_search(S, pts, n, mp);
+    }
     // pointer jumping: par[i] becomes the root of i
     for (int it = 0; it < 13; ++it) {
+        bool moved = false;
         for (int i = tid; i < n; i += MODE_THREADS) {
-            int a = par[i];
+            const int a = S.par[i];
             if (a >= 0) {
-                int b = par[a];
-                if (b >= 0) par[i] = b;
+                const int b = S.par[a];
+                if (b >= 0) {
+                    S.par[i] = b;
+                    moved = true;
+                }
             }
         }
-        __syncthreads();
+        if (!__syncthreads_or(moved)) break;
     }
+    uint32_t *size = (uint32_t *)S.pt, *cand_root = size + MAX_R;
+    for (int i = tid; i < n; i += MODE_THREADS) size[i] = 0u;
+    __syncthreads();
     for (int i = tid; i < n; i += MODE_THREADS) {
-        int r = par[i] < 0 ? i : par[i];
-        atomicAdd(&size[r], 1);
+        const int r = S.par[i];
+        atomicAdd(&size[r < 0 ? i : r], 1u);
     }
     __syncthreads();
     for (int i = tid; i < n; i += MODE_THREADS)
-        if (par[i] < 0 && size[i] >= mp.minc) {
-            int k = atomicAdd(&n_cand, 1);
-            cand_root[k] = i;
-        }
+        if (S.par[i] < 0 && size[i] >= (uint32_t)mp.minc) cand_root[atomicAdd(&S.n_cand, 1)] = (uint32_t)i;
     __syncthreads();
-    // rank candidates by (size desc, root asc); rank < M becomes the mode slot
-    // (stored in rho[], which is no longer needed)
-    int nc = n_cand;
-    for (int i = tid; i < n; i += MODE_THREADS) rho[i] = -1;
-    __syncthreads();
+    // rank candidates by (size desc, root asc); a rank below M is the mode
+    // slot, kept as -2 - rank in the root's parent word (roots hold -1)
+    const int nc = S.n_cand;
     for (int a = tid; a < nc; a += MODE_THREADS) {
-        int ra = cand_root[a], sa = size[ra], rank = 0;
+        const int ra = (int)cand_root[a];
+        const uint32_t sa = size[ra];
+        int rank = 0;
         for (int b = 0; b < nc; ++b) {
-            int rb = cand_root[b], sb = size[rb];
+            const int rb = (int)cand_root[b];
+            const uint32_t sb = size[rb];
             if (sb > sa || (sb == sa && rb < ra)) rank++;
         }
-        if (rank < mp.M) rho[ra] = rank;
+        if (rank < mp.M) S.par[ra] = -2 - rank;
     }
-    if (tid == 0) n_modes = nc < mp.M ? nc : mp.M;
     __syncthreads();
-    for (int i = tid; i < n; i += MODE_THREADS) {
-        int r = par[i] < 0 ? i : par[i];
-        int m = rho[r];
+    const int nm = nc < mp.M ? nc : mp.M;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = 4 * tid + e;
+        if (i >= n) continue;
+        const int r = S.par[i];
+        const int m = -2 - (r < 0 ? r : S.par[r]);
         if (m < 0) continue;
-        int64_t x = X[i], y = Y[i], z = Z[i];
-        uint32_t cl = col[i];
-        atomicAdd(&acc[m][0], (unsigned long long)x);
-        atomicAdd(&acc[m][1], (unsigned long long)y);
-        atomicAdd(&acc[m][2], (unsigned long long)z);
-        atomicAdd(&acc[m][3], (unsigned long long)(x * x));
-        atomicAdd(&acc[m][4], (unsigned long long)(x * y));
-        atomicAdd(&acc[m][5], (unsigned long long)(x * z));
-        atomicAdd(&acc[m][6], (unsigned long long)(y * y));
-        atomicAdd(&acc[m][7], (unsigned long long)(y * z));
-        atomicAdd(&acc[m][8], (unsigned long long)(z * z));
+        const unsigned long long x = (uint32_t)mine[e].x - (uint32_t)lo[0], y = (uint32_t)mine[e].y - (uint32_t)lo[1],
+                                 z = (uint32_t)mine[e].z - (uint32_t)lo[2];
+        const uint32_t cl = mine[e].rgb;
+        atomicAdd(&acc[m][0], x);
+        atomicAdd(&acc[m][1], y);
+        atomicAdd(&acc[m][2], z);
+        atomicAdd(&acc[m][3], x * x);
+        atomicAdd(&acc[m][4], x * y);
+        atomicAdd(&acc[m][5], x * z);
+        atomicAdd(&acc[m][6], y * y);
+        atomicAdd(&acc[m][7], y * z);
+        atomicAdd(&acc[m][8], z * z);
         atomicAdd(&acc[m][9], (unsigned long long)(cl & 255u));
         atomicAdd(&acc[m][10], (unsigned long long)((cl >> 8) & 255u));
         atomicAdd(&acc[m][11], (unsigned long long)((cl >> 16) & 255u));
         atomicAdd(&acc[m][12], 1ull);
     }
     __syncthreads();
-    int nm = n_modes;
     if (tid < nm) {
         const unsigned long long *a = acc[tid];
-        int64_t Sx[3] = {(int64_t)a[0], (int64_t)a[1], (int64_t)a[2]};
-        int64_t Sxx[6] = {(int64_t)a[3], (int64_t)a[4], (int64_t)a[5], (int64_t)a[6], (int64_t)a[7], (int64_t)a[8]};
-        int64_t nmm = (int64_t)a[12];
+        const uint64_t nmm = a[12];
         Mode md;
         double dn = (double)nmm;
-        for (int k = 0; k < 3; ++k) md.mu[k] = (float)((double)Sx[k] / (dn * 1000.0));
+        for (int k = 0; k < 3; ++k) md.mu[k] = (float)((double)(int64_t)(a[k] + nmm * (uint64_t)(int64_t)lo[k]) / (dn * 1000.0));
         const int ia[6] = {0, 0, 0, 1, 1, 2}, ib[6] = {0, 1, 2, 1, 2, 2};
-        double S[6];
+        double S6[6];
         for (int e = 0; e < 6; ++e) {
-            int64_t num = nmm * Sxx[e] - Sx[ia[e]] * Sx[ib[e]];
+            const int64_t num = (int64_t)(nmm * a[3 + e] - a[ia[e]] * a[ib[e]]);
             double cv = (double)num / (dn * dn);
             if (ia[e] == ib[e]) cv = cv + (double)mp.reg;
-            S[e] = cv * 1e-6;
+            S6[e] = cv * 1e-6;
         }
-        double A = S[0], B = S[1], Cc = S[2], Dd = S[3], E = S[4], G = S[5];
+        double A = S6[0], B = S6[1], Cc = S6[2], Dd = S6[3], E = S6[4], G = S6[5];
         double A00 = Dd * G - E * E;
         double A01 = Cc * E - B * G;
         double A02 = B * E - Cc * Dd;
@@ -628,42 +906,52 @@ __device__ void leaf_modes(const Entry *__restrict__ pts, int n, int n_total, in
         md.sinv[3] = (float)(A11 / det);
         md.sinv[4] = (float)(A12 / det);
         md.sinv[5] = (float)(A22 / det);
-        md.kappa = (float)(-log(dn / (double)n_total) + 0.5 * (3.0 * log(2.0 * M_PI) + log(det)));
+        md.kappa = (float)(-log(dn / (double)n) + 0.5 * (3.0 * log(2.0 * M_PI) + log(det)));
         md.n = (int32_t)nmm;
-        md.rgb = (uint32_t)(a[9] / (unsigned long long)nmm) | ((uint32_t)(a[10] / (unsigned long long)nmm) << 8) |
-                 ((uint32_t)(a[11] / (unsigned long long)nmm) << 16);
+        md.rgb = (uint32_t)(a[9] / nmm) | ((uint32_t)(a[10] / nmm) << 8) | ((uint32_t)(a[11] / nmm) << 16);
         out[tid] = md;
         if (rgb_out) rgb_out[tid] = md.rgb;
     } else if (rgb_out && tid < rgb_len) {
         rgb_out[tid] = RGB_NONE;
     }
     if (tid == 0) *n_out = nm;
-    __syncthreads();
 }
 
-// persistent over the dirty-leaf list; also refreshes each leaf's summary
-// for the learned proposal's inputs: {min(k, R), number of modes kept (<= 3)}
-// and, for its first three modes (the heaviest: modes are ranked by size),
+// Leaves of the dirty list, handed out by a ticket (work[1]) since their
+// point counts differ by three orders of magnitude; work[0] is the list's
+// length. Clears each leaf's dirty flag and refreshes its summary for the
+// learned proposal's inputs: {min(k, R), number of modes kept (<= 3)} and, for
+// its first three modes (the heaviest: modes are ranked by size),
 // {pi = n / min(k, R), -log(Sigma^-1_xx) / 10, -log(Sigma^-1_yy) / 10,
 // -log(Sigma^-1_zz) / 10}
-__global__ void __launch_bounds__(MODE_THREADS) k_modes(const uint32_t *__restrict__ list,
-                                                        const uint32_t *__restrict__ count,
+__global__ void __launch_bounds__(MODE_THREADS, 6) k_modes(const uint32_t *__restrict__ list,
+                                                        uint32_t *__restrict__ work,
+                                                        uint32_t *__restrict__ dirty,
                                                         const uint32_t *__restrict__ counter,
                                                         const Entry *__restrict__ res, ModeParams mp,
                                                         Mode *__restrict__ modes, uint32_t *__restrict__ mode_rgb,
                                                         int32_t *__restrict__ nmodes, float4 *__restrict__ leaf_in)
 {
-    extern __shared__ char smem[];
-    uint32_t n_list = *count;
-    for (uint32_t it = blockIdx.x; it < n_list; it += gridDim.x) {
-        uint32_t li = list[it];
-        uint32_t k = counter[li];
-        int n = k < (uint32_t)mp.R ? (int)k : mp.R;
+    extern __shared__ unsigned long long mode_acc[];
+    __shared__ ModeLds S;
+    const int tid = (int)threadIdx.x;
+    const uint32_t n_list = work[0];
+    uint32_t it = blockIdx.x;
+    while (it < n_list) {
+        uint32_t ahead = 0u;   // the next ticket, asked for before this leaf's work
+        if (tid == 0) ahead = atomicAdd(&work[1], 1u);
+        const uint32_t li = list[it];
+        const uint32_t k = counter[li];
+        const int n = k < (uint32_t)mp.R ? (int)k : mp.R;
         const int ms = rgb_stride(mp.M);
-        leaf_modes(res + (int64_t)li * mp.R, n, n, mp.R, mp, modes + (int64_t)li * mp.M, mode_rgb + (int64_t)li * ms, ms,
-                   nmodes + li, smem);
-        // leaf_modes ends with a barrier: the modes and their count are visible
-        const int tid = (int)threadIdx.x;
+        leaf_modes(res + (int64_t)li * mp.R, n, mp, modes + (int64_t)li * mp.M, mode_rgb + (int64_t)li * ms, ms,
+                   nmodes + li, S, (unsigned long long(*)[13])mode_acc);
+        if (tid == 0) {
+            S.next = gridDim.x + ahead;
+            dirty[li] = 0u;
+        }
+        __syncthreads();   // the modes, their count and the next ticket are visible
+        it = S.next;
         if (tid < 4) {
             const int nm = nmodes[li];
             const int n3 = nm < 3 ? nm : 3;
@@ -680,24 +968,22 @@ __global__ void __launch_bounds__(MODE_THREADS) k_modes(const uint32_t *__restri
             }
             leaf_in[(int64_t)li * 4 + tid] = q;
         }
-        __syncthreads();
+        __syncthreads();   // S is the next leaf's
     }
 }
 
-__global__ void k_modes_done(const uint32_t *__restrict__ list, uint32_t *__restrict__ count,
-                             uint32_t *__restrict__ dirty)
+// the dirty list is empty again
+__global__ void k_modes_done(uint32_t *__restrict__ work)
 {
-    uint32_t n = *count;
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) dirty[list[i]] = 0u;
-    __syncthreads();
-    if (threadIdx.x == 0) *count = 0u;
+    work[threadIdx.x] = 0u;
 }
 
 __global__ void __launch_bounds__(MODE_THREADS) k_modes_points(const Entry *__restrict__ pts, int n, ModeParams mp,
                                                                Mode *__restrict__ out, int32_t *__restrict__ n_out)
 {
-    extern __shared__ char smem[];
-    leaf_modes(pts, n, n, n, mp, out, nullptr, 0, n_out, smem);
+    extern __shared__ unsigned long long mode_acc[];
+    __shared__ ModeLds S;
+    leaf_modes(pts, n, mp, out, nullptr, 0, n_out, S, (unsigned long long(*)[13])mode_acc);
 }
 
 static ModeParams mode_params(const Forest *f)
@@ -748,10 +1034,10 @@ int update_modes(Forest *f, hipStream_t s)
     if (!f->maybe_dirty) return RELOC_OK;
     if (!f->res) return RELOC_E_STATE;
     ModeParams mp = mode_params(f);
-    int grid = std::min(f->T * f->L, 4096);
-    RL_LAUNCH("k_modes", k_modes, dim3(grid), dim3(MODE_THREADS), mode_smem(f->R), s, f->dirty_list, f->dirty_count,
-                       f->counter, f->res, mp, f->modes, f->mode_rgb, f->nmodes, f->leaf_in);
-    RL_LAUNCH("k_modes_done", k_modes_done, dim3(1), dim3(1024), 0, s, f->dirty_list, f->dirty_count, f->dirty);
+    int grid = std::min(f->T * f->L, 256 * 8);
+    RL_LAUNCH("k_modes", k_modes, dim3(grid), dim3(MODE_THREADS), mode_smem(f->M), s, f->dirty_list, f->dirty_count,
+                       f->dirty, f->counter, f->res, mp, f->modes, f->mode_rgb, f->nmodes, f->leaf_in);
+    RL_LAUNCH("k_modes_done", k_modes_done, dim3(1), dim3(2), 0, s, f->dirty_count);
     RL_HIP(hipGetLastError());
     f->maybe_dirty = false;
     return RELOC_OK;
@@ -790,7 +1076,7 @@ int forest_empty_leaves(Forest *f, hipStream_t s)
         hipMemsetAsync(f->mode_rgb, 0xFF, TL * rgb_stride(f->M) * sizeof(uint32_t), s) != hipSuccess ||
         hipMemsetAsync(f->leaf_in, 0, TL * 4 * sizeof(float4), s) != hipSuccess ||
         hipMemsetAsync(f->dirty, 0, TL * sizeof(uint32_t), s) != hipSuccess ||
-        hipMemsetAsync(f->dirty_count, 0, sizeof(uint32_t), s) != hipSuccess ||
+        hipMemsetAsync(f->dirty_count, 0, 2 * sizeof(uint32_t), s) != hipSuccess ||
         hipMemsetAsync(f->total_samples, 0, sizeof(unsigned long long), s) != hipSuccess)
         return RELOC_E_HIP;
     f->maybe_dirty = false;
@@ -843,7 +1129,7 @@ static void forest_free(Forest *f)
     dfree(f, &f->nmodes, TL);
     dfree(f, &f->dirty, TL);
     dfree(f, &f->dirty_list, TL);
-    dfree(f, &f->dirty_count, 1);
+    dfree(f, &f->dirty_count, 2);
     dfree(f, &f->total_samples, 1);
     dfree(f, &f->leaves, (size_t)f->T * f->cap_P);
     dfree(f, &f->packed, (size_t)f->cap_P);
@@ -880,7 +1166,7 @@ extern "C" int reloc_forest_create(const reloc_params *p, void *stream, reloc_fo
     rc |= dalloc(f, &f->nmodes, TL, s);
     rc |= dalloc(f, &f->dirty, TL, s);
     rc |= dalloc(f, &f->dirty_list, TL, s);
-    rc |= dalloc(f, &f->dirty_count, 1, s);
+    rc |= dalloc(f, &f->dirty_count, 2, s);
     rc |= dalloc(f, &f->total_samples, 1, s);
     rc |= dalloc(f, &f->mode_rgb, TL * rgb_stride(f->M), s);
     rc |= dalloc(f, &f->leaf_in, TL * 4, s);
@@ -896,7 +1182,7 @@ extern "C" int reloc_forest_create(const reloc_params *p, void *stream, reloc_fo
         hipMemsetAsync(f->mode_rgb, 0xFF, TL * rgb_stride(f->M) * sizeof(uint32_t), s) != hipSuccess ||
         hipMemsetAsync(f->leaf_in, 0, TL * 4 * sizeof(float4), s) != hipSuccess ||
         hipMemsetAsync(f->dirty, 0, TL * sizeof(uint32_t), s) != hipSuccess ||
-        hipMemsetAsync(f->dirty_count, 0, sizeof(uint32_t), s) != hipSuccess ||
+        hipMemsetAsync(f->dirty_count, 0, 2 * sizeof(uint32_t), s) != hipSuccess ||
         hipMemsetAsync(f->total_samples, 0, sizeof(unsigned long long), s) != hipSuccess) {
         forest_free(f);
         delete f;
@@ -1320,7 +1606,7 @@ extern "C" int reloc_debug_modes_from_points(reloc_forest *f, const void *entrie
         rc = RELOC_E_HIP;
     if (!rc) {
         ModeParams mp = mode_params(f);
-        RL_LAUNCH("k_modes_points", k_modes_points, dim3(1), dim3(MODE_THREADS), mode_smem(n), 0, d_pts, (int)n, mp, d_modes,
+        RL_LAUNCH("k_modes_points", k_modes_points, dim3(1), dim3(MODE_THREADS), mode_smem(mp.M), 0, d_pts, (int)n, mp, d_modes,
                            d_n);
         if (hipDeviceSynchronize() != hipSuccess ||
             hipMemcpy(n_modes_host, d_n, sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess ||
