@@ -249,8 +249,8 @@ typedef struct {
  * deviation of its training samples' world points (integer mm, as adaptation
  * stores them) from their child's mean, ties to the lower candidate; a
  * sample is every stride-th pixel in u and v, from stride / 2, of every
- * frame with a valid depth. Synchronous on `stream` (it reads per-level
- * sample counts back); allocates its scratch with hipMallocAsync on
+ * frame with a valid depth. Synchronous on `stream` (it reads the
+ * sample count back); allocates its scratch with hipMallocAsync on
  * `stream` and frees it before returning. Errors: RELOC_E_ARG (null
  * pointers, n_frames < 1, stride < 1, n_candidates outside 1..64, a frame
  * the forest rejects, a pose that is not a rigid motion), RELOC_E_RANGE
