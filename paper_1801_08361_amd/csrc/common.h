@@ -297,12 +297,74 @@ constexpr int TOP_NODES = 1023;   // levels 0..9, 32 KB prepared
 // 0-15 hold 65535 - z, where z is the depth, or 65535 outside the valid
 // range (the host keeps the range below 65535), so an invalid pixel's field
 // is 0; bits 16-31, 32-47 and 48-63 hold 255 - r, 255 - g and 255 - b.
+// A packed frame holds its P words and, behind them, the same fields in
+// planes for the probes: [H][4][W] 16-bit fields, a row of each field after
+// the other. A cache line then holds 64 neighbouring pixels' fields of the one
+// kind a node asks for, where the words' would hold 16 pixels'. The gathers
+// of the deep levels bound the traversal: 32 frames of 640 x 480 in 5 trees of
+// depth 15 took 1331 us from the words and take 1104 from the planes, one such
+// frame 41.8 and 38.4, 64 frames of mixed sizes in trees of depth 10 572 and
+// 560; a lone 320 x 240 frame, which waits for its chain of levels, 12.7 and
+// 13.3.
 __device__ __forceinline__ uint64_t pack_pixel(const Frame &fr, int64_t p)
 {
     const uint32_t d = fr.depth[p];
     const uint64_t z = valid_depth(fr, d) ? (uint64_t)(65535u - d) : 0ull;
     return z | ((uint64_t)(255u - fr.rgb[p * 3]) << 16) | ((uint64_t)(255u - fr.rgb[p * 3 + 1]) << 32) |
            ((uint64_t)(255u - fr.rgb[p * 3 + 2]) << 48);
+}
+
+constexpr int PACKED_WORDS = 2;   // 8-byte words of a packed frame per pixel
+
+// Pixels p .. p + 3 (p a multiple of 4) into the packed frame of P = W H
+// pixels, their words returned (0 past the frame's end). Frames of a width
+// that is a multiple of 4 are read and written 4 pixels at a time: such pixels
+// lie in one row, and their places in the words and planes are 8-byte aligned;
+// the frame itself may lie at any address (its loads say so).
+__device__ __forceinline__ void pack_pixels4(const Frame &fr, uint64_t RL_GLOBAL *packed, int P, int p, uint64_t w[4])
+{
+    const int W = fr.W;
+    if ((W & 3) == 0) {
+        if (p >= P) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = 0ull;
+            return;
+        }
+        typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+        typedef uint32_t u32_any __attribute__((aligned(1)));
+        const u32x2_any d = *(const u32x2_any RL_GLOBAL *)(fr.depth + p);
+        uint32_t c[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[k] = *(const u32_any RL_GLOBAL *)(fr.rgb + 3 * p + 4 * k);
+        uint64_t plane[4] = {0ull, 0ull, 0ull, 0ull};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t z = (e & 1 ? d[e >> 1] >> 16 : d[e >> 1]) & 0xFFFFu;
+            uint64_t f[4];
+            f[0] = valid_depth(fr, z) ? (uint64_t)(65535u - z) : 0ull;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) f[1 + k] = 255u - ((c[(3 * e + k) >> 2] >> (8 * ((3 * e + k) & 3))) & 0xFFu);
+            w[e] = f[0] | (f[1] << 16) | (f[2] << 32) | (f[3] << 48);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) plane[k] |= f[k] << (16 * e);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) packed[p + e] = w[e];
+        uint64_t RL_GLOBAL *f = packed + P + (3 * (p / W) * W + p) / 4;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k * (W / 4)] = plane[k];
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        w[e] = p + e < P ? pack_pixel(fr, p + e) : 0ull;
+        if (p + e < P) {
+            packed[p + e] = w[e];
+            uint16_t RL_GLOBAL *f = (uint16_t RL_GLOBAL *)(packed + P) + (3 * ((p + e) / W) * W + p + e);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f[k * W] = (uint16_t)(w[e] >> (16 * k));
+        }
+    }
 }
 
 __device__ __forceinline__ bool packed_valid(uint64_t w) { return (w & 0xFFFFull) != 0ull; }
@@ -324,11 +386,11 @@ struct ProbeNode {
     uint32_t sxy;      // signs of dx Fx (bits 0-15) and dy Fy (bits 16-31) as 16-bit +1 or -1
     uint32_t spare;
     int32_t thr;
-    uint32_t sh;       // bits 0-5: 16 kind, the field's bit position in the word (bits 0-4: in its
-                       // 32-bit half); higher bits are not read
-    uint32_t half;     // byte offset of the field's 32-bit half in the word (0 or 4)
-    uint32_t wout;     // width the field is read with when the probe leaves the image: 0 for a depth
-                       // probe (no depth), 16 for a colour probe (the clamped pixel's colour)
+    uint32_t sh;       // bits 0-5: 16 kind, the field's bit position in the pixel's word; higher bits
+                       // are not read
+    uint32_t col;      // byte offset of the field's plane in a row of planes: kind 2 W
+    uint32_t out;      // mask of the field when the probe leaves the image: 0 for a depth probe (no
+                       // depth), 65535 for a colour probe (the clamped pixel's colour)
 };
 
 __device__ __forceinline__ ProbeNode probe_node(uint64_t w, const Frame &fr)
@@ -343,16 +405,15 @@ __device__ __forceinline__ ProbeNode probe_node(uint64_t w, const Frame &fr)
     n.spare = 0u;
     n.thr = thr;
     n.sh = 16u * (uint32_t)kind;
-    n.half = 2u * (uint32_t)(kind & 2);
-    n.wout = kind ? 16u : 0u;
+    n.col = 2u * (uint32_t)(kind * fr.W);
+    n.out = kind ? 0xFFFFu : 0u;
     return n;
 }
 
 // A split node as the deep levels of the traversal read it, 16 bytes that do
 // not depend on the frame: x and y hold 2 |dx| and 2 |dy| in bits 0-21 and
-// the offset's sign in bit 31; meta holds 16 kind in bits 0-5, the byte
-// offset of the field's 32-bit half (0 or 4) in bits 6-8 and the width the
-// field is read with outside the image (0 or 16) in bits 9-13.
+// the offset's sign in bit 31; meta holds 16 kind in bits 0-5 and the mask of
+// the field outside the image (0 or 65535) in bits 16-31.
 struct DeepNode {
     uint32_t x, y;
     int32_t thr;
@@ -367,7 +428,7 @@ __host__ __device__ __forceinline__ DeepNode deep_node(uint64_t w)
     d.x = ((uint32_t)(dx < 0 ? -dx : dx) << 1) | (dx < 0 ? 0x80000000u : 0u);
     d.y = ((uint32_t)(dy < 0 ? -dy : dy) << 1) | (dy < 0 ? 0x80000000u : 0u);
     d.thr = thr;
-    d.meta = 16u * (uint32_t)kind | ((kind & 2) ? 4u : 0u) << 6 | (kind ? 16u : 0u) << 9;
+    d.meta = 16u * (uint32_t)kind | (kind ? 0xFFFF0000u : 0u);
     return d;
 }
 
@@ -384,8 +445,8 @@ __device__ __forceinline__ ProbeNode probe_node_deep(const DeepNode &d, const Fr
     n.spare = 0u;
     n.thr = d.thr;
     n.sh = d.meta;
-    n.half = __builtin_amdgcn_ubfe(d.meta, 6, 3);
-    n.wout = __builtin_amdgcn_ubfe(d.meta, 9, 5);
+    n.col = __umul24(__builtin_amdgcn_ubfe(d.meta, 4, 2), 2u * (uint32_t)fr.W);
+    n.out = d.meta >> 16;
     return n;
 }
 
@@ -395,12 +456,13 @@ __device__ __forceinline__ void stage_top(ProbeNode *__restrict__ top, const uin
     for (int k = tid; k < ntop; k += nthreads) top[k] = probe_node(tree[k], fr);
 }
 
-// A buffer resource over a packed frame of P words (P < 2^26: the host keeps
-// width and height at most 8191): probe loads take a 32-bit byte offset from
-// it, and the hardware range-checks them against the P * 8 bytes.
+// A buffer resource over the planes of a packed frame of P pixels (P < 2^26:
+// the host keeps width and height at most 8191): probe loads take a 32-bit
+// byte offset from it, and the hardware range-checks them against the P * 8
+// bytes.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t packed_rsrc(const uint64_t *packed, int P)
 {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)packed, (short)0, P * 8, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(packed + P), (short)0, P * 8, 0x00020000);
 }
 
 typedef short i16x2 __attribute__((ext_vector_type(2)));
@@ -408,13 +470,17 @@ typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 
 // node_response_d of a prepared node, from the packed frame: `own` is the
 // pixel's own packed word. Branch-free: the probe position is clamped into
-// the image and the field's 32-bit half is loaded; a depth probe whose
-// position was clamped reads its field with width 0, that is as "no depth".
+// the image and the field is loaded from its plane; a depth probe whose
+// position was clamped has its field masked to 0, that is to "no depth".
 // Both coordinates are placed, clamped and turned into the byte offset
 // together as 16-bit lanes (x low, y high): the host keeps W and H below 8192
 // and every probe offset below 2^14, so u + o, v + o and 8 W fit the lanes.
-__device__ __forceinline__ int32_t probe_response(__amdgpu_buffer_rsrc_t packed, int W, int H, int u, int v,
-                                                  uint64_t own, const PixelDen &pd, const ProbeNode &n)
+struct Probe {
+    uint32_t at;       // byte of the field in the planes
+    uint32_t mask;
+};
+
+__device__ __forceinline__ Probe probe_place(int W, int H, int u, int v, const PixelDen &pd, const ProbeNode &n)
 {
     const uint32_t ox = div_mag2(n.ax, pd), oy = div_mag2(n.ay, pd);
     const i16x2 o = __builtin_bit_cast(i16x2, ox | (oy << 16));
@@ -423,14 +489,30 @@ __device__ __forceinline__ int32_t probe_response(__amdgpu_buffer_rsrc_t packed,
     const i16x2 zero = {0, 0};
     const i16x2 hi = __builtin_bit_cast(i16x2, (uint32_t)(W - 1) | ((uint32_t)(H - 1) << 16));
     const i16x2 c = __builtin_elementwise_min(__builtin_elementwise_max(q, zero), hi);
-    // (c.y W + c.x) 8 + half
-    const u16x2_t rowb = __builtin_bit_cast(u16x2_t, 8u | ((uint32_t)(8 * W) << 16));
-    const uint32_t at = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2_t, c), rowb, n.half, false);
-    const uint32_t word = __builtin_bit_cast(uint32_t, __builtin_amdgcn_raw_buffer_load_b32(packed, (int)at, 0, 0));
-    const uint32_t width = __builtin_bit_cast(uint32_t, q) != __builtin_bit_cast(uint32_t, c) ? n.wout : 16u;
-    const uint32_t probed = __builtin_amdgcn_ubfe(word, n.sh, width);
+    // c.y 8 W + c.x 2 + col
+    const u16x2_t rowb = __builtin_bit_cast(u16x2_t, 2u | ((uint32_t)(8 * W) << 16));
+    Probe p;
+    p.at = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2_t, c), rowb, n.col, false);
+    p.mask = __builtin_bit_cast(uint32_t, q) != __builtin_bit_cast(uint32_t, c) ? n.out : 0xFFFFu;
+    return p;
+}
+
+__device__ __forceinline__ uint32_t probe_load(__amdgpu_buffer_rsrc_t packed, const Probe &p)
+{
+    return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(packed, (int)p.at, 0, 0);
+}
+
+__device__ __forceinline__ int32_t probe_finish(uint32_t field, const Probe &p, uint64_t own, const ProbeNode &n)
+{
     const uint32_t mine = (uint32_t)(own >> (n.sh & 63u)) & 0xFFFFu;
-    return (int32_t)mine - (int32_t)probed;
+    return (int32_t)mine - (int32_t)(field & p.mask);
+}
+
+__device__ __forceinline__ int32_t probe_response(__amdgpu_buffer_rsrc_t packed, int W, int H, int u, int v,
+                                                  uint64_t own, const PixelDen &pd, const ProbeNode &n)
+{
+    const Probe p = probe_place(W, H, u, v, pd, n);
+    return probe_finish(probe_load(packed, p), p, own, n);
 }
 
 // Traversal of one tree for K pixels of a packed frame at once (their
@@ -461,13 +543,22 @@ __device__ __forceinline__ void traverse_packed_k(const ProbeNode *__restrict__ 
     const uint32_t otop = (uint32_t)ntop * 32u;
     const char *tb = (const char *)top;
     while (o[0] < otop) {
+        // all K probes are in flight before the first is waited for
+        ProbeNode n[K];
+        Probe pr[K];
+        uint32_t field[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const ProbeNode n = *(const ProbeNode *)__builtin_assume_aligned(tb + o[k], 32);
-            const int32_t r = probe_response(rs, fr.W, fr.H, u[k], v[k], own[k], pd[k], n);
+        for (int k = 0; k < K; ++k) n[k] = *(const ProbeNode *)__builtin_assume_aligned(tb + o[k], 32);
+#pragma unroll
+        for (int k = 0; k < K; ++k) pr[k] = probe_place(fr.W, fr.H, u[k], v[k], pd[k], n[k]);
+        if constexpr (K > 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) field[k] = probe_load(rs, pr[k]);
+        if constexpr (K > 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
             // child 2 i + 1 + (r >= thr) at byte offset 2 o + 32 + 32 (r >= thr)
-            o[k] = 2u * o[k] + (r >= n.thr ? 64u : 32u);
-        }
+            o[k] = 2u * o[k] + (probe_finish(field[k], pr[k], own[k], n[k]) >= n[k].thr ? 64u : 32u);
     }
     // below: byte offsets into the tree's DeepNodes (16 per node), read
     // through a buffer resource over its (L - 1) 16 bytes (below 2^20)
@@ -477,14 +568,26 @@ __device__ __forceinline__ void traverse_packed_k(const ProbeNode *__restrict__ 
 #pragma unroll
     for (int k = 0; k < K; ++k) o[k] >>= 1;
     while (o[0] < oend) {
+        DeepNode d[K];
+        ProbeNode n[K];
+        Probe pr[K];
+        uint32_t field[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            d[k] = __builtin_bit_cast(DeepNode, __builtin_amdgcn_raw_buffer_load_b128(ts, (int)o[k], 0, 0));
+        if constexpr (K > 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const DeepNode d =
-                __builtin_bit_cast(DeepNode, __builtin_amdgcn_raw_buffer_load_b128(ts, (int)o[k], 0, 0));
-            const ProbeNode n = probe_node_deep(d, fr);
-            const int32_t r = probe_response(rs, fr.W, fr.H, u[k], v[k], own[k], pd[k], n);
-            o[k] = 2u * o[k] + (r >= n.thr ? 32u : 16u);
+            n[k] = probe_node_deep(d[k], fr);
+            pr[k] = probe_place(fr.W, fr.H, u[k], v[k], pd[k], n[k]);
         }
+        if constexpr (K > 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) field[k] = probe_load(rs, pr[k]);
+        if constexpr (K > 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            o[k] = 2u * o[k] + (probe_finish(field[k], pr[k], own[k], n[k]) >= n[k].thr ? 32u : 16u);
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) leaf[k] = ok[k] ? (int32_t)(o[k] >> 4) - (L - 1) : -1;

@@ -157,8 +157,9 @@ __global__ void k_gen_nodes(uint64_t *nodes, DeepNode *deep, int T, int L, uint6
 // chains run side by side instead of one after another
 __global__ void __launch_bounds__(256) k_pack(Frame fr, uint64_t *__restrict__ packed)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < (int64_t)fr.W * fr.H) packed[p] = pack_pixel(fr, p);
+    const int p = 4 * (int)(blockIdx.x * blockDim.x + threadIdx.x), P = fr.W * fr.H;
+    uint64_t w[4];
+    if (p < P) pack_pixels4(fr, (uint64_t RL_GLOBAL *)packed, P, p, w);
 }
 
 // block (x) of 4 x 256 pixels and tree (y): each thread walks 4 pixels of
@@ -1007,7 +1008,7 @@ static int ensure_frame_scratch(Forest *f, int64_t P, hipStream_t s)
     if (P <= f->cap_P) return RELOC_OK;
     int64_t C_old = (f->cap_P + CHUNK - 1) / CHUNK;
     dfree(f, &f->leaves, (size_t)f->T * f->cap_P);
-    dfree(f, &f->packed, (size_t)f->cap_P);
+    dfree(f, &f->packed, (size_t)PACKED_WORDS * f->cap_P);
     dfree(f, &f->rank, (size_t)f->T * f->cap_P);
     dfree(f, &f->slot, (size_t)f->T * f->cap_P);
     dfree(f, &f->kval, (size_t)f->T * f->cap_P);
@@ -1017,7 +1018,7 @@ static int ensure_frame_scratch(Forest *f, int64_t P, hipStream_t s)
     int64_t C = (P + CHUNK - 1) / CHUNK;
     int rc = RELOC_OK;
     rc |= dalloc(f, &f->leaves, (size_t)f->T * P, s);
-    rc |= dalloc(f, &f->packed, (size_t)P, s);
+    rc |= dalloc(f, &f->packed, (size_t)PACKED_WORDS * P, s);
     rc |= dalloc(f, &f->rank, (size_t)f->T * P, s);
     rc |= dalloc(f, &f->slot, (size_t)f->T * P, s);
     rc |= dalloc(f, &f->kval, (size_t)f->T * P, s);
@@ -1048,7 +1049,7 @@ int traverse_frame(Forest *f, const Frame &fr, hipStream_t s)
     int64_t P = (int64_t)fr.W * fr.H;
     int rc = ensure_frame_scratch(f, P, s);
     if (rc) return rc;
-    RL_LAUNCH("k_pack", k_pack, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, fr, f->packed);
+    RL_LAUNCH("k_pack", k_pack, dim3((unsigned)((P + 1023) / 1024)), dim3(256), 0, s, fr, f->packed);
     RL_LAUNCH("k_leaves", k_leaves, dim3((unsigned)((P + LEAF_PIX * 256 - 1) / (LEAF_PIX * 256)), (unsigned)f->T),
               dim3(256), 0, s, f->nodes, f->deep, f->T, f->L, fr, f->packed, f->leaves);
     RL_HIP(hipGetLastError());
@@ -1132,7 +1133,7 @@ static void forest_free(Forest *f)
     dfree(f, &f->dirty_count, 2);
     dfree(f, &f->total_samples, 1);
     dfree(f, &f->leaves, (size_t)f->T * f->cap_P);
-    dfree(f, &f->packed, (size_t)f->cap_P);
+    dfree(f, &f->packed, (size_t)PACKED_WORDS * f->cap_P);
     dfree(f, &f->rank, (size_t)f->T * f->cap_P);
     dfree(f, &f->slot, (size_t)f->T * f->cap_P);
     dfree(f, &f->kval, (size_t)f->T * f->cap_P);

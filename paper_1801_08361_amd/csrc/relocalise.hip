@@ -313,8 +313,7 @@ __device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long l
 // per pixel), the block's count of valid pixels and, for pick weights given
 // by the caller, the block's weight sum (learned weights computed in the
 // batch add theirs in k_b_weights, onto the zero written here)
-// (POOL_BLOCK / PB_PIX threads per block: thread t handles pixels
-// t + j POOL_BLOCK / PB_PIX of it, all loads first)
+// (POOL_BLOCK / PB_PIX threads per block, thread t on pixels 4 t .. + 3 of it)
 __global__ void __launch_bounds__(POOL_BLOCK / PB_PIX) k_b_pack(const Attempt *__restrict__ att, Stage S)
 {
     constexpr int NT = POOL_BLOCK / PB_PIX;
@@ -327,20 +326,16 @@ __global__ void __launch_bounds__(POOL_BLOCK / PB_PIX) k_b_pack(const Attempt *_
         const int b = u - S.off[a];
         uint64_t w[PB_PIX];
         bool ok[PB_PIX];
-#pragma unroll
-        for (int j = 0; j < PB_PIX; ++j) {
-            const int p = b * POOL_BLOCK + j * NT + tid;
-            w[j] = p < A.P ? pack_pixel(A.fr, p) : 0ull;
-        }
+        static_assert(PB_PIX == 4, "four pixels a thread");
+        const int p0 = b * POOL_BLOCK + 4 * tid;
+        pack_pixels4(A.fr, A.packed, A.P, p0, w);
         int n = 0;
         unsigned long long ws = 0ull;
 #pragma unroll
         for (int j = 0; j < PB_PIX; ++j) {
-            const int p = b * POOL_BLOCK + j * NT + tid;
-            ok[j] = p < A.P && packed_valid(w[j]);
-            if (p < A.P) A.packed[p] = w[j];
+            ok[j] = packed_valid(w[j]);   // 0 past the frame's end
             n += __popcll(__ballot(ok[j]));
-            if (A.weights && !A.mq && ok[j]) ws += (unsigned long long)A.weights[p];
+            if (A.weights && !A.mq && ok[j]) ws += (unsigned long long)A.weights[p0 + j];
         }
         // the block's valid pixels and, for given weights, their weight sum
         if (A.weights && !A.mq)
@@ -1718,7 +1713,7 @@ static size_t carve(const Shape &s, char *base, Attempt &A)
         return p;
     };
     A.leaves = (decltype(A.leaves))take((size_t)s.T * P * 4);
-    A.packed = (decltype(A.packed))take((size_t)P * 8);
+    A.packed = (decltype(A.packed))take((size_t)PACKED_WORDS * P * 8);
     A.pool = (decltype(A.pool))take((size_t)P * 4);
     A.blockcnt = (decltype(A.blockcnt))take((size_t)nb * 4);
     A.blockw = (decltype(A.blockw))take((size_t)nb * 8);
