@@ -77,7 +77,6 @@ using Result = reloc_result;
 constexpr uint64_t TAG_FOREST = 1, TAG_RESERVOIR = 2, TAG_HYP = 3, TAG_PIX = 4, TAG_TRAIN = 8;
 
 constexpr int GROUP = 8;        // energy partial sums run over 8 consecutive draws
-constexpr int CHUNK = 4096;     // pixels per reservoir-rank chunk
 constexpr int MAX_HYP = 4096;
 constexpr int MAX_B = 2048;
 constexpr int MAX_R = 1024;
@@ -987,17 +986,18 @@ struct Forest {
     int32_t *nmodes = nullptr;     // [T][L]
     uint32_t *dirty = nullptr;     // [T][L]
     uint32_t *dirty_list = nullptr;
-    uint32_t *dirty_count = nullptr;
+    uint32_t *dirty_count = nullptr;  // dirty leaves, the mode kernel's ticket
     unsigned long long *total_samples = nullptr;
     bool maybe_dirty = false;
     bool dropped = false;
     // per-frame adaptation scratch (grows with the frame size)
-    int64_t cap_P = 0;
+    int64_t cap_P = 0;             // pixels the frame scratch holds
+    int64_t cap_C = 0;             // chunks per tree the chunk tables hold
     int32_t *leaves = nullptr;     // [T][P]
     uint64_t *packed = nullptr;    // [P] the frame packed for probing
     uint16_t *rank = nullptr;      // [T][P]
-    int32_t *slot = nullptr;       // [T][P]
-    uint32_t *kval = nullptr;      // [T][P]
+    uint8_t *late = nullptr;       // per workgroup of the reservoir kernel: pixels that met a taken slot
+    uint32_t *n_late = nullptr;    // their numbers
     uint16_t *chunk_cnt = nullptr; // [T][C][L]
     uint32_t *chunk_pref = nullptr;// [T][C][L]
     // the plain relocalisation path: a batch of one attempt

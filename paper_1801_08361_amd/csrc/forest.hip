@@ -6,9 +6,10 @@
 // (tree, leaf, k)) while running every pixel in parallel: a pixel's k is its
 // leaf's counter plus its stable rank among the frame's pixels in the same
 // leaf, and because a slot depends only on k, each slot keeps the sample with
-// the largest k that maps to it. Ranks come from an LDS sort of each 4096-pixel
-// chunk plus a per-leaf prefix over chunks; "largest k wins" is an atomicMax
-// on a per-slot stamp followed by the write of the single winner.
+// the largest k that maps to it. Ranks come from an ordered count of each
+// chunk of pixels plus a per-leaf prefix over chunks; "largest k wins" is an
+// atomicMax on a per-slot stamp: the first pixel of a frame that reaches a slot
+// writes it, and of those that came later the one whose stamp remains.
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -219,240 +220,198 @@ __global__ void k_features8(const uint64_t *__restrict__ extra, Frame fr, int32_
 // kernels: reservoir adaptation
 // ---------------------------------------------------------------------------
 
-constexpr int RANK_THREADS = 512;
+// Per (chunk, tree): the stable rank of each valid pixel among the chunk's
+// pixels in the same leaf, and the chunk's per-leaf counts into the dense
+// [T][C][L] table (kept zero elsewhere). A wavefront finds the equal leaves of
+// 64 consecutive pixels with one ballot per bit of the leaf index; then one
+// wavefront takes the chunk's 16 E such rows in order through a table of
+// counts in LDS (two 16-bit counts a word), each leaf once per row with all
+// its pixels, so that what it finds there is the leaf's count in the rows
+// before. A wavefront's LDS operations run in issue order, so the rows need no
+// wait between them. (A bitonic sort of the chunk's keys took 33 us for a 640
+// x 480 frame in 5 trees of depth 15 and 24 us for 320 x 240 in depth 10; this
+// takes 13.6 and 4.5.)
+constexpr int RANK_THREADS = 1024, RANK_BATCH = 16;
 
-// Per (chunk, tree): stable rank of each valid pixel among the chunk's pixels
-// in the same leaf (bitonic sort of (leaf, local index) keys in LDS), and the
-// chunk's per-leaf counts into the dense [T][C][L] table (kept zero elsewhere).
-// one bitonic step at distance D < 8 over a thread's eight keys (key i = 8
-// tid + e in register e), for the merge of size k
-template <int D>
-__device__ __forceinline__ void bitonic_in_thread(uint32_t v[8], int tid, int k)
+static inline size_t rank_smem(int L) { return (size_t)(L / 2 + 64) * 4; }
+
+// Pixels of a chunk over RANK_THREADS: as many as leave about two chunks for
+// three CUs (160 over all trees), 2 to 8. Larger chunks make the table of
+// counts smaller, which the prefix reads whole (640 x 480: ranks and prefix take
+// 13.6 + 11.2 us with 8, 14.6 + 13.3 with 4, 14 + 33 with 2); smaller ones keep
+// small frames' chunks on all CUs (320 x 240: 4.5 us with 2, 6.9 with 4). The
+// deepest tree's table of counts leaves no room for 8.
+static inline int chunk_pixels(int64_t P, int T, int L)
 {
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        if ((e & D) == 0) {
-            const bool asc = ((8 * tid + e) & k) == 0;
-            const uint32_t a = v[e], b = v[e + D];
-            if ((a > b) == asc) {
-                v[e] = b;
-                v[e + D] = a;
-            }
-        }
+    int e = L > 32768 ? 4 : 8;
+    while (e > 2 && T * P < (int64_t)160 * RANK_THREADS * e) e >>= 1;
+    return RANK_THREADS * e;
 }
 
-// the same in the strided layout (key tid + RANK_THREADS e in register e),
-// for distance D RANK_THREADS
-template <int D>
-__device__ __forceinline__ void bitonic_strided(uint32_t v[8], int tid, int k)
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        if ((e & D) == 0) {
-            const bool asc = ((tid + RANK_THREADS * e) & k) == 0;
-            const uint32_t a = v[e], b = v[e + D];
-            if ((a > b) == asc) {
-                v[e] = b;
-                v[e + D] = a;
-            }
-        }
-}
-
-__global__ void __launch_bounds__(RANK_THREADS) k_chunk_rank(const int32_t *__restrict__ leaves, int P, int L,
+template <int E>
+__global__ void __launch_bounds__(RANK_THREADS) k_chunk_rank(const int32_t *__restrict__ leaves, int P, int L, int D,
                                                              int C, uint16_t *__restrict__ rank,
                                                              uint16_t *__restrict__ cnt)
 {
-    __shared__ uint32_t keys[CHUNK];
-    const int c = blockIdx.x, t = blockIdx.y, tid = threadIdx.x;
-    const int64_t base = (int64_t)c * CHUNK;
-    // Bitonic sort with key i (of CHUNK) in register e of thread tid for
-    // i = E tid + e: exchanges at distance j < E stay in the thread, those at
-    // E <= j < 64 E are between lanes of one wavefront (xor shuffles), and
-    // only those at j >= 64 E go through LDS between barriers.
-    constexpr int E = CHUNK / RANK_THREADS;
-    static_assert(E == 8, "eight keys per thread");
-    uint32_t v[E];
+    constexpr int CHUNK = RANK_THREADS * E, ROWS = CHUNK / 64;
+    extern __shared__ uint32_t leaf_cnt[];   // [L / 2], then a word a lane
+    __shared__ uint32_t row[CHUNK];          // leaf | pixels << 16 of a row's leaders, then the count before
+    const int c = blockIdx.x, t = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t base = (int64_t)t * P + (int64_t)c * CHUNK;
+    const int left = P - c * CHUNK;
+    int32_t leaf[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int j = E * tid + e;
-        const int64_t p = base + j;
-        const int32_t leaf = p < P ? leaves[(int64_t)t * P + p] : -1;
-        v[e] = leaf >= 0 ? (((uint32_t)leaf << 12) | (uint32_t)j) : 0xFFFFFFFFu;
+        const int i = 64 * (E * wave + e) + lane;
+        leaf[e] = i < left ? leaves[base + i] : -1;
     }
-    for (int k = 2; k <= CHUNK; k <<= 1) {
-        int j = k >> 1;
-        if (j >= 64 * E) {
-            // distances of 512 and more: through LDS into the strided layout
-            // (key tid + 512 e in register e), where they are exchanges
-            // inside the thread, and back
+    for (int i = tid; i < L / 2 + 64; i += RANK_THREADS) leaf_cnt[i] = 0u;
+    uint32_t same[E][2];
 #pragma unroll
-            for (int e = 0; e < E; ++e) keys[E * tid + e] = v[e];
-            __syncthreads();
+    for (int e = 0; e < E; ++e) {
+        const uint64_t valid = __ballot(leaf[e] >= 0);
+        same[e][0] = (uint32_t)valid;
+        same[e][1] = (uint32_t)(valid >> 32);
+    }
+    // four bits a step; those past the index's are zero in every valid lane
+    for (int b0 = 0; b0 < D; b0 += 4)
 #pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = keys[tid + RANK_THREADS * e];
-            for (; j >= 64 * E; j >>= 1) {
-                if (j == 4 * RANK_THREADS)
-                    bitonic_strided<4>(v, tid, k);
-                else if (j == 2 * RANK_THREADS)
-                    bitonic_strided<2>(v, tid, k);
-                else
-                    bitonic_strided<1>(v, tid, k);
-            }
-#pragma unroll
-            for (int e = 0; e < E; ++e) keys[tid + RANK_THREADS * e] = v[e];
-            __syncthreads();
-#pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = keys[E * tid + e];
-            __syncthreads();
-        }
-        for (; j >= E; j >>= 1) {
-            const int m = j / E;
+        for (int b = 0; b < 4; ++b)
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                const int i = E * tid + e;
-                const uint32_t o = __shfl_xor(v[e], m, 64);
-                v[e] = (((i & j) == 0) == ((i & k) == 0)) ? min(v[e], o) : max(v[e], o);
+                const uint32_t bit = (uint32_t)__builtin_amdgcn_sbfe(leaf[e], b0 + b, 1);   // all ones or zero
+                const uint64_t with = __ballot(bit != 0u);
+                same[e][0] &= ~((uint32_t)with ^ bit);
+                same[e][1] &= ~((uint32_t)(with >> 32) ^ bit);
             }
-        }
-        for (; j > 0; j >>= 1) {
-            if (j == 4)
-                bitonic_in_thread<4>(v, tid, k);
-            else if (j == 2)
-                bitonic_in_thread<2>(v, tid, k);
-            else
-                bitonic_in_thread<1>(v, tid, k);
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) keys[E * tid + e] = v[e];
-    __syncthreads();
-    // A key's rank is its sorted position s minus the first position of its
-    // leaf's run: the running maximum of the run starts (positions whose leaf
-    // differs from the previous key's), in the thread, over the wavefront's
-    // lanes and over the wavefronts.
-    __shared__ uint32_t wmax[RANK_THREADS / 64];
-    const int lane = tid & 63, wave = tid >> 6;
-    uint32_t m[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int s = E * tid + e;
-        const uint32_t prev = e > 0 ? v[e - 1] >> 12 : (s > 0 ? keys[s - 1] >> 12 : 0xFFFFFFFFu);
-        const uint32_t start = (s == 0 || (v[e] >> 12) != prev) ? (uint32_t)s : 0u;
-        m[e] = e > 0 ? max(m[e - 1], start) : start;
+        const uint32_t lo = same[e][0], hi = same[e][1];
+        const int first = lo ? __builtin_ctz(lo) : 32 + (hi ? __builtin_ctz(hi) : 0);
+        row[64 * (E * wave + e) + lane] =
+            leaf[e] >= 0 && first == lane ? (uint32_t)leaf[e] | ((uint32_t)(__popc(lo) + __popc(hi)) << 16) : 0u;
     }
-    uint32_t x = m[E - 1];
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x = max(x, y);
-    }
-    uint32_t before = __shfl_up(x, 1, 64);
-    if (lane == 0) before = 0u;
-    if (lane == 63) wmax[wave] = x;
     __syncthreads();
-    for (int w = 0; w < wave; ++w) before = max(before, wmax[w]);
+    if (wave == 0) {
+        // lanes without a leader add nothing to a word of their own, so that no
+        // row branches and a batch's additions are all in flight together
+        for (int r0 = 0; r0 < ROWS; r0 += RANK_BATCH) {
+            uint32_t v[RANK_BATCH], old[RANK_BATCH];
+#pragma unroll
+            for (int r = 0; r < RANK_BATCH; ++r) v[r] = row[64 * (r0 + r) + lane];
+#pragma unroll
+            for (int r = 0; r < RANK_BATCH; ++r)
+                old[r] = atomicAdd(&leaf_cnt[v[r] ? (int)((v[r] & 0xFFFFu) >> 1) : L / 2 + lane],
+                                   (v[r] >> 16) << (16u * (v[r] & 1u)));
+#pragma unroll
+            for (int r = 0; r < RANK_BATCH; ++r)
+                row[64 * (r0 + r) + lane] = (old[r] >> (16u * (v[r] & 1u))) & 0xFFFFu;
+        }
+    }
+    __syncthreads();
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int s = E * tid + e;
-        const uint32_t key = v[e];
-        if (key == 0xFFFFFFFFu) continue;
-        const uint32_t leaf = key >> 12;
-        const int r = s - (int)max(m[e], before);
-        rank[(int64_t)t * P + base + (key & 4095u)] = (uint16_t)r;
-        const uint32_t next = e + 1 < E ? v[e + 1] >> 12 : (s + 1 < CHUNK ? keys[s + 1] >> 12 : 0xFFFFFFFFu);
-        if (next != leaf) cnt[((int64_t)t * C + c) * L + leaf] = (uint16_t)(r + 1);
+        if (leaf[e] < 0) continue;
+        const int r = 64 * (E * wave + e);
+        const uint64_t m = ((uint64_t)same[e][1] << 32) | same[e][0];
+        const uint32_t k = row[r + __builtin_ctzll(m)] + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        rank[base + r + lane] = (uint16_t)k;
+        const uint32_t all = (leaf_cnt[leaf[e] >> 1] >> (16 * (leaf[e] & 1))) & 0xFFFFu;
+        if (k + 1u == all) cnt[((int64_t)t * C + c) * L + leaf[e]] = (uint16_t)all;
     }
 }
 
 // Per (tree, leaf): prefix of chunk counts in chunk order, reset of the
-// table, counter update, and marking of the leaf for mode extraction.
-__global__ void k_leaf_scan(int T, int L, int C, uint16_t *__restrict__ cnt, uint32_t *__restrict__ pref,
-                            uint32_t *__restrict__ counter, uint32_t *__restrict__ base,
-                            uint32_t *__restrict__ dirty, uint32_t *__restrict__ dirty_list,
-                            uint32_t *__restrict__ dirty_count, unsigned long long *__restrict__ total)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)T * L) return;
-    int t = (int)(i / L), leaf = (int)(i % L);
-    uint32_t run = 0;
-    // chunks 16 at a time: their counts are loaded before any of them is
-    // cleared (the clears would otherwise order every load after the last)
-    constexpr int CB = 16;
-    for (int c0 = 0; c0 < C; c0 += CB) {
-        uint32_t v[CB];
-#pragma unroll
-        for (int q = 0; q < CB; ++q)
-            v[q] = c0 + q < C ? (uint32_t)cnt[((int64_t)t * C + c0 + q) * L + leaf] : 0u;
-#pragma unroll
-        for (int q = 0; q < CB; ++q)
-            if (v[q]) {
-                const int64_t idx = ((int64_t)t * C + c0 + q) * L + leaf;
-                pref[idx] = run;
-                cnt[idx] = 0;
-                run += v[q];
-            }
-    }
-    uint32_t k0 = counter[i];
-    base[i] = k0;
-    if (run) {
-        counter[i] = k0 + run;
-        if (atomicExch(&dirty[i], 1u) == 0u) {
-            uint32_t pos = atomicAdd(dirty_count, 1u);
-            dirty_list[pos] = (uint32_t)i;
-        }
-        if (t == 0) atomicAdd(total, (unsigned long long)run);
-    }
-}
+// table, counter update, and marking of the leaf for mode extraction (its flag;
+// a list of flagged leaves kept here cost a same-address atomic per workgroup,
+// 20 us a frame). A thread
+// has two neighbouring leaves; the four wavefronts of a workgroup split the
+// chunks of the same 128 leaves, add up their shares in LDS and then each
+// writes its own (kept in registers up to SCAN_KEEP chunks, read again
+// beyond).
+constexpr int SCAN_KEEP = 24;
 
-// Per pixel: k and slot for every tree; the stamp of the slot takes the
-// largest k + 1 that maps to it.
-__global__ void k_slots(const int32_t *__restrict__ leaves, const uint16_t *__restrict__ rank,
-                        const uint32_t *__restrict__ pref, const uint32_t *__restrict__ base, int T, int L, int R,
-                        int C, int P, uint64_t seed, int32_t *__restrict__ slot, uint32_t *__restrict__ kval,
-                        uint32_t *__restrict__ stamp)
+__global__ void __launch_bounds__(256) k_leaf_scan(int T, int L, int C, uint16_t *__restrict__ cnt,
+                                                   uint32_t *__restrict__ pref, uint32_t *__restrict__ counter,
+                                                   uint32_t *__restrict__ base, uint32_t *__restrict__ dirty,
+                                                   unsigned long long *__restrict__ total)
 {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    int c = p / CHUNK;
-    for (int t = 0; t < T; ++t) {
-        int64_t ti = (int64_t)t * P + p;
-        int32_t leaf = leaves[ti];
-        int32_t s = -1;
-        uint32_t k = 0;
-        if (leaf >= 0) {
-            int64_t li = (int64_t)t * L + leaf;
-            k = base[li] + pref[((int64_t)t * C + c) * L + leaf] + rank[ti];
-            if (k < (uint32_t)R) {
-                s = (int32_t)k;
-            } else {
-                U4 u = philox((uint64_t)t, (uint64_t)leaf, (uint64_t)k, 0, seed, TAG_RESERVOIR);
-                uint64_t j = uniform_int(u.x[0], (uint64_t)k + 1);
-                if (j < (uint64_t)R) s = (int32_t)j;
+    __shared__ uint2 share[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i = 2 * ((int64_t)blockIdx.x * 64 + lane);
+    const bool in = i < (int64_t)T * L;
+    const int t = in ? (int)(i / L) : 0, leaf = in ? (int)(i % L) : 0;
+    const int c0 = C * wave / 4, nc = C * (wave + 1) / 4 - c0;
+    uint32_t *tab = (uint32_t *)(cnt + ((int64_t)t * C + c0) * L + leaf);   // row stride L / 2 words
+    const int64_t step = L / 2;
+    uint32_t v[SCAN_KEEP];
+    uint2 sum = make_uint2(0u, 0u);
+    if (in) {
+        if (nc <= SCAN_KEEP) {
+#pragma unroll
+            for (int q = 0; q < SCAN_KEEP; ++q) v[q] = q < nc ? tab[q * step] : 0u;
+#pragma unroll
+            for (int q = 0; q < SCAN_KEEP; ++q) {
+                sum.x += v[q] & 0xFFFFu;
+                sum.y += v[q] >> 16;
             }
-            if (s >= 0) atomicMax(&stamp[li * R + s], k + 1u);
+        } else {
+            for (int q = 0; q < nc; ++q) {
+                const uint32_t w = tab[q * step];
+                sum.x += w & 0xFFFFu;
+                sum.y += w >> 16;
+            }
         }
-        slot[ti] = s;
-        kval[ti] = k;
     }
+    share[wave][lane] = sum;
+    __syncthreads();
+    uint2 run = make_uint2(0u, 0u), all = make_uint2(0u, 0u);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if (w == wave) run = all;
+        all.x += share[w][lane].x;
+        all.y += share[w][lane].y;
+    }
+    uint2 *out = (uint2 *)(pref + ((int64_t)t * C + c0) * L + leaf);
+    auto put = [&](int q, uint32_t w) {
+        if (w) {
+            out[q * step] = run;
+            tab[q * step] = 0u;
+            run.x += w & 0xFFFFu;
+            run.y += w >> 16;
+        }
+    };
+    if (in) {
+        if (nc <= SCAN_KEEP) {
+#pragma unroll
+            for (int q = 0; q < SCAN_KEEP; ++q) put(q, v[q]);
+        } else {
+            for (int q = 0; q < nc; ++q) put(q, tab[q * step]);
+        }
+    }
+    if (wave) return;
+    unsigned long long first_tree = in && t == 0 ? (unsigned long long)all.x + all.y : 0ull;
+    for (int o = 32; o >= 1; o >>= 1) first_tree += __shfl_xor(first_tree, o, 64);
+    if (lane == 0 && first_tree) atomicAdd(total, first_tree);
+    if (!in) return;
+    const uint2 k0 = *(const uint2 *)(counter + i);
+    *(uint2 *)(base + i) = k0;
+    if (all.x | all.y) *(uint2 *)(counter + i) = make_uint2(k0.x + all.x, k0.y + all.y);
+    if (all.x) dirty[i] = 1u;
+    if (all.y) dirty[i + 1] = 1u;
 }
 
 struct Pose32 {
     float R[9], t[3];
 };
 
-// Per pixel: the winner of each slot writes the world point (integer mm,
-// FP32 transform then round-half-even) and the colour.
-__global__ void k_write(const int32_t *__restrict__ leaves, const int32_t *__restrict__ slot,
-                        const uint32_t *__restrict__ kval, const uint32_t *__restrict__ stamp, int T, int L, int R,
-                        Frame fr, Pose32 pose, Entry *__restrict__ res)
+// The reservoir entry of pixel p: its world point (integer mm, FP32 transform
+// then round-half-even) and colour.
+__device__ __forceinline__ Entry frame_entry(const Frame &fr, const Pose32 &pose, int p)
 {
-    int P = fr.W * fr.H;
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    uint32_t d = fr.depth[p];
-    if (!valid_depth(fr, d)) return;
-    int u = p % fr.W, v = p / fr.W;
+    const int u = p % fr.W, v = p / fr.W;
     float c[3];
-    cam_point(fr, u, v, d, c);
+    cam_point(fr, u, v, fr.depth[p], c);
     Entry e;
     float w0 = ((pose.R[0] * c[0] + pose.R[1] * c[1]) + pose.R[2] * c[2]) + pose.t[0];
     float w1 = ((pose.R[3] * c[0] + pose.R[4] * c[1]) + pose.R[5] * c[2]) + pose.t[1];
@@ -461,12 +420,89 @@ __global__ void k_write(const int32_t *__restrict__ leaves, const int32_t *__res
     e.y = (int32_t)rintf(w1 * 1000.0f);
     e.z = (int32_t)rintf(w2 * 1000.0f);
     e.rgb = (uint32_t)fr.rgb[p * 3] | ((uint32_t)fr.rgb[p * 3 + 1] << 8) | ((uint32_t)fr.rgb[p * 3 + 2] << 16);
-    for (int t = 0; t < T; ++t) {
-        int64_t ti = (int64_t)t * P + p;
-        int32_t s = slot[ti];
-        if (s < 0) continue;
-        int64_t si = ((int64_t)t * L + leaves[ti]) * R + s;
-        if (stamp[si] == kval[ti] + 1u) res[si] = e;
+    return e;
+}
+
+// a pixel that met a slot already taken by another pixel of the frame
+struct Late {
+    uint32_t cell;    // slot over all leaves
+    uint32_t stamp;   // k + 1
+    int32_t p;
+};
+
+// Per (pixel, tree): k and the slot. The slot's stamp takes the largest k + 1
+// that maps to it. A stamp of an earlier frame is at most the leaf's counter
+// at the frame's start, so the stamp found there tells whether another pixel
+// of this frame was first: the first one writes its entry at once, a later one
+// of larger k goes to its workgroup's list for k_late (a later one of smaller k
+// has lost). (Slots, then a second pass that compared every pixel's k with its
+// slot's stamp and wrote the winners: 22.7 + 16.9 us for a 640 x 480 frame
+// in 5 trees; this and k_late: 27 + 5, mostly the
+// chain of loads and the atomic's return. With one list for the frame its
+// counter's atomics alone made it 58.)
+constexpr int RES_THREADS = 256;
+
+__global__ void __launch_bounds__(RES_THREADS) k_reservoir(const int32_t *__restrict__ leaves,
+                                                           const uint16_t *__restrict__ rank,
+                                                           const uint32_t *__restrict__ pref,
+                                                           const uint32_t *__restrict__ base, int L, int R, int C,
+                                                           int chunk, uint64_t seed, Frame fr, Pose32 pose,
+                                                           uint32_t *__restrict__ stamp, Entry *__restrict__ res,
+                                                           Late *__restrict__ late, uint32_t *__restrict__ n_late)
+{
+    __shared__ uint32_t wave_n[RES_THREADS / 64];
+    const int P = fr.W * fr.H, p = blockIdx.x * RES_THREADS + threadIdx.x, t = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t ti = (int64_t)t * P + p;
+    const int32_t leaf = p < P ? leaves[ti] : -1;
+    bool again = false;
+    Late l = {0u, 0u, p};
+    if (leaf >= 0) {
+        const int64_t li = (int64_t)t * L + leaf;
+        const uint32_t k0 = base[li];
+        const uint32_t k = k0 + pref[((int64_t)t * C + p / chunk) * L + leaf] + rank[ti];
+        int32_t s = -1;
+        if (k < (uint32_t)R) {
+            s = (int32_t)k;
+        } else {
+            const U4 u = philox((uint64_t)t, (uint64_t)leaf, (uint64_t)k, 0, seed, TAG_RESERVOIR);
+            const uint64_t j = uniform_int(u.x[0], (uint64_t)k + 1);
+            if (j < (uint64_t)R) s = (int32_t)j;
+        }
+        if (s >= 0) {
+            l.cell = (uint32_t)(li * R + s);
+            l.stamp = k + 1u;
+            const uint32_t was = atomicMax(&stamp[l.cell], l.stamp);
+            if (was <= k0) res[l.cell] = frame_entry(fr, pose, p);
+            else again = was < l.stamp;
+        }
+    }
+    const uint64_t m = __ballot(again);
+    if (lane == 0) wave_n[wave] = (uint32_t)__popcll(m);
+    __syncthreads();
+    const int64_t list = (int64_t)t * gridDim.x + blockIdx.x;
+    uint32_t at = 0u, n = 0u;
+#pragma unroll
+    for (int w = 0; w < RES_THREADS / 64; ++w) {
+        if (w < wave) at += wave_n[w];
+        n += wave_n[w];
+    }
+    if (again) late[list * RES_THREADS + at + __popcll(m & ((1ull << lane) - 1ull))] = l;
+    if (threadIdx.x == 0) n_late[list] = n;
+}
+
+// the listed pixels whose stamp has remained write over the slot's first
+// entry; a wavefront per list
+__global__ void __launch_bounds__(256) k_late(const Late *__restrict__ late, const uint32_t *__restrict__ n_late,
+                                              int lists, const uint32_t *__restrict__ stamp, Frame fr, Pose32 pose,
+                                              Entry *__restrict__ res)
+{
+    const int list = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    if (list >= lists) return;
+    const uint32_t n = n_late[list];
+    for (uint32_t i = threadIdx.x & 63; i < n; i += 64) {
+        const Late l = late[(int64_t)list * RES_THREADS + i];
+        if (stamp[l.cell] == l.stamp) res[l.cell] = frame_entry(fr, pose, l.p);
     }
 }
 
@@ -918,6 +954,35 @@ __device__ __forceinline__ void leaf_modes(const Entry *__restrict__ pts, int n,
     if (tid == 0) *n_out = nm;
 }
 
+// the flagged leaves as a list, 4 leaves a thread
+__global__ void __launch_bounds__(256) k_dirty_list(const uint32_t *__restrict__ dirty, int n,
+                                                    uint32_t *__restrict__ list, uint32_t *__restrict__ work)
+{
+    __shared__ uint32_t wave_n[4], at0;
+    const int i = 4 * (int)(blockIdx.x * 256 + threadIdx.x), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    bool is[4];
+    uint64_t m[4];
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        is[e] = i + e < n && dirty[i + e] != 0u;
+        m[e] = __ballot(is[e]);
+        mine += (uint32_t)__popcll(m[e]);
+    }
+    if (lane == 0) wave_n[wave] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) at0 = atomicAdd(&work[0], wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3]);
+    __syncthreads();
+    uint32_t at = at0;
+    for (int w = 0; w < wave; ++w) at += wave_n[w];
+    const uint64_t before = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (is[e]) list[at + (uint32_t)__popcll(m[e] & before)] = (uint32_t)(i + e);
+        at += (uint32_t)__popcll(m[e]);
+    }
+}
+
 // Leaves of the dirty list, handed out by a ticket (work[1]) since their
 // point counts differ by three orders of magnitude; work[0] is the list's
 // length. Clears each leaf's dirty flag and refreshes its summary for the
@@ -1003,30 +1068,50 @@ static ModeParams mode_params(const Forest *f)
 // host side
 // ---------------------------------------------------------------------------
 
-static int ensure_frame_scratch(Forest *f, int64_t P, hipStream_t s)
+// workgroups of k_reservoir per tree
+static int64_t res_blocks(int64_t P) { return (P + RES_THREADS - 1) / RES_THREADS; }
+
+static void free_frame_scratch(Forest *f)
 {
-    if (P <= f->cap_P) return RELOC_OK;
-    int64_t C_old = (f->cap_P + CHUNK - 1) / CHUNK;
     dfree(f, &f->leaves, (size_t)f->T * f->cap_P);
     dfree(f, &f->packed, (size_t)PACKED_WORDS * f->cap_P);
     dfree(f, &f->rank, (size_t)f->T * f->cap_P);
-    dfree(f, &f->slot, (size_t)f->T * f->cap_P);
-    dfree(f, &f->kval, (size_t)f->T * f->cap_P);
-    dfree(f, &f->chunk_cnt, (size_t)f->T * C_old * f->L);
-    dfree(f, &f->chunk_pref, (size_t)f->T * C_old * f->L);
+    dfree(f, &f->late, (size_t)f->T * res_blocks(f->cap_P) * RES_THREADS * sizeof(Late));
+    dfree(f, &f->n_late, (size_t)f->T * res_blocks(f->cap_P));
     f->cap_P = 0;
-    int64_t C = (P + CHUNK - 1) / CHUNK;
-    int rc = RELOC_OK;
-    rc |= dalloc(f, &f->leaves, (size_t)f->T * P, s);
-    rc |= dalloc(f, &f->packed, (size_t)PACKED_WORDS * P, s);
-    rc |= dalloc(f, &f->rank, (size_t)f->T * P, s);
-    rc |= dalloc(f, &f->slot, (size_t)f->T * P, s);
-    rc |= dalloc(f, &f->kval, (size_t)f->T * P, s);
-    rc |= dalloc(f, &f->chunk_cnt, (size_t)f->T * C * f->L, s);
-    rc |= dalloc(f, &f->chunk_pref, (size_t)f->T * C * f->L, s);
-    if (rc) return RELOC_E_NOMEM;
-    RL_HIP(hipMemsetAsync(f->chunk_cnt, 0, (size_t)f->T * C * f->L * sizeof(uint16_t), s));
-    f->cap_P = P;
+}
+
+static void free_chunk_tables(Forest *f)
+{
+    dfree(f, &f->chunk_cnt, (size_t)f->T * f->cap_C * f->L);
+    dfree(f, &f->chunk_pref, (size_t)f->T * f->cap_C * f->L);
+    f->cap_C = 0;
+}
+
+static int ensure_frame_scratch(Forest *f, int64_t P, hipStream_t s)
+{
+    if (P > f->cap_P) {
+        free_frame_scratch(f);
+        int rc = RELOC_OK;
+        rc |= dalloc(f, &f->leaves, (size_t)f->T * P, s);
+        rc |= dalloc(f, &f->packed, (size_t)PACKED_WORDS * P, s);
+        rc |= dalloc(f, &f->rank, (size_t)f->T * P, s);
+        rc |= dalloc(f, &f->late, (size_t)f->T * res_blocks(P) * RES_THREADS * sizeof(Late), s);
+        rc |= dalloc(f, &f->n_late, (size_t)f->T * res_blocks(P), s);
+        if (rc) return RELOC_E_NOMEM;
+        f->cap_P = P;
+    }
+    const int chunk = chunk_pixels(P, f->T, f->L);
+    const int64_t C = (P + chunk - 1) / chunk;
+    if (C > f->cap_C) {
+        free_chunk_tables(f);
+        int rc = RELOC_OK;
+        rc |= dalloc(f, &f->chunk_cnt, (size_t)f->T * C * f->L, s);
+        rc |= dalloc(f, &f->chunk_pref, (size_t)f->T * C * f->L, s);
+        if (rc) return RELOC_E_NOMEM;
+        RL_HIP(hipMemsetAsync(f->chunk_cnt, 0, (size_t)f->T * C * f->L * sizeof(uint16_t), s));
+        f->cap_C = C;
+    }
     return RELOC_OK;
 }
 
@@ -1036,6 +1121,8 @@ int update_modes(Forest *f, hipStream_t s)
     if (!f->res) return RELOC_E_STATE;
     ModeParams mp = mode_params(f);
     int grid = std::min(f->T * f->L, 256 * 8);
+    RL_LAUNCH("k_dirty_list", k_dirty_list, dim3((unsigned)((f->T * f->L + 1023) / 1024)), dim3(256), 0, s, f->dirty,
+              f->T * f->L, f->dirty_list, f->dirty_count);
     RL_LAUNCH("k_modes", k_modes, dim3(grid), dim3(MODE_THREADS), mode_smem(f->M), s, f->dirty_list, f->dirty_count,
                        f->dirty, f->counter, f->res, mp, f->modes, f->mode_rgb, f->nmodes, f->leaf_in);
     RL_LAUNCH("k_modes_done", k_modes_done, dim3(1), dim3(2), 0, s, f->dirty_count);
@@ -1118,7 +1205,6 @@ extern "C" const char *reloc_status_string(int code)
 
 static void forest_free(Forest *f)
 {
-    int64_t C = (f->cap_P + CHUNK - 1) / CHUNK;
     size_t TL = (size_t)f->T * f->L;
     dfree(f, &f->nodes, (size_t)f->T * (f->L - 1) + 8);
     dfree(f, &f->deep, (size_t)f->T * (f->L - 1));
@@ -1132,13 +1218,8 @@ static void forest_free(Forest *f)
     dfree(f, &f->dirty_list, TL);
     dfree(f, &f->dirty_count, 2);
     dfree(f, &f->total_samples, 1);
-    dfree(f, &f->leaves, (size_t)f->T * f->cap_P);
-    dfree(f, &f->packed, (size_t)PACKED_WORDS * f->cap_P);
-    dfree(f, &f->rank, (size_t)f->T * f->cap_P);
-    dfree(f, &f->slot, (size_t)f->T * f->cap_P);
-    dfree(f, &f->kval, (size_t)f->T * f->cap_P);
-    dfree(f, &f->chunk_cnt, (size_t)f->T * C * f->L);
-    dfree(f, &f->chunk_pref, (size_t)f->T * C * f->L);
+    free_frame_scratch(f);
+    free_chunk_tables(f);
     dfree(f, &f->mode_rgb, TL * rgb_stride(f->M));
     dfree(f, &f->leaf_in, TL * 4);
 }
@@ -1238,22 +1319,24 @@ extern "C" int reloc_adapt_frame(reloc_forest *f, const uint16_t *depth_dev, con
     int64_t P = (int64_t)fr.W * fr.H;
     rc = traverse_frame(f, fr, s);
     if (rc) return rc;
-    int C = (int)((P + CHUNK - 1) / CHUNK);
-    RL_LAUNCH("k_chunk_rank", k_chunk_rank, dim3(C, f->T), dim3(RANK_THREADS), 0, s, f->leaves, (int)P, f->L, C, f->rank,
-                       f->chunk_cnt);
-    int64_t TL = (int64_t)f->T * f->L;
-    RL_LAUNCH("k_leaf_scan", k_leaf_scan, dim3((unsigned)((TL + 255) / 256)), dim3(256), 0, s, f->T, f->L, C,
-                       f->chunk_cnt, f->chunk_pref, f->counter, f->base, f->dirty, f->dirty_list, f->dirty_count,
-                       f->total_samples);
-    RL_LAUNCH("k_slots", k_slots, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, f->leaves, f->rank,
-                       f->chunk_pref, f->base, f->T, f->L, f->R, C, (int)P, f->p.seed, f->slot, f->kval, f->stamp);
+    const int chunk = chunk_pixels(P, f->T, f->L), C = (int)((P + chunk - 1) / chunk);
     Pose32 ps;
     for (int r = 0; r < 3; ++r) {
         for (int c = 0; c < 3; ++c) ps.R[r * 3 + c] = (float)pose_c2w[r * 4 + c];
         ps.t[r] = (float)pose_c2w[r * 4 + 3];
     }
-    RL_LAUNCH("k_write", k_write, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, f->leaves, f->slot, f->kval,
-                       f->stamp, f->T, f->L, f->R, fr, ps, f->res);
+    Late *late = (Late *)f->late;
+    auto rank_kernel = chunk == 2 * RANK_THREADS ? k_chunk_rank<2> : chunk == 4 * RANK_THREADS ? k_chunk_rank<4> : k_chunk_rank<8>;
+    RL_LAUNCH("k_chunk_rank", rank_kernel, dim3(C, f->T), dim3(RANK_THREADS), rank_smem(f->L), s, f->leaves, (int)P, f->L,
+              f->D, C, f->rank, f->chunk_cnt);
+    const int64_t TL = (int64_t)f->T * f->L;
+    RL_LAUNCH("k_leaf_scan", k_leaf_scan, dim3((unsigned)((TL + 127) / 128)), dim3(256), 0, s, f->T, f->L, C, f->chunk_cnt,
+              f->chunk_pref, f->counter, f->base, f->dirty, f->total_samples);
+    const int64_t nb = res_blocks(P), lists = nb * f->T;
+    RL_LAUNCH("k_reservoir", k_reservoir, dim3((unsigned)nb, (unsigned)f->T), dim3(RES_THREADS), 0, s, f->leaves, f->rank,
+              f->chunk_pref, f->base, f->L, f->R, C, chunk, f->p.seed, fr, ps, f->stamp, f->res, late, f->n_late);
+    RL_LAUNCH("k_late", k_late, dim3((unsigned)((lists + 3) / 4)), dim3(256), 0, s, late, f->n_late, (int)lists, f->stamp,
+              fr, ps, f->res);
     RL_HIP(hipGetLastError());
     f->maybe_dirty = true;
     return RELOC_OK;

@@ -20,7 +20,7 @@
 // into its children's. So no sample is ever counted or placed by a contended
 // atomic, a node's samples are read in order, and nothing of a level passes
 // through the host. Per level:
-//   k_tr_units    the nodes' ranges cut into units of at most TR_CHUNK samples
+//   k_tr_units    the nodes' ranges cut into units of 256 or 512 samples
 //   k_tr_eval     one wavefront per unit, one lane per candidate: the
 //                 candidate's response for each sample, the right child's
 //                 sums in registers (the left's are the unit's less those); a
