@@ -6,11 +6,11 @@
 // stays the judge.
 //
 // Matrix products run on the gfx950 matrix cores (v_mfma_f32_16x16x32_bf16:
-// bfloat16 operands, FP32 accumulation). One wavefront owns a tile of 64 rows:
-// forward (two MFMA layers and an FP32 output dot), loss, and backward (weight
-// gradients and the hidden-layer input gradient are MFMA as well), staged in
-// LDS; per-tile gradient partials are summed in a fixed order, then Adam
-// updates the FP32 master weights and their bfloat16 copies are refreshed.
+// bfloat16 operands, FP32 accumulation). In training a workgroup owns a tile
+// of 64 rows: forward (two MFMA layers and an FP32 output dot), loss, and
+// backward (weight gradients and the hidden-layer input gradient are MFMA as
+// well); the per-tile gradient partials are summed in a fixed order by the
+// Adam step, which updates the FP32 master weights and their bfloat16 copies.
 //
 // Also here: the per-pixel inputs and the inlier labeller that trains the MLP
 // from poses accepted by the depth-difference check of Sec. 3.3.1, Eqs. 3-4
@@ -38,8 +38,8 @@ struct reloc_mlp {
     float *partial = nullptr;    // [cap_tiles][NP + 1]
     int cap_tiles = 0;
     uint16_t *q = nullptr;       // [NQ] bfloat16 copies
-    int32_t *rows = nullptr;     // [cap_rows] minibatch row indices
-    int cap_rows = 0;
+    float *loss = nullptr;       // [cap_loss] loss sums of the epochs' last minibatches
+    int cap_loss = 0;
     int step = 0;
 };
 
@@ -96,24 +96,28 @@ __global__ void k_mlp_pack(const float *__restrict__ w, uint16_t *__restrict__ q
 }
 
 // ---------------------------------------------------------------------------
-// one 64-row tile in LDS
+// training: one 64-row tile per workgroup
 // ---------------------------------------------------------------------------
 
-struct __align__(16) TileLds {
-    uint16_t X[ROWS * 32], XT[32 * ROWS];
-    uint16_t H1[ROWS * 64], H1T[64 * ROWS];
-    uint16_t H2[ROWS * 64];
-    uint16_t Db[ROWS * 64], DT[64 * ROWS];
-    float z[ROWS], dz[ROWS];
-};
-
-// X (row-major) -> XT
-__device__ __forceinline__ void tile_transpose_x(TileLds &S)
+// Orders one wavefront's LDS writes before its later reads of other lanes'
+// data (its LDS operations are performed in issue order).
+__device__ __forceinline__ void wave_sync()
 {
-    const int l = __lane_id();
-    for (int k = 0; k < 32; ++k) S.XT[k * ROWS + l] = S.X[l * 32 + k];
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+constexpr int TS = 72;   // row stride of a tile's arrays: 16-byte rows, off the banks' period
+
+struct __align__(16) TrainTile {
+    uint16_t XT[32 * TS];                  // [input][row]
+    uint16_t H1[ROWS * TS], H1T[64 * TS];  // [row][unit], [unit][row]
+    uint16_t H2[ROWS * TS];
+    uint16_t D2[ROWS * TS], D2T[64 * TS];  // loss gradient of layer 2's sums
+    uint16_t D1T[64 * TS];                 // and of layer 1's
+    float dz[5][ROWS];
+};
 
 // column sums of a 4-row-per-lane tile value over the 4 row groups of a wave
 __device__ __forceinline__ float col_sum(float s)
@@ -123,158 +127,292 @@ __device__ __forceinline__ float col_sum(float s)
     return s;
 }
 
-// backward of the tile: gradient partial (NP values) and the loss sum of the
-// valid rows (entry NP) into `out`; the target of label q is q / 255 and
-// dz = (sigmoid(z) - q / 255) * inv_n
-__device__ void tile_backward(TileLds &S, const uint16_t *__restrict__ q, const uint8_t *ys, int nvalid, float inv_n,
-                              float *__restrict__ out)
+// four values rounded to bfloat16, as two pairs
+__device__ __forceinline__ uint2 round4(const float v[4])
 {
-    const int l = __lane_id(), col = l & 15, r0 = (l >> 4) * 4;
-    {
-        const float z = S.z[l];
-        float dz = 0.0f, loss = 0.0f;
-        if (l < nvalid) {
-            const float y = (float)ys[l] / 255.0f;
-            dz = (1.0f / (1.0f + expf(-z)) - y) * inv_n;
-            loss = fmaxf(z, 0.0f) - z * y + log1pf(expf(-fabsf(z)));
+    return make_uint2(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]));
+}
+
+__device__ __forceinline__ uint16_t half_of(const uint2 &p, int i)
+{
+    return (uint16_t)((i & 2 ? p.y : p.x) >> (16 * (i & 1)));
+}
+
+// where a minibatch's rows come from: all rows in order (n_rows = 0), or drawn
+// uniformly with replacement by Philox (key (seed, 6), counter (epoch, step,
+// j, 0))
+struct RowDraw {
+    uint64_t seed;
+    int32_t n_rows, epoch, step;
+};
+
+// Gradient partial (NP values) and loss sum (entry NP) of one tile's rows:
+// forward, loss and backward. Wavefronts 0-3 have 16 units each of every layer
+// and hold the weights they multiply by in registers from the start (loaded
+// one by one inside the layers they were most of a launch's 34 us on a single
+// wavefront per tile; 64 tiles take 8.5 us this way, the chain of draws,
+// gathers and three exchanges); wavefront 4 stages the transposed inputs and
+// computes the output layer's gradient and the loss meanwhile. All wavefronts
+// compute the logits (lane = row), so that only the layers' activations and
+// layer 2's gradient pass between them. Every sum has the order of the
+// single-wavefront form: a product's k in two steps of 32, the logit over the
+// units, dw3 and db3 over the rows, biases over (16-row group, row) and then
+// the four row groups. The target of label q is q / 255 and
+// dz = (sigmoid(z) - q / 255) * inv_n.
+__global__ void __launch_bounds__(320) k_mlp_fwd_bwd(const uint16_t *__restrict__ X, const uint8_t *__restrict__ Y,
+                                                     RowDraw draw, int n, float inv_n, const uint16_t *__restrict__ q,
+                                                     const float *__restrict__ w, float *__restrict__ partial)
+{
+    __shared__ TrainTile S;
+    const int tile = blockIdx.x, wave = threadIdx.x >> 6, l = __lane_id();
+    const int col = l & 15, r0 = (l >> 4) * 4, kb = (l >> 4) * 8, c = 16 * (wave & 3) + col;
+    float *out = partial + (int64_t)tile * (NP + 1);
+    // lane's row of the tile, -1 past the minibatch's end
+    int32_t src = tile * ROWS + l < n ? tile * ROWS + l : -1;
+    if (draw.n_rows && src >= 0) {
+        const U4 u = philox((uint64_t)draw.epoch, (uint64_t)draw.step, (uint64_t)src, 0, draw.seed, TAG_MLP_BATCH);
+        src = (int32_t)uniform_int(u.x[0], (uint64_t)draw.n_rows);
+    }
+    const uint8_t label = src >= 0 ? Y[src] : (uint8_t)0;
+    const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0u, 0u, 0u, 0u));
+    bf16x8 xa[4], w1b, w2b[2], w2tb[2];
+    float b1c = 0.0f, b2c = 0.0f, w3c = 0.0f;
+    if (wave < 4) {
+#pragma unroll
+        for (int ti = 0; ti < 4; ++ti) {
+            const int32_t row = __shfl(src, 16 * ti + col, 64);
+            xa[ti] = row >= 0 ? load8(X + (int64_t)row * 32 + kb) : zero8;
         }
-        S.dz[l] = dz;
-        for (int o = 32; o >= 1; o >>= 1) loss += __shfl_xor(loss, o, 64);
-        if (l == 0) out[NP] = loss;
+        w1b = load8(q + QW1 + c * 32 + kb);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            w2b[k] = load8(q + QW2 + c * 64 + 32 * k + kb);
+            w2tb[k] = load8(q + QW2T + c * 64 + 32 * k + kb);
+        }
+        b1c = w[OB1 + c];
+        b2c = w[OB2 + c];
+        w3c = bf2f(q[QW3 + c]);
+    } else {
+        uint4 x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            x[k] = src >= 0 ? *(const uint4 *)(X + (int64_t)src * 32 + 8 * k) : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t v[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) S.XT[(8 * k + e) * TS + l] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+        }
+    }
+    const float b3 = w[OB3];
+    uint32_t on1 = 0u, on2 = 0u;   // the lane's 16 activations above 0, bit 4 ti + i
+    if (wave < 4) {
+        // layer 1: H1 = relu(X W1^T + b1)
+#pragma unroll
+        for (int ti = 0; ti < 4; ++ti) {
+            floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ti], w1b, acc, 0, 0, 0);
+            float hv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                hv[i] = acc[i] + b1c;
+                hv[i] = hv[i] > 0.0f ? hv[i] : 0.0f;
+            }
+            const uint2 h = round4(hv);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                on1 |= half_of(h, i) ? 1u << (4 * ti + i) : 0u;
+                S.H1[(16 * ti + r0 + i) * TS + c] = half_of(h, i);
+            }
+            *(uint2 *)(S.H1T + c * TS + 16 * ti + r0) = h;
+        }
     }
     __syncthreads();
-    {   // dw3[j] = sum_rows dz h2 (lane = j), db3 = sum dz
+    if (wave < 4) {
+        // layer 2: H2 = relu(H1 W2^T + b2)
+#pragma unroll
+        for (int ti = 0; ti < 4; ++ti) {
+            floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load8(S.H1 + (16 * ti + col) * TS + 32 * k + kb), w2b[k], acc,
+                                                              0, 0, 0);
+            float hv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                hv[i] = acc[i] + b2c;
+                hv[i] = hv[i] > 0.0f ? hv[i] : 0.0f;
+            }
+            const uint2 h = round4(hv);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                on2 |= half_of(h, i) ? 1u << (4 * ti + i) : 0u;
+                S.H2[(16 * ti + r0 + i) * TS + c] = half_of(h, i);
+            }
+        }
+    }
+    __syncthreads();
+    // output: z = w3 . h2 + b3 (FP32, lane = row), loss and its gradient
+    float z = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint4 h = *(const uint4 *)(S.H2 + l * TS + 8 * k), v = *(const uint4 *)(q + QW3 + 8 * k);
+        const uint32_t hw[4] = {h.x, h.y, h.z, h.w}, vw[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            z = fmaf(__uint_as_float(vw[e] << 16), __uint_as_float(hw[e] << 16), z);
+            z = fmaf(__uint_as_float(vw[e] & 0xFFFF0000u), __uint_as_float(hw[e] & 0xFFFF0000u), z);
+        }
+    }
+    z = z + b3;
+    const bool valid = tile * ROWS + l < n;
+    const float y = (float)label / 255.0f;
+    S.dz[wave][l] = valid ? (1.0f / (1.0f + expf(-z)) - y) * inv_n : 0.0f;
+    wave_sync();
+    const float *dz = S.dz[wave];
+    if (wave == 4) {
+        float loss = valid ? fmaxf(z, 0.0f) - z * y + log1pf(expf(-fabsf(z))) : 0.0f;
+        for (int o = 32; o >= 1; o >>= 1) loss += __shfl_xor(loss, o, 64);
+        if (l == 0) out[NP] = loss;
+        // dw3[j] = sum_rows dz h2 (lane = j), db3 = sum dz
         float g = 0.0f, b = 0.0f;
+#pragma unroll 16
         for (int row = 0; row < ROWS; ++row) {
-            g = fmaf(S.dz[row], bf2f(S.H2[row * 64 + l]), g);
-            b += S.dz[row];
+            g = fmaf(dz[row], bf2f(S.H2[row * TS + l]), g);
+            b += dz[row];
         }
         out[OW3 + l] = g;
         if (l == 0) out[OB3] = b;
-    }
-    // dH2 = dz w3 [h2 > 0]; db2 = column sums
-    for (int tj = 0; tj < 4; ++tj) {
-        const int c = 16 * tj + col;
-        const float w3 = bf2f(q[QW3 + c]);
+    } else {
+        // dH2 = dz w3 [h2 > 0]; db2 = column sums
         float bs = 0.0f;
-        for (int ti = 0; ti < 4; ++ti)
+#pragma unroll
+        for (int ti = 0; ti < 4; ++ti) {
+            const float4 dr = *(const float4 *)(dz + 16 * ti + r0);
+            const float drow[4] = {dr.x, dr.y, dr.z, dr.w};
+            float d[4];
+#pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int row = 16 * ti + r0 + i;
-                const float d = S.H2[row * 64 + c] ? S.dz[row] * w3 : 0.0f;
-                bs += d;
-                const uint16_t h = f2bf(d);
-                S.Db[row * 64 + c] = h;
-                S.DT[c * ROWS + row] = h;
+                d[i] = (on2 >> (4 * ti + i)) & 1u ? drow[i] * w3c : 0.0f;
+                bs += d[i];
             }
+            const uint2 h = round4(d);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) S.D2[(16 * ti + r0 + i) * TS + c] = half_of(h, i);
+            *(uint2 *)(S.D2T + c * TS + 16 * ti + r0) = h;
+        }
         bs = col_sum(bs);
         if (l < 16) out[OB2 + c] = bs;
-    }
-    __syncthreads();
-    // dW2 = dH2^T H1
-    for (int ti = 0; ti < 4; ++ti)
+        wave_sync();
+        // dW2 = dH2^T H1: this wavefront's units (its own rows of D2T) by all of layer 1's
+        bf16x8 a[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) a[k] = load8(S.D2T + c * TS + 32 * k + kb);
+#pragma unroll
         for (int tj = 0; tj < 4; ++tj) {
             floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            acc = mfma_tile(S.DT + 16 * ti * ROWS, ROWS, S.H1T + 16 * tj * ROWS, ROWS, ROWS, acc);
-            for (int i = 0; i < 4; ++i) out[OW2 + (16 * ti + r0 + i) * 64 + 16 * tj + col] = acc[i];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[k], load8(S.H1T + (16 * tj + col) * TS + 32 * k + kb), acc, 0,
+                                                              0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[OW2 + (16 * wave + r0 + i) * 64 + 16 * tj + col] = acc[i];
         }
-    __syncthreads();
-    // dH1 = dH2 W2 [h1 > 0] (into DT, transposed); db1 = column sums
-    for (int tj = 0; tj < 4; ++tj) {
-        const int c = 16 * tj + col;
-        float bs = 0.0f;
-        floatx4 acc[4];
-        for (int ti = 0; ti < 4; ++ti) {
-            floatx4 a0 = {0.0f, 0.0f, 0.0f, 0.0f};
-            acc[ti] = mfma_tile(S.Db + 16 * ti * 64, 64, q + QW2T + 16 * tj * 64, 64, 64, a0);
-        }
-        __syncthreads();
-        for (int ti = 0; ti < 4; ++ti)
-            for (int i = 0; i < 4; ++i) {
-                const int row = 16 * ti + r0 + i;
-                const float d = S.H1[row * 64 + c] ? acc[ti][i] : 0.0f;
-                bs += d;
-                S.DT[c * ROWS + row] = f2bf(d);
-            }
-        bs = col_sum(bs);
-        if (l < 16) out[OB1 + c] = bs;
     }
     __syncthreads();
+    if (wave == 4) return;
+    // dH1 = dH2 W2 [h1 > 0]; db1 = column sums
+    float bs = 0.0f;
+#pragma unroll
+    for (int ti = 0; ti < 4; ++ti) {
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load8(S.D2 + (16 * ti + col) * TS + 32 * k + kb), w2tb[k], acc, 0, 0,
+                                                          0);
+        float d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            d[i] = (on1 >> (4 * ti + i)) & 1u ? acc[i] : 0.0f;
+            bs += d[i];
+        }
+        *(uint2 *)(S.D1T + c * TS + 16 * ti + r0) = round4(d);
+    }
+    bs = col_sum(bs);
+    if (l < 16) out[OB1 + c] = bs;
+    wave_sync();
     // dW1 = dH1^T X (input columns 24..31 are padding)
-    for (int ti = 0; ti < 4; ++ti)
-        for (int tj = 0; tj < 2; ++tj) {
-            floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            acc = mfma_tile(S.DT + 16 * ti * ROWS, ROWS, S.XT + 16 * tj * ROWS, ROWS, ROWS, acc);
-            const int c = 16 * tj + col;
-            if (c < 24)
-                for (int i = 0; i < 4; ++i) out[OW1 + (16 * ti + r0 + i) * 24 + c] = acc[i];
-        }
-    __syncthreads();
-}
-
-// rows r0.. of X (or the rows listed in idx) into the tile
-__device__ void tile_load(TileLds &S, const uint16_t *__restrict__ X, const int32_t *__restrict__ idx, int r0, int n)
-{
-    const int l = __lane_id();
-    const int row = r0 + l;
-    uint4 *d = (uint4 *)(S.X + l * 32);
-    if (row < n) {
-        const int64_t src = idx ? idx[row] : row;
-        const uint4 *s = (const uint4 *)(X + src * 32);
-        for (int k = 0; k < 4; ++k) d[k] = s[k];
-    } else {
-        for (int k = 0; k < 4; ++k) d[k] = make_uint4(0, 0, 0, 0);
+    bf16x8 a[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) a[k] = load8(S.D1T + c * TS + 32 * k + kb);
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj) {
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[k], load8(S.XT + (16 * tj + col) * TS + 32 * k + kb), acc, 0, 0, 0);
+        const int x = 16 * tj + col;
+        if (x < 24)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[OW1 + (16 * wave + r0 + i) * 24 + x] = acc[i];
     }
-    __syncthreads();
-    tile_transpose_x(S);
 }
 
-__global__ void __launch_bounds__(64) k_mlp_fwd_bwd(const uint16_t *__restrict__ X, const uint8_t *__restrict__ Y,
-                                                    const int32_t *__restrict__ idx, int n, float inv_n,
-                                                    const uint16_t *__restrict__ q, const float *__restrict__ w,
-                                                    float *__restrict__ partial)
+// sum over the tiles of one gradient entry, in tile order (the additions wait
+// for one another, so a batch's loads are issued ahead of them)
+__device__ __forceinline__ float tile_sum(const float *__restrict__ partial, int tiles, int k)
 {
-    __shared__ TileLds S;
-    __shared__ uint8_t ys[ROWS];
-    const int tile = blockIdx.x, r0 = tile * ROWS, l = __lane_id();
-    tile_load(S, X, idx, r0, n);
-    const int row = r0 + l;
-    ys[l] = row < n ? Y[idx ? idx[row] : row] : 0;
-    __syncthreads();
-    tile_forward<TileLds, true>(S, q, w);
-    tile_backward(S, q, ys, min(ROWS, n - r0), inv_n, partial + (int64_t)tile * (NP + 1));
-}
-
-// fixed-order sum of the tile partials (gradient and loss)
-__global__ void k_mlp_reduce(const float *__restrict__ partial, int tiles, float *__restrict__ grad)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k > NP) return;
+    constexpr int B = 32;
     float s = 0.0f;
-    for (int t = 0; t < tiles; ++t) s += partial[(int64_t)t * (NP + 1) + k];
-    grad[k] = s;
+    for (int t0 = 0; t0 < tiles; t0 += B) {
+        float v[B];
+#pragma unroll
+        for (int t = 0; t < B; ++t) v[t] = partial[(int64_t)min(t0 + t, tiles - 1) * (NP + 1) + k];
+#pragma unroll
+        for (int t = 0; t < B; ++t)
+            if (t0 + t < tiles) s += v[t];
+    }
+    return s;
 }
 
-__global__ void k_mlp_adam(float *__restrict__ w, float *__restrict__ m, float *__restrict__ v,
-                           const float *__restrict__ grad, float lr, float c1, float c2)
+__global__ void __launch_bounds__(64) k_mlp_reduce(const float *__restrict__ partial, int tiles, float *__restrict__ grad)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= NP) return;
-    const float g = grad[k];
-    const float mk = 0.9f * m[k] + 0.1f * g;
-    const float vk = 0.999f * v[k] + 0.001f * g * g;
+    const int k = blockIdx.x * 64 + threadIdx.x;
+    if (k <= NP) grad[k] = tile_sum(partial, tiles, k);
+}
+
+// One Adam step from the tiles' partials: the entry's sum, its moments, the
+// FP32 weight and its bfloat16 copies; the thread past the parameters writes
+// the minibatch's loss sum to *loss where one is wanted. (Sum, Adam and copies
+// as three kernels took 16.0 + 4.7 + 4.6 us a step of 64 tiles; this takes 4.7.)
+__global__ void __launch_bounds__(64) k_mlp_update(const float *__restrict__ partial, int tiles, float *__restrict__ w,
+                                                   float *__restrict__ m, float *__restrict__ v, uint16_t *__restrict__ q,
+                                                   float lr, float c1, float c2, float *__restrict__ loss)
+{
+    const int k = blockIdx.x * 64 + threadIdx.x;
+    if (k > NP) return;
+    if (k == NP) {
+        if (loss) *loss = tile_sum(partial, tiles, k);
+        return;
+    }
+    const float m0 = m[k], v0 = v[k], w0 = w[k];
+    const float g = tile_sum(partial, tiles, k);
+    const float mk = 0.9f * m0 + 0.1f * g;
+    const float vk = 0.999f * v0 + 0.001f * g * g;
     m[k] = mk;
     v[k] = vk;
-    w[k] -= lr * (mk / c1) / (sqrtf(vk / c2) + 1e-8f);
-}
-
-// rows of minibatch `step` of `epoch`: uniform with replacement (Philox key
-// (seed, 6), counter (epoch, step, j, 0))
-__global__ void k_mlp_rows(int32_t *__restrict__ rows, int nb, int n_rows, uint64_t seed, int epoch, int step)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= nb) return;
-    const U4 u = philox((uint64_t)epoch, (uint64_t)step, (uint64_t)j, 0, seed, TAG_MLP_BATCH);
-    rows[j] = (int32_t)uniform_int(u.x[0], (uint64_t)n_rows);
+    const float wk = w0 - lr * (mk / c1) / (sqrtf(vk / c2) + 1e-8f);
+    w[k] = wk;
+    const uint16_t h = f2bf(wk);
+    if (k < OB1) {
+        q[QW1 + (k / 24) * 32 + k % 24] = h;
+    } else if (k >= OW2 && k < OB2) {
+        const int e = k - OW2;
+        q[QW2 + e] = h;
+        q[QW2T + (e & 63) * 64 + (e >> 6)] = h;
+    } else if (k >= OW3 && k < OB3) {
+        q[QW3 + k - OW3] = h;
+    }
 }
 
 __global__ void __launch_bounds__(64) k_mlp_logits(const uint16_t *__restrict__ X, int n,
@@ -411,27 +549,26 @@ static int ensure_tiles(reloc_mlp *m, int tiles)
     return RELOC_OK;
 }
 
-static int ensure_rows(reloc_mlp *m, int n)
+static int ensure_loss(reloc_mlp *m, int n)
 {
-    if (n <= m->cap_rows) return RELOC_OK;
-    if (m->rows) (void)hipFree(m->rows);
-    m->rows = nullptr;
-    m->cap_rows = 0;
-    RL_HIP(hipMalloc((void **)&m->rows, (size_t)n * sizeof(int32_t)));
-    m->cap_rows = n;
+    if (n <= m->cap_loss) return RELOC_OK;
+    if (m->loss) (void)hipFree(m->loss);
+    m->loss = nullptr;
+    m->cap_loss = 0;
+    RL_HIP(hipMalloc((void **)&m->loss, (size_t)n * sizeof(float)));
+    m->cap_loss = n;
     return RELOC_OK;
 }
 
-// gradient of the mean loss over rows (idx or 0..n-1) into m->grad
-static int mlp_gradient(reloc_mlp *m, const uint16_t *X, const uint8_t *Y, const int32_t *idx, int n, hipStream_t s)
+// the tiles' gradient partials of the mean loss over n rows into m->partial
+static int mlp_partials(reloc_mlp *m, const uint16_t *X, const uint8_t *Y, const RowDraw &draw, int n, int *tiles,
+                        hipStream_t s)
 {
-    const int tiles = (n + ROWS - 1) / ROWS;
-    int rc = ensure_tiles(m, tiles);
+    *tiles = (n + ROWS - 1) / ROWS;
+    int rc = ensure_tiles(m, *tiles);
     if (rc) return rc;
-    RL_LAUNCH("k_mlp_fwd_bwd", k_mlp_fwd_bwd, dim3(tiles), dim3(64), 0, s, X, Y, idx, n, 1.0f / (float)n, m->q, m->w,
+    RL_LAUNCH("k_mlp_fwd_bwd", k_mlp_fwd_bwd, dim3(*tiles), dim3(320), 0, s, X, Y, draw, n, 1.0f / (float)n, m->q, m->w,
               m->partial);
-    RL_LAUNCH("k_mlp_reduce", k_mlp_reduce, dim3((NP + 1 + 255) / 256), dim3(256), 0, s, m->partial, tiles, m->grad);
-    RL_HIP(hipGetLastError());
     return RELOC_OK;
 }
 
@@ -538,7 +675,7 @@ static void mlp_free(reloc_mlp *m)
     (void)hipFree(m->grad);
     (void)hipFree(m->partial);
     (void)hipFree(m->q);
-    (void)hipFree(m->rows);
+    (void)hipFree(m->loss);
 }
 
 extern "C" int reloc_mlp_create(uint64_t seed, void *stream, reloc_mlp **out)
@@ -603,8 +740,11 @@ extern "C" int reloc_mlp_gradient(reloc_mlp *m, const uint16_t *x_dev, const uin
 {
     if (!m || !x_dev || !y_dev || n < 1 || !grad_host || ((uintptr_t)x_dev & 15)) return RELOC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
-    int rc = mlp_gradient(m, x_dev, y_dev, nullptr, n, s);
+    int tiles = 0;
+    int rc = mlp_partials(m, x_dev, y_dev, RowDraw{0, 0, 0, 0}, n, &tiles, s);
     if (rc) return rc;
+    RL_LAUNCH("k_mlp_reduce", k_mlp_reduce, dim3((NP + 1 + 63) / 64), dim3(64), 0, s, m->partial, tiles, m->grad);
+    RL_HIP(hipGetLastError());
     std::vector<float> g(NP + 1);
     RL_HIP(hipMemcpyAsync(g.data(), m->grad, (NP + 1) * 4, hipMemcpyDeviceToHost, s));
     RL_HIP(hipStreamSynchronize(s));
@@ -621,32 +761,27 @@ extern "C" int reloc_mlp_train(reloc_mlp *m, const uint16_t *x_dev, const uint8_
         ((uintptr_t)x_dev & 15))
         return RELOC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
-    int rc = ensure_rows(m, batch_rows);
+    int rc = ensure_loss(m, std::max(epochs, 1));
     if (rc) return rc;
     const int steps = std::max(1, n_rows / batch_rows);
-    std::vector<float> g(NP + 1);
     for (int e = 0; e < epochs; ++e) {
-        double loss = 0.0;
         for (int st = 0; st < steps; ++st) {
-            RL_LAUNCH("k_mlp_rows", k_mlp_rows, dim3((batch_rows + 255) / 256), dim3(256), 0, s, m->rows, batch_rows,
-                      n_rows, seed, e, st);
-            rc = mlp_gradient(m, x_dev, y_dev, m->rows, batch_rows, s);
+            int tiles = 0;
+            rc = mlp_partials(m, x_dev, y_dev, RowDraw{seed, n_rows, e, st}, batch_rows, &tiles, s);
             if (rc) return rc;
             m->step++;
             const float c1 = 1.0f - powf(0.9f, (float)m->step), c2 = 1.0f - powf(0.999f, (float)m->step);
-            RL_LAUNCH("k_mlp_adam", k_mlp_adam, dim3((NP + 255) / 256), dim3(256), 0, s, m->w, m->m, m->v, m->grad, lr,
-                      c1, c2);
-            rc = mlp_pack(m, s);
-            if (rc) return rc;
-            if (epoch_loss_host && st == steps - 1) {
-                RL_HIP(hipMemcpyAsync(g.data(), m->grad, (NP + 1) * 4, hipMemcpyDeviceToHost, s));
-                RL_HIP(hipStreamSynchronize(s));
-                loss = g[NP] / (double)batch_rows;
-            }
+            RL_LAUNCH("k_mlp_update", k_mlp_update, dim3((NP + 1 + 63) / 64), dim3(64), 0, s, m->partial, tiles, m->w, m->m,
+                      m->v, m->q, lr, c1, c2, st == steps - 1 ? m->loss + e : nullptr);
         }
-        if (epoch_loss_host) epoch_loss_host[e] = (float)loss;
     }
     RL_HIP(hipGetLastError());
+    if (epoch_loss_host && epochs > 0) {
+        std::vector<float> g(epochs);
+        RL_HIP(hipMemcpyAsync(g.data(), m->loss, epochs * sizeof(float), hipMemcpyDeviceToHost, s));
+        RL_HIP(hipStreamSynchronize(s));
+        for (int e = 0; e < epochs; ++e) epoch_loss_host[e] = (float)(g[e] / (double)batch_rows);
+    }
     return RELOC_OK;
 }
 

@@ -81,52 +81,6 @@ __device__ __forceinline__ void stage_head(InTile &S, const uint16_t *__restrict
     }
 }
 
-// Forward pass of the 64 rows in S.X (bfloat16, 24 inputs + 8 zeros): H1, H2
-// in bfloat16, logits in S.z. With kTrans the tile also keeps H1 transposed
-// (for the weight gradient of layer 2).
-template <class Tile, bool kTrans>
-__device__ void tile_forward(Tile &S, const uint16_t *__restrict__ q, const float *__restrict__ w)
-{
-    const int l = __lane_id(), col = l & 15, r0 = (l >> 4) * 4;
-    // layer 1: H1 = relu(X W1^T + b1), stored bfloat16
-#pragma unroll 1
-    for (int ti = 0; ti < 4; ++ti)
-        for (int tj = 0; tj < 4; ++tj) {
-            floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            acc = mfma_tile(S.X + 16 * ti * 32, 32, q + QW1 + 16 * tj * 32, 32, 32, acc);
-            const int c = 16 * tj + col;
-            const float b = w[OB1 + c];
-            for (int i = 0; i < 4; ++i) {
-                const int row = 16 * ti + r0 + i;
-                const float hv = acc[i] + b;
-                const uint16_t h = hv > 0.0f ? f2bf(hv) : (uint16_t)0;
-                S.H1[row * 64 + c] = h;
-                if constexpr (kTrans) S.H1T[c * ROWS + row] = h;
-            }
-        }
-    __syncthreads();
-    // layer 2: H2 = relu(H1 W2^T + b2)
-#pragma unroll 1
-    for (int ti = 0; ti < 4; ++ti)
-        for (int tj = 0; tj < 4; ++tj) {
-            floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            acc = mfma_tile(S.H1 + 16 * ti * 64, 64, q + QW2 + 16 * tj * 64, 64, 64, acc);
-            const int c = 16 * tj + col;
-            const float b = w[OB2 + c];
-            for (int i = 0; i < 4; ++i) {
-                const int row = 16 * ti + r0 + i;
-                const float hv = acc[i] + b;
-                S.H2[row * 64 + c] = hv > 0.0f ? f2bf(hv) : (uint16_t)0;
-            }
-        }
-    __syncthreads();
-    // output: z = w3 . h2 + b3 (FP32, lane = row)
-    float z = 0.0f;
-    for (int j = 0; j < 64; ++j) z = fmaf(bf2f(q[QW3 + j]), bf2f(S.H2[l * 64 + j]), z);
-    S.z[l] = z + w[OB3];
-    __syncthreads();
-}
-
 // Layer 1's A operand for hidden rows 16 tj .. + 15 as lane l supplies it:
 // row 16 tj + (l & 15) of W1 (bfloat16, [64][32]), k-block 8 (l >> 4) .. + 7.
 __device__ __forceinline__ bf16x8 w1_operand(const uint16_t *__restrict__ q, int tj, int l)
@@ -155,7 +109,7 @@ __device__ __forceinline__ bf16x8 w2_operand(const uint16_t *__restrict__ q, int
 // from that lane for its two 32-wide k-chunks, once W2's columns are taken in
 // the same order (w2_operand; an MFMA sums the same products whatever the
 // slot order). H1 and H2 are rounded to bfloat16 (nearest even, by the
-// conversion instruction) after bias and ReLU as in tile_forward; the output
+// conversion instruction) after bias and ReLU as in training; the output
 // dot w3 . h2 is summed per lane over its 16 hidden units, then over the four
 // lane groups.
 __device__ __forceinline__ float tile_forward_core(const uint16_t *X, const bf16x8 a1[4], const bf16x8 a2[4][2],
