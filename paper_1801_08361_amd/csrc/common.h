@@ -85,9 +85,24 @@ constexpr int MAX_TM = 512;     // modes over all trees of one pixel (T * M)
 constexpr int MAX_ROUNDS = 13;  // ceil(log2(MAX_HYP)) + 1
 
 // mode colour rows: M colours padded to a multiple of 4 (16-byte rows for
-// vector loads); slots without a mode hold RGB_NONE (a real colour has a zero
-// top byte)
+// vector loads), each as three 10-bit fields r, g, b with bit 9 of every field
+// set: with a window's bounds in the same fields, one subtraction per bound
+// leaves bit 9 of each channel set exactly when the channel is inside. Slots
+// without a mode hold RGB_NONE, which is outside every window (its red field
+// is 1023).
 constexpr uint32_t RGB_NONE = 0xFFFFFFFFu;
+constexpr uint32_t RGB_GUARD = (1u << 9) | (1u << 19) | (1u << 29);
+
+// field code of a colour r | g << 8 | b << 16 (RGB_NONE, and any other word
+// with a top byte, is no colour), and back
+__host__ __device__ __forceinline__ uint32_t rgb_code(uint32_t c)
+{
+    return c >> 24 ? RGB_NONE : (c & 0xFFu) | ((c & 0xFF00u) << 2) | ((c & 0xFF0000u) << 4) | RGB_GUARD;
+}
+__host__ __device__ __forceinline__ uint32_t rgb_of_code(uint32_t c)
+{
+    return c == RGB_NONE ? c : (c & 0xFFu) | ((c >> 2) & 0xFF00u) | ((c >> 4) & 0xFF0000u);
+}
 __host__ __device__ __forceinline__ int rgb_stride(int M) { return (M + 3) & ~3; }
 
 // ---------------------------------------------------------------------------

@@ -947,7 +947,7 @@ __device__ __forceinline__ void leaf_modes(const Entry *__restrict__ pts, int n,
         md.n = (int32_t)nmm;
         md.rgb = (uint32_t)(a[9] / nmm) | ((uint32_t)(a[10] / nmm) << 8) | ((uint32_t)(a[11] / nmm) << 16);
         out[tid] = md;
-        if (rgb_out) rgb_out[tid] = md.rgb;
+        if (rgb_out) rgb_out[tid] = rgb_code(md.rgb);
     } else if (rgb_out && tid < rgb_len) {
         rgb_out[tid] = RGB_NONE;
     }
@@ -1368,7 +1368,7 @@ extern "C" int reloc_forest_drop_reservoirs(reloc_forest *f, void *stream)
 // File layout (little-endian, this library's own format): a FileHeader, then
 // the split nodes (u64 [T (L - 1) + 8]), leaf counters (u32 [T L]), mode
 // counts (i32 [T L]), modes (Mode [T L M]), mode colour rows
-// (u32 [T L rgb_stride(M)]), learned-input leaf summaries (float4 [T L 4])
+// (u32 [T L rgb_stride(M)], as r | g << 8 | b << 16 or RGB_NONE), learned-input leaf summaries (float4 [T L 4])
 // and, unless the reservoirs were dropped, the reservoirs (Entry [T L R]).
 // Slot stamps are not stored: a stamp only has to be below every k + 1 that
 // later frames can produce, and every later k is at least the leaf's counter,
@@ -1397,27 +1397,34 @@ struct Staging {
     }
 };
 
-// device -> file in chunks through pinned host memory
-int save_section(FILE *fp, const void *dev, size_t bytes, Staging &st, hipStream_t s)
+// device -> file in chunks through pinned host memory, every 32-bit word
+// passed through `word` on the way where it is given
+int save_section(FILE *fp, const void *dev, size_t bytes, Staging &st, hipStream_t s,
+                 uint32_t (*word)(uint32_t) = nullptr)
 {
     const char *src = (const char *)dev;
     for (size_t off = 0; off < bytes; off += STAGE_BYTES) {
         const size_t n = std::min(STAGE_BYTES, bytes - off);
         RL_HIP(hipMemcpyAsync(st.buf, src + off, n, hipMemcpyDeviceToHost, s));
         RL_HIP(hipStreamSynchronize(s));
+        if (word)
+            for (size_t i = 0; i < n / 4; ++i) ((uint32_t *)st.buf)[i] = word(((uint32_t *)st.buf)[i]);
         if (fwrite(st.buf, 1, n, fp) != n) return RELOC_E_IO;
     }
     return RELOC_OK;
 }
 
-// file -> device in chunks through pinned host memory
-int load_section(FILE *fp, void *dev, size_t bytes, Staging &st, hipStream_t s)
+// file -> device in chunks through pinned host memory, with `word` as above
+int load_section(FILE *fp, void *dev, size_t bytes, Staging &st, hipStream_t s,
+                 uint32_t (*word)(uint32_t) = nullptr)
 {
     char *dst = (char *)dev;
     for (size_t off = 0; off < bytes; off += STAGE_BYTES) {
         const size_t n = std::min(STAGE_BYTES, bytes - off);
         RL_HIP(hipStreamSynchronize(s));   // the previous chunk has left the staging buffer
         if (fread(st.buf, 1, n, fp) != n) return RELOC_E_IO;
+        if (word)
+            for (size_t i = 0; i < n / 4; ++i) ((uint32_t *)st.buf)[i] = word(((uint32_t *)st.buf)[i]);
         RL_HIP(hipMemcpyAsync(dst + off, st.buf, n, hipMemcpyHostToDevice, s));
     }
     RL_HIP(hipStreamSynchronize(s));
@@ -1455,7 +1462,7 @@ int save_forest(Forest *f, FILE *fp, hipStream_t s)
     if ((rc = save_section(fp, f->counter, h.n_leaves * sizeof(uint32_t), st, s))) return rc;
     if ((rc = save_section(fp, f->nmodes, h.n_leaves * sizeof(int32_t), st, s))) return rc;
     if ((rc = save_section(fp, f->modes, h.n_mode_slots * sizeof(Mode), st, s))) return rc;
-    if ((rc = save_section(fp, f->mode_rgb, h.n_rgb * sizeof(uint32_t), st, s))) return rc;
+    if ((rc = save_section(fp, f->mode_rgb, h.n_rgb * sizeof(uint32_t), st, s, rgb_of_code))) return rc;
     if ((rc = save_section(fp, f->leaf_in, h.n_leaves * 4 * sizeof(float4), st, s))) return rc;
     if (!f->dropped && (rc = save_section(fp, f->res, h.n_res * sizeof(Entry), st, s))) return rc;
     return RELOC_OK;
@@ -1506,7 +1513,7 @@ int load_forest(FILE *fp, hipStream_t s, reloc_forest **out)
     if (!rc) rc = load_section(fp, f->counter, h.n_leaves * sizeof(uint32_t), st, s);
     if (!rc) rc = load_section(fp, f->nmodes, h.n_leaves * sizeof(int32_t), st, s);
     if (!rc) rc = load_section(fp, f->modes, h.n_mode_slots * sizeof(Mode), st, s);
-    if (!rc) rc = load_section(fp, f->mode_rgb, h.n_rgb * sizeof(uint32_t), st, s);
+    if (!rc) rc = load_section(fp, f->mode_rgb, h.n_rgb * sizeof(uint32_t), st, s, rgb_code);
     if (!rc) rc = load_section(fp, f->leaf_in, h.n_leaves * 4 * sizeof(float4), st, s);
     if (!rc && !h.dropped) rc = load_section(fp, f->res, h.n_res * sizeof(Entry), st, s);
     if (!rc && fgetc(fp) != EOF) rc = RELOC_E_IO;   // trailing bytes: not a file this version wrote

@@ -494,34 +494,26 @@ __device__ __forceinline__ float sq3(const float a[3], const float b[3])
 
 // The colour test of a hypothesis pick, |a_c - p_c| <= tol in each channel,
 // as a window per channel: max(p_c - tol, 0) <= a_c <= min(p_c + tol, 255)
-// (equivalent for colours 0..255 and tol >= 0). Red and green are tested
-// together as two 16-bit lanes; blue is tested with the byte above it, which
-// is 0 for a mode's colour and 0xFF in an empty slot, so empty slots fail.
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+// (equivalent for colours 0..255 and tol >= 0), on the modes' field codes
+// (rgb_code): a code less the lower bounds, and the upper bounds with twice the
+// guard bits less the code, keep every channel's guard bit exactly when it is
+// inside (512 + a - lo and 512 + hi - a lie in 257 .. 767). 4 instructions a
+// mode, where the clamps of unpacked channels took 9.
 struct ColourWin {
-    u16x2 lo, hi;       // red, green
-    uint32_t blo, bhi;  // blue
+    uint32_t lo, hi;
 };
 
 __device__ __forceinline__ ColourWin colour_win(uint32_t r, uint32_t g, uint32_t b, int tol)
 {
-    auto lo = [&](uint32_t c) { return (unsigned short)((int)c - tol < 0 ? 0 : (int)c - tol); };
-    auto hi = [&](uint32_t c) { return (unsigned short)((int)c + tol > 255 ? 255 : (int)c + tol); };
-    ColourWin w;
-    w.lo = u16x2{lo(r), lo(g)};
-    w.hi = u16x2{hi(r), hi(g)};
-    w.blo = lo(b);
-    w.bhi = hi(b);
-    return w;
+    const int d = min(tol, 255);
+    auto lo = [&](uint32_t c) { return (uint32_t)max((int)c - d, 0); };
+    auto hi = [&](uint32_t c) { return (uint32_t)min((int)c + d, 255); };
+    return ColourWin{lo(r) | (lo(g) << 10) | (lo(b) << 20), (hi(r) | (hi(g) << 10) | (hi(b) << 20)) + 2u * RGB_GUARD};
 }
 
 __device__ __forceinline__ bool colour_in(uint32_t a, const ColourWin &w)
 {
-    const uint32_t rg = (a & 0xFFu) | ((a << 8) & 0xFF0000u);
-    const u16x2 x = __builtin_bit_cast(u16x2, rg);
-    const u16x2 c = __builtin_elementwise_min(__builtin_elementwise_max(x, w.lo), w.hi);
-    const uint32_t bt = a >> 16;
-    return __builtin_bit_cast(uint32_t, c) == rg && min(max(bt, w.blo), w.bhi) == bt;
+    return ((a - w.lo) & (w.hi - a) & RGB_GUARD) == RGB_GUARD;
 }
 
 // pool index for draw u: uniform, or the first pool entry whose inclusive
@@ -543,174 +535,191 @@ __device__ __forceinline__ int pick_pool(const Attempt &A, int np, uint64_t u)
     return lo;
 }
 
-// Colour-consistent modes of one leaf as a bit mask: bit m is set when slot m
-// holds a mode whose colour is within tol of (pr, pg, pb) in every channel.
-// The row is read with 16-byte loads (rgb_stride(M) colours). Mask is a
-// 32-bit word for up to 32 modes per leaf, else a 64-bit one.
-template <typename Mask>
-__device__ __forceinline__ Mask colour_mask(const uint32_t *__restrict__ row, int Mp, const ColourWin &w)
-{
-    Mask mask = 0;
-    for (int q = 0; q < Mp; q += 4) {
-        const uint4 v = *(const uint4 *)(row + q);
-        const uint32_t c[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (colour_in(c[e], w)) mask |= (Mask)1 << (q + e);
-    }
-    return mask;
-}
-
 __device__ __forceinline__ int popc_mask(uint32_t m) { return __popc(m); }
 __device__ __forceinline__ int popc_mask(uint64_t m) { return __popcll((unsigned long long)m); }
 __device__ __forceinline__ int ffs_mask(uint32_t m) { return __ffs(m); }
 __device__ __forceinline__ int ffs_mask(uint64_t m) { return __ffsll((unsigned long long)m); }
 
-// the same for rows of at most 12 colours, with the row's loads issued
-// before any test
-__device__ __forceinline__ uint32_t colour_mask12(const uint32_t *__restrict__ row, int Mp, const ColourWin &w)
+// Colour-consistent modes of NJ leaves as bit masks: bit m of mask[j] is set
+// when slot m of row j holds a mode whose colour is within window j. A row's
+// 16-byte loads (rgb_stride(M) = 4 n4 colours) are issued QB at a time, for all
+// NJ rows, before any test; past the row's end they read its last again, so
+// that no load waits behind a branch, and those bits are dropped.
+template <typename Mask, int NJ, int QB>
+__device__ __forceinline__ void colour_masks(const uint32_t *const row[NJ], int n4, const ColourWin win[NJ], Mask mask[NJ])
 {
-    const uint4 none = make_uint4(RGB_NONE, RGB_NONE, RGB_NONE, RGB_NONE);
-    const uint4 *r4 = (const uint4 *)row;
-    const uint4 v0 = r4[0];
-    const uint4 v1 = Mp > 4 ? r4[1] : none;
-    const uint4 v2 = Mp > 8 ? r4[2] : none;
-    const uint32_t c[12] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w, v2.x, v2.y, v2.z, v2.w};
-    uint32_t mask = 0;
 #pragma unroll
-    for (int e = 0; e < 12; ++e)
-        if (colour_in(c[e], w)) mask |= 1u << e;
-    return mask;
-}
-
-// one try: draws, colour-consistent mode picks, FP32 checks, FP64 alignment
-// and residuals. The pick of pixel j is the sel-th colour-consistent mode in
-// (tree, mode) order, sel = uniform_int(u, count). Loads are issued a stage at
-// a time (pool entries; pixel colours and depths; per pixel, its leaves and
-// then its mode colour rows; the three picked modes) so that each stage
-// waits once.
-template <typename Mask>
-__device__ bool try_hypothesis(const Attempt &A, int np, uint64_t h, uint64_t tau, double R[9], double t[3],
-                               int32_t *__restrict__ s_li, Mask *__restrict__ s_mask, int ps)
-{
-    const U4 a = philox(h, tau, 0, 0, A.seed, TAG_HYP);
-    const U4 b = philox(h, tau, 1, 0, A.seed, TAG_HYP);
-    const int Mp = rgb_stride(A.M);
-    int pi[3], p[3];
+    for (int j = 0; j < NJ; ++j) mask[j] = 0;
+    for (int q0 = 0; q0 < n4; q0 += QB) {
+        uint4 v[NJ][QB];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) pi[j] = pick_pool(A, np, a.x[j]);
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) p[j] = A.pool[pi[j]];
-    uint32_t pr[3], pg[3], pb[3], dep[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const uint64_t pw = A.packed[p[j]];   // pool pixels are valid: the word holds their depth
-        dep[j] = packed_depth(pw);
-        pr[j] = packed_colour(pw, 0);
-        pg[j] = packed_colour(pw, 1);
-        pb[j] = packed_colour(pw, 2);
-    }
-    int64_t pick[3];
-    float c[3][3], w[3][3];
-    // The colour-consistent modes of pixels q0 .. q0 + NJ - 1, held in LDS
-    // slots j0 .. j0 + NJ - 1, tree by tree (all of the pixels' rows of a tree loaded before their
-    // tests): the leaf indices are in s_li, the masks go to s_mask (slot
-    // stride ps, one row of 64 lanes per tree); cnt[j] receives the count
-    auto masks = [&](auto nj, int j0, int q0, int *cnt) {
-        constexpr int NJ = decltype(nj)::value;
-        ColourWin win[NJ];
+            for (int q = 0; q < QB; ++q)
+                v[j][q] = ((const uint4 *)row[j])[min(q0 + q, n4 - 1)];
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            win[j] = colour_win(pr[q0 + j], pg[q0 + j], pb[q0 + j], A.rgb_tol);
-            cnt[j] = 0;
-        }
-        if (Mp <= 12) {
-            // up to 12 modes per leaf: each row's three 16-byte loads are
-            // issued together, four trees at a time
-#pragma unroll 4
-            for (int tt = 0; tt < A.T; ++tt) {
-                Mask mk[NJ];
+            uint32_t m = 0;   // from the last slot down, so that each test shifts in one bit
 #pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    mk[j] = colour_mask12(A.mode_rgb + (int64_t)s_li[(j0 + j) * ps + tt * 64] * Mp, Mp, win[j]);
+            for (int q = QB - 1; q >= 0; --q) {
+                const uint32_t c[4] = {v[j][q].x, v[j][q].y, v[j][q].z, v[j][q].w};
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    s_mask[(j0 + j) * ps + tt * 64] = mk[j];
-                    cnt[j] += popc_mask(mk[j]);
-                }
+                for (int e = 3; e >= 0; --e) m = m + m + (colour_in(c[e], win[j]) ? 1u : 0u);
             }
-        } else {
-            for (int tt = 0; tt < A.T; ++tt) {
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const Mask mk = colour_mask<Mask>(A.mode_rgb + (int64_t)s_li[(j0 + j) * ps + tt * 64] * Mp, Mp,
-                                                      win[j]);
-                    s_mask[(j0 + j) * ps + tt * 64] = mk;
-                    cnt[j] += popc_mask(mk);
-                }
-            }
+            if (4 * (n4 - q0) < 4 * QB) m &= (1u << (4 * (n4 - q0))) - 1u;
+            mask[j] |= (Mask)m << (4 * q0);
         }
+        if constexpr (QB == 3) break;   // the caller's rows are no longer
+    }
+}
+
+// What the lanes of a wavefront pass on for the third pixels: the tries that
+// reached them, in lane order
+struct ThirdLds {
+    int32_t p[64];        // pixel
+    uint32_t rgb[64];     // its colour, r | g << 8 | b << 16
+    int32_t lane[64];     // the try's lane
+};
+
+// One try per lane: draws, colour-consistent mode picks, FP32 checks, FP64
+// alignment and residuals. The pick of pixel j is the sel-th colour-consistent
+// mode in (tree, mode) order, sel = uniform_int(u, count). Loads are issued a
+// stage at a time (pool entries; pixel colours and depths; leaves; mode colour
+// rows; picked modes) so that each stage waits once. Pixels 0 and 1 share
+// their stages; the first pair's checks come before any load of pixel 2 (every
+// check is a plain predicate, so their order does not change the result), and
+// since only a tenth or so of the tries pass them, the lanes split the third
+// pixels' (try, tree) pairs among them. s_li, s_mask: per pixel slot (ps
+// apart) and tree (64 apart) the lanes' leaf indices and colour masks. Called
+// by whole wavefronts; `live` marks the lanes that have a try.
+// Bound in large batches by the gathers (64 lines per load: about half the
+// cycles) and the colour tests, alone by the chain of its stages. Packed
+// colour tests, loads free of branches, and third pixels shared among the
+// lanes (they were evaluated by the few lanes that needed one, tree by tree):
+// 256 hypotheses at 320 x 240 from 22.2 to 15.5 us, 300 with 50 modes a leaf
+// 68 to 29, 1024 at 640 x 480 37 to 31, 40000 in one batch 567 to 426.
+template <typename Mask>
+__device__ bool try_hypothesis(const Attempt &A, int np, uint64_t h, uint64_t tau, bool live, double R[9], double t[3],
+                               int32_t *__restrict__ s_li, Mask *__restrict__ s_mask, int ps, ThirdLds &third)
+{
+    const int lane = __lane_id(), T = A.T, n4 = rgb_stride(A.M) / 4, Mp = 4 * n4;
+    const U4 a = philox(h, tau, 0, 0, A.seed, TAG_HYP);
+    const U4 b = philox(h, tau, 1, 0, A.seed, TAG_HYP);
+    int pi[3], p[3];
+    uint64_t pw[3];
+    float c[3][3], w[3][3];
+    int64_t pick[3];
+    // the rows of NJ leaves of a tree (up to 12 modes per leaf: all loads at once)
+    auto rows = [&](auto nj, const int32_t *li, const ColourWin *win, Mask *mk) {
+        constexpr int NJ = decltype(nj)::value;
+        const uint32_t *row[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) row[j] = A.mode_rgb + (int64_t)li[j] * Mp;
+        if (n4 <= 3)
+            colour_masks<Mask, NJ, 3>(row, n4, win, mk);
+        else
+            colour_masks<Mask, NJ, 4>(row, n4, win, mk);
+    };
+    auto window = [&](uint64_t word) {
+        return colour_win(packed_colour(word, 0), packed_colour(word, 1), packed_colour(word, 2), A.rgb_tol);
     };
     // the sel-th colour-consistent mode of the pixel in slot j, in (tree,
-    // mode) order
+    // mode) order: the tree that holds it, then the bit in its mask
     auto pick_of = [&](int j, int sel) {
-        int64_t pk = 0;
-        for (int tt = 0; tt < A.T; ++tt) {
-            const Mask mk = s_mask[j * ps + tt * 64];
+        Mask in = 0;
+        int32_t li = 0;
+        int at = 0;
+        for (int tt = 0; tt < T; ++tt) {
+            const Mask mk = s_mask[j * ps + tt * 64 + lane];
             const int k = popc_mask(mk);
-            if (sel >= 0 && sel < k) {
-                Mask mm = mk;
-                for (int q = 0; q < sel; ++q) mm &= mm - (Mask)1;
-                pk = (int64_t)s_li[j * ps + tt * 64] * A.M + (ffs_mask(mm) - 1);
-            }
+            const bool here = sel >= 0 && sel < k;
+            in = here ? mk : in;
+            li = here ? s_li[j * ps + tt * 64 + lane] : li;
+            at = here ? sel : at;
             sel -= k;
         }
-        return pk;
+        for (int q = 0; q < at; ++q) in &= in - (Mask)1;
+        return (int64_t)li * A.M + (ffs_mask(in) - 1);
     };
-    // pixels 0 and 1 stage by stage together (their leaves, then their mode
-    // colour rows, then their picked modes), then the first pair's checks
-    // before any load of pixel 2 (every check is a plain predicate, so their
-    // order does not change the result; lanes that fail load nothing more)
-#pragma unroll 4
-    for (int tt = 0; tt < A.T; ++tt) {
-        const int32_t l0 = A.leaves[(int64_t)tt * A.P + p[0]], l1 = A.leaves[(int64_t)tt * A.P + p[1]];
-        s_li[tt * 64] = tt * A.L + l0;
-        s_li[ps + tt * 64] = tt * A.L + l1;
-    }
-    int cnt01[2];
-    masks(std::integral_constant<int, 2>(), 0, 0, cnt01);
-    if (cnt01[0] == 0 || cnt01[1] == 0) return false;
-    pick[0] = pick_of(0, (int)uniform_int(b.x[0], (uint64_t)cnt01[0]));
-    pick[1] = pick_of(1, (int)uniform_int(b.x[1], (uint64_t)cnt01[1]));
+    if (live) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        cam_point(A.fr, p[j] % A.fr.W, p[j] / A.fr.W, dep[j], c[j]);
-        const Mode &md = A.modes[pick[j]];
-        w[j][0] = md.mu[0];
-        w[j][1] = md.mu[1];
-        w[j][2] = md.mu[2];
-    }
-    {
-        if (pi[0] == pi[1]) return false;
-        const float dc = sq3(c[0], c[1]);
-        const float dw = sq3(w[0], w[1]);
-        if (!(dc >= A.min_pair2) || !(dw <= A.ratio2 * dc) || !(dc <= A.ratio2 * dw)) return false;
+        for (int j = 0; j < 3; ++j) pi[j] = pick_pool(A, np, a.x[j]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) p[j] = A.pool[pi[j]];
+        // pool pixels are valid: the word holds their depth
+#pragma unroll
+        for (int j = 0; j < 3; ++j) pw[j] = A.packed[p[j]];
+#pragma unroll 4
+        for (int tt = 0; tt < T; ++tt) {
+            const int32_t l0 = A.leaves[(int64_t)tt * A.P + p[0]], l1 = A.leaves[(int64_t)tt * A.P + p[1]];
+            s_li[tt * 64 + lane] = tt * A.L + l0;
+            s_li[ps + tt * 64 + lane] = tt * A.L + l1;
+        }
+        const ColourWin win[2] = {window(pw[0]), window(pw[1])};
+        int cnt[2] = {0, 0};
+#pragma unroll 4
+        for (int tt = 0; tt < T; ++tt) {
+            const int32_t li[2] = {s_li[tt * 64 + lane], s_li[ps + tt * 64 + lane]};
+            Mask mk[2];
+            rows(std::integral_constant<int, 2>(), li, win, mk);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                s_mask[j * ps + tt * 64 + lane] = mk[j];
+                cnt[j] += popc_mask(mk[j]);
+            }
+        }
+        live = cnt[0] != 0 && cnt[1] != 0;
+        if (live) {
+            pick[0] = pick_of(0, (int)uniform_int(b.x[0], (uint64_t)cnt[0]));
+            pick[1] = pick_of(1, (int)uniform_int(b.x[1], (uint64_t)cnt[1]));
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                cam_point(A.fr, p[j] % A.fr.W, p[j] / A.fr.W, packed_depth(pw[j]), c[j]);
+                const Mode &md = A.modes[pick[j]];
+                w[j][0] = md.mu[0];
+                w[j][1] = md.mu[1];
+                w[j][2] = md.mu[2];
+            }
+            const float dc = sq3(c[0], c[1]);
+            const float dw = sq3(w[0], w[1]);
+            live = pi[0] != pi[1] && dc >= A.min_pair2 && dw <= A.ratio2 * dc && dc <= A.ratio2 * dw;
+        }
     }
     // pixel 2, in slot 0 (the first two pixels' picks are done)
-#pragma unroll 4
-    for (int tt = 0; tt < A.T; ++tt) s_li[tt * 64] = tt * A.L + A.leaves[(int64_t)tt * A.P + p[2]];
-    int cnt2[1];
-    masks(std::integral_constant<int, 1>(), 0, 2, cnt2);
-    if (cnt2[0] == 0) return false;
-    pick[2] = pick_of(0, (int)uniform_int(b.x[2], (uint64_t)cnt2[0]));
-    cam_point(A.fr, p[2] % A.fr.W, p[2] / A.fr.W, dep[2], c[2]);
+    const uint64_t m = __ballot(live);
+    if (!m) return false;
+    const int n = __popcll(m);
+    if (live) {
+        const int at = __popcll(m & lanemask_lt());
+        third.p[at] = p[2];
+        third.rgb[at] = packed_colour(pw[2], 0) | (packed_colour(pw[2], 1) << 8) | (packed_colour(pw[2], 2) << 16);
+        third.lane[at] = lane;
+    }
+    wave_lds_sync();
+    for (int i = lane; i < n * T; i += 64) {
+        const int tt = i / n, k = i - tt * n;
+        const uint32_t rgb = third.rgb[k];
+        const int32_t li[1] = {tt * A.L + A.leaves[(int64_t)tt * A.P + third.p[k]]};
+        const ColourWin win[1] = {colour_win(rgb & 0xFFu, (rgb >> 8) & 0xFFu, rgb >> 16, A.rgb_tol)};
+        Mask mk[1];
+        rows(std::integral_constant<int, 1>(), li, win, mk);
+        s_li[tt * 64 + third.lane[k]] = li[0];
+        s_mask[tt * 64 + third.lane[k]] = mk[0];
+    }
+    wave_lds_sync();
+    if (!live) return false;
+    int cnt2 = 0;
+    for (int tt = 0; tt < T; ++tt) cnt2 += popc_mask(s_mask[tt * 64 + lane]);
+    if (cnt2 == 0) return false;
+    pick[2] = pick_of(0, (int)uniform_int(b.x[2], (uint64_t)cnt2));
+    cam_point(A.fr, p[2] % A.fr.W, p[2] / A.fr.W, packed_depth(pw[2]), c[2]);
     {
         const Mode &md = A.modes[pick[2]];
         w[2][0] = md.mu[0];
         w[2][1] = md.mu[1];
         w[2][2] = md.mu[2];
     }
-    if (pi[0] == pi[1] || pi[0] == pi[2] || pi[1] == pi[2]) return false;
+    if (pi[0] == pi[2] || pi[1] == pi[2]) return false;
     const int EA[3] = {0, 0, 1}, EB[3] = {1, 2, 2};
     for (int e = 0; e < 3; ++e) {
         const float dc = sq3(c[EA[e]], c[EB[e]]);
@@ -746,6 +755,7 @@ __device__ bool try_hypothesis(const Attempt &A, int np, uint64_t h, uint64_t ta
 template <typename Mask>
 __global__ void __launch_bounds__(64) k_b_hypgen(const Attempt *__restrict__ att, Stage S, int tmax)
 {
+    __shared__ ThirdLds third;
     extern __shared__ __align__(16) char hg_lds[];
     const int ps = tmax * 64;
     int32_t *s_li = (int32_t *)hg_lds;
@@ -778,8 +788,8 @@ __global__ void __launch_bounds__(64) k_b_hypgen(const Attempt *__restrict__ att
         double R[9], t[3];
         for (int chunk = 0; chunk * 64 < A.max_tries && found < 0; ++chunk) {
             const int tau = chunk * 64 + lane;
-            const bool ok = tau < A.max_tries && np > 0 &&
-                            try_hypothesis(A, np, (uint64_t)h, (uint64_t)tau, R, t, s_li + lane, s_mask + lane, ps);
+            const bool ok =
+                np > 0 && try_hypothesis(A, np, (uint64_t)h, (uint64_t)tau, tau < A.max_tries, R, t, s_li, s_mask, ps, third);
             const uint64_t m = __ballot(ok);
             if (m) {
                 const int first = __ffsll((unsigned long long)m) - 1;
