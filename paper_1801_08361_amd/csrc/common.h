@@ -303,7 +303,14 @@ __device__ __forceinline__ int32_t traverse(const uint64_t *__restrict__ tree, i
 // lengths; each pixel's divisor and own colour are set up once
 // ---------------------------------------------------------------------------
 
-constexpr int TOP_NODES = 1023;   // levels 0..9, 32 KB prepared
+// Nodes prepared in LDS (32 bytes each) by a kernel that walks k pixels per
+// thread. Levels 0..8 where registers allow 6 and more wavefronts per SIMD (4
+// pixels), so that the 16 KB leave room for them: with levels 0..9 a
+// 640 x 480 frame's 1500 workgroups took two turns on the chip (49.5 to 43 us;
+// the adaptation's traversal 40.3 to 38.3). 8 pixels' registers allow 4
+// wavefronts whatever the LDS, and one level more in LDS saves 1 % (32 frames:
+// 1108 us, 1121 with levels 0..8).
+constexpr int top_nodes(int k) { return k > 4 ? 1023 : 511; }
 
 // One pixel of a frame packed for probing: four 16-bit fields, each holding
 // the complement of its value, so that every probe's response is the pixel's

@@ -171,12 +171,12 @@ __global__ void __launch_bounds__(256) k_leaves(const uint64_t *__restrict__ nod
                                                 int T, int L, Frame fr, const uint64_t *__restrict__ packed,
                                                 int32_t *__restrict__ leaves)
 {
-    __shared__ ProbeNode top[TOP_NODES];
+    __shared__ ProbeNode top[top_nodes(LEAF_PIX)];
     const int P = fr.W * fr.H;
     const int base = blockIdx.x * (LEAF_PIX * 256) + threadIdx.x;
     const int t = blockIdx.y;
     const uint64_t *tree = nodes + (int64_t)t * (L - 1);
-    const int ntop = L - 1 < TOP_NODES ? L - 1 : TOP_NODES;
+    const int ntop = L - 1 < top_nodes(LEAF_PIX) ? L - 1 : top_nodes(LEAF_PIX);
     stage_top(top, tree, ntop, fr, (int)threadIdx.x, (int)blockDim.x);
     __syncthreads();
     if (base >= P || t >= T) return;

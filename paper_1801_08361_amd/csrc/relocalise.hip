@@ -141,9 +141,10 @@ __device__ void pool_block_uniform(const Attempt &A, int b, const bool ok[4], ui
 // the attempt's frame (restaged only when the (attempt, tree) pair changes
 // between its units).
 template <int K>
-__global__ void __launch_bounds__(PIX_BLOCK) k_b_leaves(const Attempt *__restrict__ att, Stage S, int do_pool)
+__global__ void __launch_bounds__(PIX_BLOCK, K > 4 ? 4 : 6) k_b_leaves(const Attempt *__restrict__ att, Stage S, int do_pool)
 {
-    __shared__ ProbeNode top[TOP_NODES];
+    constexpr int TOP = top_nodes(K);
+    __shared__ ProbeNode top[TOP];
     __shared__ uint8_t p_wcnt[K == 4 ? 4 * (PIX_BLOCK / 64) : 1];
     int cached_a = -1, cached_t = -1;
     FOR_UNITS(S, u) {
@@ -154,7 +155,7 @@ __global__ void __launch_bounds__(PIX_BLOCK) k_b_leaves(const Attempt *__restric
         const int local = u - S.off[a];
         const int t = local / nb;
         const uint64_t *tree = A.nodes + (int64_t)t * (A.L - 1);
-        const int ntop = A.L - 1 < TOP_NODES ? A.L - 1 : TOP_NODES;
+        const int ntop = A.L - 1 < TOP ? A.L - 1 : TOP;
         const Frame fr = A.fr;
         if (a != cached_a || t != cached_t) {
             __syncthreads();
