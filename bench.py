@@ -68,6 +68,8 @@ FLOP_PER_PAIR = 18                # y = R c + t: 9 fma
 REFINE_BYTES_PER_SURVIVOR = 2 * 22 * 8 + 8 + 12 * 8 + 12 * 4 + 12 * 4
 FUSED_LIVE = 64                   # planned live hypotheses from which a round culls inside its refinement
 FUSED_REFINE = 1024               # planned survivors of a batch up to which a round refines in one kernel
+NEXT_DRAWS = 16                   # draws per workgroup of a cull and refinement that scores the next round
+NEXT_UNITS = 1024                 # workgroups up to which it does
 
 
 def log(msg: str) -> None:
@@ -243,8 +245,6 @@ def rooflines(kernels, res, attempts, batch_pixels=500, batched=False):
                 "frac": achieved / peak, "traffic": None, "avg_launch_us": avg_s * 1e6,
                 "work_per_launch": work / n, "launches": n}
 
-    flops = sum(r["mode_evals"] * FLOP_PER_MODE_TERM + r["pair_evals"] * FLOP_PER_PAIR for r in res)
-    out["k_b_score"] = entry("k_b_score", "alu", flops, FP32_PEAK_TFLOPS, "TFLOP/s")
     leaf_bytes = sum(P * (5 + 4 * T) for P, T, _, _ in attempts)
     out["k_b_leaves"] = entry("k_b_leaves", "hbm", leaf_bytes, HBM_PEAK_GBS, "GB/s")
     # Which kernels refine round r, as the library plans a batch: from the
@@ -273,15 +273,30 @@ def rooflines(kernels, res, attempts, batch_pixels=500, batched=False):
             total = sum(bound(n, k + 1) for n in ns if k < rounds_for(n))
             kinds.append("fused" if k >= fused_from and total <= FUSED_REFINE
                          else ("one" if total <= FUSED_REFINE else "split"))
-        return kinds
+        # from the first fused round after round 0 with few enough
+        # workgroups on, a round's refinement scores the next round: how many
+        # rounds k_b_score scores
+        parts = (batch_pixels + NEXT_DRAWS - 1) // NEXT_DRAWS
+        scored = len(kinds)
+        for k in range(max(fused_from, 1), len(kinds) - 1):
+            if kinds[k] == "fused" and parts * sum(bound(n, k) for n in ns if k < rounds_for(n)) <= NEXT_UNITS:
+                scored = k + 1
+                break
+        return kinds, scored
 
     groups = (batch_pixels + 7) // 8
-    kinds_b = plan([a[3] for a in attempts]) if batched else None
+    plan_b = plan([a[3] for a in attempts]) if batched else None
     surv = {"one": 0, "split": 0, "fused": 0}
     cull_fused = 0
+    flops = 0.0
     for r, (_, _, _, n_hyp) in zip(res, attempts):
-        kinds = kinds_b if batched else plan([n_hyp])
+        kinds, scored = plan_b if batched else plan([n_hyp])
         na = r["n_valid"]
+        # k_b_score's part of the attempt's work: its rounds' live
+        # hypotheses (a round's draws have the same number of modes, nearly)
+        lives = [(na + (1 << k) - 1) >> k for k in range(r["n_rounds"])]
+        flops += ((r["mode_evals"] * FLOP_PER_MODE_TERM + r["pair_evals"] * FLOP_PER_PAIR)
+                  * sum(lives[:scored]) / max(sum(lives), 1))
         for k in range(r["n_rounds"]):
             keep = (na + 1) // 2
             surv[kinds[k]] += keep
@@ -290,6 +305,7 @@ def rooflines(kernels, res, attempts, batch_pixels=500, batched=False):
                 # positions and the round's trace written
                 cull_fused += na * (8 + 4 * groups + 8) + keep * 12
             na = keep
+    out["k_b_score"] = entry("k_b_score", "alu", flops, FP32_PEAK_TFLOPS, "TFLOP/s")
     per_survivor = 4 * batch_pixels + REFINE_BYTES_PER_SURVIVOR
     out["k_b_refine"] = entry("k_b_refine", "hbm", surv["one"] * per_survivor, HBM_PEAK_GBS, "GB/s")
     out["k_b_cull_refine"] = entry("k_b_cull_refine", "hbm", cull_fused + surv["fused"] * per_survivor,

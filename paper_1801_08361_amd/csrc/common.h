@@ -1067,6 +1067,8 @@ struct Attempt {
     int32_t RL_GLOBAL *hyp_try;             // [N]
     float RL_GLOBAL *energy;                // [2][N] accumulated energy of the hypothesis at each live position
     double RL_GLOBAL *sums;                 // [N][NSUM] running inlier sums
+    double RL_GLOBAL *lsums;                // [2][min(N, 64)][NSUM] the same per live position, where a round's refinement
+                                            // scores the next round (buffer r & 1 as round r reads it)
     int32_t RL_GLOBAL *alive;               // [2][N] the live list scored in round r is buffer r & 1; the cull of round r
                                             // writes buffer (r + 1) & 1, so that it never overwrites what it reads
     int32_t RL_GLOBAL *pos;                 // [N] survivor i's position in the list it was scored in
@@ -1075,7 +1077,7 @@ struct Attempt {
     int2 RL_GLOBAL *dtree;                  // [rounds][B][T] per draw and tree: first global mode index (leaf * M), mode count
     float RL_GLOBAL *gs;                    // [ceil(B / GROUP)][N] energy sum of each group of GROUP draws, per live position
     int32_t RL_GLOBAL *inl;                 // [ceil(B/8)][N][8] global index (leaf * M + mode) of an inlier's best mode, -1 otherwise
-    unsigned long long RL_GLOBAL *stats;    // [0] mode evaluations [1] pair evaluations [2] round mode count
+    unsigned long long RL_GLOBAL *stats;    // [0] mode evaluations [1] pair evaluations [2 + (r & 1)] mode count of round r
     int32_t RL_GLOBAL *tr_alive;            // [MAX_ROUNDS][N]
     float RL_GLOBAL *tr_energy;             // [MAX_ROUNDS][N]
     int32_t RL_GLOBAL *tr_n_alive;          // [MAX_ROUNDS]

@@ -119,6 +119,7 @@ __device__ void pool_block_uniform(const Attempt &A, int b, const bool ok[4], ui
         A.stats[0] = 0ull;
         A.stats[1] = 0ull;
         A.stats[2] = 0ull;
+        A.stats[3] = 0ull;
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -428,6 +429,7 @@ __global__ void __launch_bounds__(POOL_BLOCK / PB_PIX) k_b_pool_write(const Atte
             A.stats[0] = 0ull;
             A.stats[1] = 0ull;
             A.stats[2] = 0ull;
+            A.stats[3] = 0ull;
         }
         uint32_t dep[PB_PIX];
 #pragma unroll
@@ -907,10 +909,12 @@ __device__ __forceinline__ float group_total(const float RL_GLOBAL *gs, int ap, 
     float S = 0.0f;
     for (int k0 = 0; k0 < ng; k0 += CH) {
         float v[CH];
-        const float RL_GLOBAL *row = gs + (int64_t)k0 * stride + ap;
         const int last = ng - 1 - k0;
 #pragma unroll
-        for (int k = 0; k < CH; ++k) v[k] = row[(int64_t)min(k, last) * stride];
+        for (int k = 0; k < CH; ++k) {
+            const float RL_GLOBAL *row = gs + (int64_t)(k0 + min(k, last)) * stride;   // wavefront-uniform
+            v[k] = row[(uint32_t)ap];
+        }
 #pragma unroll
         for (int k = 0; k < CH; ++k) S = S + (k <= last ? v[k] : 0.0f);
     }
@@ -985,9 +989,9 @@ __device__ void cull_round(const Attempt &A, int r, unsigned long long *__restri
     __syncthreads();
     if (threadIdx.x == 0) {
         if (r < MAX_ROUNDS) A.tr_n_alive[r] = na;
-        A.stats[0] += (unsigned long long)na * A.stats[2];
+        A.stats[0] += (unsigned long long)na * A.stats[2 + (r & 1)];
         A.stats[1] += (unsigned long long)na * (unsigned long long)A.B;
-        A.stats[2] = 0ull;
+        A.stats[2 + (r & 1)] = 0ull;
         A.rl[r + 1] = keep;
     }
     __syncthreads();
@@ -1060,9 +1064,9 @@ __global__ void __launch_bounds__(CULL_THREADS) k_b_cull_rank(const Attempt *__r
         }
         if (blk == 0 && threadIdx.x == 0) {
             if (r < MAX_ROUNDS) A.tr_n_alive[r] = na;
-            A.stats[0] += (unsigned long long)na * A.stats[2];
+            A.stats[0] += (unsigned long long)na * A.stats[2 + (r & 1)];
             A.stats[1] += (unsigned long long)na * (unsigned long long)A.B;
-            A.stats[2] = 0ull;
+            A.stats[2 + (r & 1)] = 0ull;
             A.rl[r + 1] = keep;
         }
     }
@@ -1272,7 +1276,7 @@ __global__ void __launch_bounds__(64 * GROUP) k_b_score(const Attempt *__restric
                 if (threadIdx.x == 0) {
                     uint32_t c = 0;
                     for (int w = 0; w < nw; ++w) c += s_cnt[w];
-                    if (c) atomicAdd(&A.stats[2], (unsigned long long)c);
+                    if (c) atomicAdd(&A.stats[2 + (r & 1)], (unsigned long long)c);
                 }
             }
         }
@@ -1376,17 +1380,17 @@ __device__ __forceinline__ void refine_batch_load(const Attempt &A, int r, int a
     }
 }
 
-// this round's inlier sums of hypothesis h (scored at live position ap), its
-// first batch already loaded, added to its running sums and stored; s
-// receives the totals (wavefront-uniform values)
-__device__ __forceinline__ void refine_sums_pre(const Attempt &A, int r, int h, int ap, const RefBatch &q0,
-                                                double s[NSUM])
+// this round's inlier sums of the hypothesis scored at live position ap, its
+// first batch already loaded, added to its running sums `run`; s receives the
+// totals (wavefront-uniform values). Returns the lane's own total.
+__device__ __forceinline__ double refine_sums_pre(const Attempt &A, int r, int ap, const RefBatch &q0,
+                                                  const double RL_GLOBAL *run, double s[NSUM])
 {
     const int lane = __lane_id();
     const int mine = rs_sum_of(lane);
     // the running sum of the lane's own total, fetched while this round's are
     // formed
-    const double runk = mine >= 0 ? A.sums[(int64_t)h * NSUM + mine] : 0.0;
+    const double runk = mine >= 0 ? run[mine] : 0.0;
 #pragma unroll
     for (int k = 0; k < NSUM; ++k) s[k] = 0.0;
     // lane-strided draws, RB per lane at a time: all inlier ids first, then the
@@ -1425,16 +1429,24 @@ __device__ __forceinline__ void refine_sums_pre(const Attempt &A, int r, int h, 
     double u = rs_pair<2>(z2[0], z2[1]);
     u = u + xor_lane_f64<1>(u);
     const double tot = runk + u;
-    if (mine >= 0 && (lane & 1) == 0) A.sums[(int64_t)h * NSUM + mine] = tot;
 #pragma unroll
     for (int k = 0; k < NSUM; ++k) s[k] = lane_f64(tot, rs_lane_of(k));
+    return tot;
+}
+
+// stores the lanes' own totals as a hypothesis's running sums
+__device__ __forceinline__ void refine_store_sums(double RL_GLOBAL *run, double tot)
+{
+    const int lane = __lane_id(), mine = rs_sum_of(lane);
+    if (mine >= 0 && (lane & 1) == 0) run[mine] = tot;
 }
 
 __device__ __forceinline__ void refine_sums_at(const Attempt &A, int r, int h, int ap, double s[NSUM])
 {
     RefBatch q0;
     refine_batch_load(A, r, ap, 0, q0);
-    refine_sums_pre(A, r, h, ap, q0, s);
+    double RL_GLOBAL *run = A.sums + (int64_t)h * NSUM;
+    refine_store_sums(run, refine_sums_pre(A, r, ap, q0, run, s));
 }
 
 // the same for survivor position sidx of round r; returns the hypothesis index
@@ -1445,28 +1457,36 @@ __device__ __forceinline__ int refine_sums_of(const Attempt &A, int r, int sidx,
     return h;
 }
 
+// stores hypothesis h's re-solved pose; p is its FP32 rounding (R row-major, t)
+__device__ __forceinline__ void store_pose(const Attempt &A, int h, const double R[9], const double t[3], const float p[12])
+{
+    Hyp &hy = A.hyp[h];
+    for (int k = 0; k < 9; ++k) {
+        hy.R[k] = R[k];
+        hy.R32[k] = p[k];
+    }
+    for (int k = 0; k < 3; ++k) {
+        hy.t[k] = t[k];
+        hy.t32[k] = p[9 + k];
+    }
+}
+
 // re-solves hypothesis h, survivor sidx, from its running sums s when
 // refinement is on, and stores its FP32 pose at its live position
 __device__ __forceinline__ void refine_solve_of(const Attempt &A, int sidx, int h, const double s[NSUM])
 {
     double R[9], t[3];
-    float *lp = A.lpose + sidx * 12;
-    Hyp &hy = A.hyp[h];
+    float p[12];
     if (A.refine && pose_from_sums(s, R, t)) {
-        for (int k = 0; k < 9; ++k) {
-            hy.R[k] = R[k];
-            hy.R32[k] = (float)R[k];
-            lp[k] = (float)R[k];
-        }
-        for (int k = 0; k < 3; ++k) {
-            hy.t[k] = t[k];
-            hy.t32[k] = (float)t[k];
-            lp[9 + k] = (float)t[k];
-        }
+        for (int k = 0; k < 9; ++k) p[k] = (float)R[k];
+        for (int k = 0; k < 3; ++k) p[9 + k] = (float)t[k];
+        store_pose(A, h, R, t, p);
     } else {
-        for (int k = 0; k < 9; ++k) lp[k] = hy.R32[k];
-        for (int k = 0; k < 3; ++k) lp[9 + k] = hy.t32[k];
+        for (int k = 0; k < 9; ++k) p[k] = A.hyp[h].R32[k];
+        for (int k = 0; k < 3; ++k) p[9 + k] = A.hyp[h].t32[k];
     }
+    float *lp = A.lpose + sidx * 12;
+    for (int k = 0; k < 12; ++k) lp[k] = p[k];
 }
 
 // sums and solve in one kernel: one wavefront per survivor
@@ -1565,77 +1585,257 @@ __global__ void __launch_bounds__(64) k_b_finish(const Attempt *__restrict__ att
 }
 
 // Cull and refinement of a small round (at most FUSED_LIVE live hypotheses
-// per attempt) in one kernel: one wavefront per live position w. Each
+// per attempt) in one kernel: a workgroup per live position w. Its first
 // wavefront forms every live hypothesis's energy exactly as the cull does
 // (group sums in group order, added to the accumulated energy, one position
 // per lane) and counts the keys (energy, index) below position w's: that
 // rank is w's place in the sorted order, so the positions of rank below
-// ceil(n / 2) survive, each into the slot of its rank, and are refined by
-// their own wavefront (whose inlier ids and draws, indexed by w, were
-// loaded together with the group sums). The wavefront of slot 0 writes the
-// round's trace, statistics and survivor count. The lists are
-// double-buffered by round parity, so no wavefront overwrites what another
-// reads. With `fin` (the plan's last round, a lone attempt) lane 0 of slot 0
-// then writes the attempt's result too, after its own refinement (all that
-// the result reads was written by that lane or by earlier launches), in
-// place of a separate finishing launch.
+// ceil(n / 2) survive, each into the slot of its rank. Its second wavefront
+// refines w's hypothesis meanwhile, before it is known whether it survives:
+// each of the two is a chain of loads and sums (one wavefront for both took
+// 13.7 us a round in 32 full-size attempts, 11.2 apart; 13.3 and 9.4 in 64
+// mixed ones), and what the refinement stores waits for the rank. The
+// wavefronts of slot 0 write the round's trace, statistics and survivor
+// count. The lists are double-buffered by round parity, so no workgroup
+// overwrites what another reads. With `fin` (the plan's last round, a lone
+// attempt) the refining lane of slot 0 then writes the attempt's result too
+// (all that the result reads was written by its workgroup or by earlier
+// launches), in place of a separate finishing launch.
+//
+// NEXT: the kernel also scores round r + 1, in place of a launch whose few
+// microseconds are load latency. A workgroup is (live position, part of
+// NEXT_DRAWS draws): two wavefronts cull and refine as above, once per part
+// with the same results (part 0 stores them), while each of the others loads
+// the modes of a group of 8 draws of round r + 1, 8 lanes per draw, into
+// registers. The refined pose then reaches them through LDS, and they score
+// it: lane j of a draw takes modes j, j + 8, ... of its (tree, mode) order,
+// and the 8 lanes' first minima are combined, ties to the lower mode, as the
+// scoring kernel does with a hypothesis split over lanes. Per round, with 16
+// live and 500 draws 11.8 + 6.7 us and the gap between two launches, now 10.3;
+// with 32 live and 64 draws 9.9 + 6.8, now 6.8.
+// Workgroups of a launch run in any order, so what it reads and what it
+// writes lie apart: running sums are kept per live position by round parity
+// (round `from`, the first such round, reads them per hypothesis), and the
+// scores go to columns that the round's own do not use.
+//
+// NEXT_GROUPS: the refinement's registers leave 8 wavefronts to a CU, that is
+// two workgroups of 4; with 4 groups (6 wavefronts, one workgroup) a round of 16
+// live took 12.2 us, with 6 groups 12.9, with 2 10.3. NEXT_UNITS: two turns
+// of the chip, where 32 live of 500 draws take 15.3 us against 9.4 + 6.7
+// and the gap apart; at 64 live four turns would cost more than two launches.
 constexpr int FUSED_LIVE = 64;    // live hypotheses per attempt up to which a round culls in its refinement
+constexpr int NEXT_GROUPS = 2;    // draw groups per workgroup that scores the next round
+constexpr int NEXT_DRAWS = NEXT_GROUPS * GROUP;
+constexpr int NEXT_PRE = 8;       // modes per lane loaded ahead of the pose
+constexpr int NEXT_UNITS = 1024;  // workgroups of a round up to which it scores the next one
+constexpr int NO_ROUND = 1 << 20;
 
-__global__ void __launch_bounds__(64) k_b_cull_refine(const Attempt *__restrict__ att, Stage S, int r, int fin)
+// live hypotheses at the start of round r, at most: N halved r times
+__host__ __device__ __forceinline__ int live_bound(int N, int r) { return (int)(((int64_t)N + (1ll << r) - 1) >> r); }
+__host__ __device__ __forceinline__ int next_parts(int B) { return (B + NEXT_DRAWS - 1) / NEXT_DRAWS; }
+
+// first column of round r's scores (group sums and inlier ids): 0, or past
+// the previous round's columns where that round's refinement scored it
+// (alternately 0 and live_bound(from); with from >= 1 both rounds' columns
+// fit N)
+__device__ __forceinline__ int score_col(const Attempt &A, int r, int from)
 {
+    return r > from && ((r - from) & 1) ? live_bound(A.N, from) : 0;
+}
+
+struct NextLds {
+    int2 tree[NEXT_GROUPS][GROUP][16];   // per draw and tree: modes up to its last; first global index less those before
+    float pose[12];
+    int32_t slot;                        // the survivor's, or -1
+};
+
+template <bool NEXT>
+__global__ void __launch_bounds__(64 * (NEXT ? 2 + NEXT_GROUPS : 2))
+    k_b_cull_refine(const Attempt *__restrict__ att, Stage S, int r, int fin, int from)
+{
+    static_assert(GROUP == 8, "8 lanes per draw of a group of 8");
+    __shared__ NextLds nx;
     FOR_UNITS(S, u) {
         const int a = attempt_of(S, u);
         const Attempt &A = att[a];
-        const int w = u - S.off[a];    // below the planned live bound, so within the lists
-        const int lane = __lane_id();
+        const int parts = NEXT ? next_parts(A.B) : 1;
+        const int w = (u - S.off[a]) / parts, part = (u - S.off[a]) - w * parts;   // w: below the planned live bound
+        const int lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
         const int na = A.rl[r];        // <= FUSED_LIVE: one live position per lane
-        // positions clamped into the lists, so that these loads issue with
-        // the live count, and position w's first batch of inlier ids and
-        // draws with them
-        const int apl = min(lane, A.N - 1);
-        const int hl = live_list(A, r)[apl];
-        const float El = live_energy(A, r)[apl];
-        RefBatch q0;
-        refine_batch_load(A, r, w, 0, q0);
-        const int ng = (A.B + GROUP - 1) / GROUP;
-        // the group sums in group order, 64 loads at a time
-        const float Ssum = group_total<64>(A.gs, apl, ng, A.N);
-        if (!round_active(A, r)) {
-            if (fin && w == 0 && lane == 0) finish_attempt(A);
-            continue;
-        }
-        if (w >= na) continue;
         const int keep = (na + 1) / 2;
-        const bool live = lane < na;
-        const float E = El + Ssum;
-        const unsigned long long key = live ? cull_key(E, hl, lane) : ~0ull;
-        // rank of position w: how many live keys are smaller (keys are distinct)
-        const unsigned long long kw = lane_u64(key, w);
-        const int sidx = __popcll(__ballot(live && key < kw));
-        if (sidx >= keep) continue;
-        const int h = (int)((kw >> 12) & 0xFFFFFull);
-        if (lane == 0) {
-            live_list(A, r + 1)[sidx] = h;
-            live_energy(A, r + 1)[sidx] = key_float((uint32_t)(kw >> 32));
-            A.pos[sidx] = w;
-        }
-        if (sidx == 0) {
-            if (r < MAX_ROUNDS && live) {
-                A.tr_alive[r * A.N + lane] = hl;
-                A.tr_energy[r * A.N + lane] = E;
+        const int col = score_col(A, r, from);
+        // (uniform over the workgroup; each role's first loads are issued
+        // before it waits for the live count)
+        auto idle = [&] { return !round_active(A, r) || w >= na || (part > 0 && keep <= 1); };
+        __syncthreads();   // the previous unit's reads of nx are done
+        if (wave == 0) {
+            // positions clamped into the lists, so that these loads issue with
+            // the live count
+            const int apl = min(lane, A.N - 1);
+            const int hl = live_list(A, r)[apl];
+            const float El = live_energy(A, r)[apl];
+            // the group sums in group order, 64 loads at a time
+            const float Ssum = group_total<64>(A.gs, min(col + lane, A.N - 1), (A.B + GROUP - 1) / GROUP, A.N);
+            if (!NEXT && fin && w == 0 && lane == 0 && !round_active(A, r)) finish_attempt(A);
+            if (idle()) continue;
+            const bool live = lane < na;
+            const float E = El + Ssum;
+            const unsigned long long key = live ? cull_key(E, hl, lane) : ~0ull;
+            // rank of position w: how many live keys are smaller (keys are distinct)
+            const unsigned long long kw = lane_u64(key, w);
+            const int sidx = __popcll(__ballot(live && key < kw));
+            if (sidx < keep && part == 0) {
+                if (lane == 0) {
+                    live_list(A, r + 1)[sidx] = (int)((kw >> 12) & 0xFFFFFull);
+                    live_energy(A, r + 1)[sidx] = key_float((uint32_t)(kw >> 32));
+                    A.pos[sidx] = w;
+                }
+                if (sidx == 0) {
+                    if (r < MAX_ROUNDS && live) {
+                        A.tr_alive[r * A.N + lane] = hl;
+                        A.tr_energy[r * A.N + lane] = E;
+                    }
+                    if (lane == 0) {
+                        if (r < MAX_ROUNDS) A.tr_n_alive[r] = na;
+                        A.stats[0] += (unsigned long long)na * A.stats[2 + (r & 1)];
+                        A.stats[1] += (unsigned long long)na * (unsigned long long)A.B;
+                        A.stats[2 + (r & 1)] = 0ull;
+                        A.rl[r + 1] = keep;
+                    }
+                }
+            }
+            if (lane == 0) nx.slot = sidx < keep ? sidx : -1;
+            __syncthreads();   // the wavefronts' roles meet here, once each
+        } else if (wave == 1) {
+            const int h = max(live_list(A, r)[w], 0);   // (read past the live count, but not used)
+            RefBatch q0;
+            refine_batch_load(A, r, col + w, 0, q0);
+            if (idle()) continue;
+            const int LB = min(A.N, FUSED_LIVE);
+            double sm[NSUM], R[9], t[3];
+            const double tot = refine_sums_pre(
+                A, r, col + w, q0, r > from ? A.lsums + (int64_t)((r & 1) * LB + w) * NSUM : A.sums + (int64_t)h * NSUM, sm);
+            const bool solved = A.refine && pose_from_sums(sm, R, t);   // the same in every lane
+            float p[12];
+            if (solved) {
+                for (int k = 0; k < 9; ++k) p[k] = (float)R[k];
+                for (int k = 0; k < 3; ++k) p[9 + k] = (float)t[k];
+            } else {
+                for (int k = 0; k < 9; ++k) p[k] = A.hyp[h].R32[k];
+                for (int k = 0; k < 3; ++k) p[9 + k] = A.hyp[h].t32[k];
+            }
+            if (NEXT && lane == 0) {
+#pragma unroll
+                for (int k = 0; k < 12; ++k) nx.pose[k] = p[k];
+            }
+            __syncthreads();
+            const int sidx = nx.slot;
+            if (sidx < 0 || part > 0) continue;
+            const bool again = NEXT && keep > 1;    // a round that this kernel scores follows
+            refine_store_sums(again ? A.lsums + (int64_t)(((r + 1) & 1) * LB + sidx) * NSUM : A.sums + (int64_t)h * NSUM, tot);
+            if (lane == 0) {
+                if (solved) store_pose(A, h, R, t, p);
+                if (!again)
+                    for (int k = 0; k < 12; ++k) A.lpose[sidx * 12 + k] = p[k];
+                if (fin && sidx == 0) finish_attempt(A);
+            }
+        } else if constexpr (NEXT) {
+            // the wavefront's draws: one per 8 lanes
+            const int i0 = part * NEXT_DRAWS + (wave - 2) * GROUP, d = lane >> 3, sub = lane & 7;
+            float4 dr = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            int2 (*const trees)[16] = nx.tree[wave - 2];
+            int32_t gi[NEXT_PRE];
+            Mode md[NEXT_PRE];
+            const int64_t q = (int64_t)(r + 1) * A.B + i0 + d;
+            const bool has = r + 1 < A.rounds && i0 + d < A.B;
+            int2 e0 = make_int2(0, 0), e1 = make_int2(0, 0);
+            if (has) {
+                dr = A.draws[q];
+                if (sub < A.T) e0 = A.dtree[q * A.T + sub];
+                if (sub + 8 < A.T) e1 = A.dtree[q * A.T + sub + 8];
+            }
+            // modes up to each tree's last, over the draw's 8 lanes
+            auto scan8 = [&](int x) {
+                int y = row_up<1>(x);
+                x += sub >= 1 ? y : 0;
+                y = row_up<2>(x);
+                x += sub >= 2 ? y : 0;
+                y = row_up<4>(x);
+                return x + (sub >= 4 ? y : 0);
+            };
+            if (idle()) continue;
+            const int n0 = scan8(e0.y), n07 = __shfl(n0, lane | 7, 64), n1 = n07 + scan8(e1.y);
+            trees[d][sub] = make_int2(n0, e0.x - (n0 - e0.y));
+            trees[d][sub + 8] = make_int2(n1, e1.x - (n1 - e1.y));
+            const int cnt = __shfl(n1, lane | 7, 64);
+            wave_lds_sync();
+            int tree = 0;
+            int2 te = trees[d][0];
+            // global index of mode j < cnt of the lane's draw, j rising from call to call
+            auto index_of = [&](int j) {
+                while (j >= te.x) te = trees[d][++tree];
+                return j + te.y;
+            };
+#pragma unroll
+            for (int e = 0; e < NEXT_PRE; ++e) gi[e] = sub + 8 * e < cnt ? index_of(sub + 8 * e) : -1;
+#pragma unroll
+            for (int e = 0; e < NEXT_PRE; ++e) md[e] = A.modes[max(gi[e], 0)];
+            __syncthreads();
+            const int slot = nx.slot;
+            if (slot < 0 || keep <= 1 || i0 >= A.B) continue;
+            const float *R = nx.pose, *t = nx.pose + 9;
+            const float y0 = fmaf(R[0], dr.x, fmaf(R[1], dr.y, fmaf(R[2], dr.z, t[0])));
+            const float y1 = fmaf(R[3], dr.x, fmaf(R[4], dr.y, fmaf(R[5], dr.z, t[1])));
+            const float y2 = fmaf(R[6], dr.x, fmaf(R[7], dr.y, fmaf(R[8], dr.z, t[2])));
+            float best = INFINITY;
+            int32_t bk = -1;   // the best mode's global index, times 2, plus 1 for an inlier
+            auto take = [&](const Mode &m, int g) {
+                const float d0 = y0 - m.mu[0], d1 = y1 - m.mu[1], d2 = y2 - m.mu[2];
+                const float a0 = fmaf(m.sinv[2], d2, fmaf(m.sinv[1], d1, m.sinv[0] * d0));
+                const float a1 = fmaf(m.sinv[4], d2, fmaf(m.sinv[3], d1, m.sinv[1] * d0));
+                const float a2 = fmaf(m.sinv[5], d2, fmaf(m.sinv[4], d1, m.sinv[2] * d0));
+                const float term = fmaf(0.5f, fmaf(d2, a2, fmaf(d1, a1, d0 * a0)), m.kappa);
+                if (g >= 0 && term < best) {
+                    best = term;
+                    bk = 2 * g + ((d0 * d0 + d1 * d1) + d2 * d2 <= A.inl2 ? 1 : 0);
+                }
+            };
+#pragma unroll
+            for (int e = 0; e < NEXT_PRE; ++e) take(md[e], gi[e]);
+            for (int j = sub + 8 * NEXT_PRE; j < cnt; j += 8 * 4) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) gi[e] = j + 8 * e < cnt ? index_of(j + 8 * e) : -1;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) md[e] = A.modes[max(gi[e], 0)];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) take(md[e], gi[e]);
+            }
+            // the 8 lanes combine their minima (best is +inf exactly when bk < 0)
+            auto merge = [&](float ob, int32_t ok) {
+                if (ob < best || (ob == best && ok < bk)) {
+                    best = ob;
+                    bk = ok;
+                }
+            };
+            merge(__uint_as_float(xor_lane<1>(__float_as_uint(best))), (int32_t)xor_lane<1>((uint32_t)bk));
+            merge(__uint_as_float(xor_lane<2>(__float_as_uint(best))), (int32_t)xor_lane<2>((uint32_t)bk));
+            merge(__uint_as_float(xor_lane<4>(__float_as_uint(best))), (int32_t)xor_lane<4>((uint32_t)bk));
+            const int ap = score_col(A, r + 1, from) + slot;
+            if (sub == 0 && i0 + d < A.B) A.inl[inl_at(A, i0 + d, ap)] = bk & 1 && bk > 0 ? bk >> 1 : -1;
+            // the group's energy in draw order, and its modes
+            const int ev = __float_as_int(best < 0.0f ? best : 0.0f);
+            float g = 0.0f;
+            uint32_t modes = 0;
+#pragma unroll
+            for (int k = 0; k < GROUP; ++k) {
+                if (i0 + k < A.B) g = g + __int_as_float(__builtin_amdgcn_readlane(ev, 8 * k));
+                modes += (uint32_t)__builtin_amdgcn_readlane(cnt, 8 * k);
             }
             if (lane == 0) {
-                if (r < MAX_ROUNDS) A.tr_n_alive[r] = na;
-                A.stats[0] += (unsigned long long)na * A.stats[2];
-                A.stats[1] += (unsigned long long)na * (unsigned long long)A.B;
-                A.stats[2] = 0ull;
-                A.rl[r + 1] = keep;
+                A.gs[(int64_t)(i0 / GROUP) * A.N + ap] = g;
+                if (slot == 0 && modes) atomicAdd(&A.stats[2 + ((r + 1) & 1)], (unsigned long long)modes);
             }
         }
-        double sm[NSUM];
-        refine_sums_pre(A, r, h, w, q0, sm);
-        if (lane == 0) refine_solve_of(A, sidx, h, sm);
-        if (fin && sidx == 0 && lane == 0) finish_attempt(A);
     }
 }
 
@@ -1683,6 +1883,7 @@ struct Plan {
     std::vector<Shape> shape;
     int n = 0, rounds = 0, tm_max = 1, m_max = 1;
     int fused_from = 0;             // rounds from here on cull inside their refinement (k_b_cull_refine)
+    int score_from = NO_ROUND;      // and from here on also score the next round in it
     char *arena = nullptr;
     size_t arena_bytes = 0;
     Attempt *d_att = nullptr;
@@ -1739,6 +1940,7 @@ static size_t carve(const Shape &s, char *base, Attempt &A)
     A.hyp_try = (decltype(A.hyp_try))take((size_t)s.N * 4);
     A.energy = (decltype(A.energy))take((size_t)2 * s.N * 4);
     A.sums = (decltype(A.sums))take((size_t)s.N * NSUM * 8);
+    A.lsums = (decltype(A.lsums))take((size_t)2 * std::min(s.N, FUSED_LIVE) * NSUM * 8);
     A.alive = (decltype(A.alive))take((size_t)2 * s.N * 4);
     A.pos = (decltype(A.pos))take((size_t)s.N * 4);
     A.lpose = (decltype(A.lpose))take((size_t)s.N * 12 * 4);
@@ -1747,7 +1949,7 @@ static size_t carve(const Shape &s, char *base, Attempt &A)
     A.dtree = (decltype(A.dtree))take((size_t)rounds * s.B * s.T * 8);
     A.gs = (decltype(A.gs))take((size_t)((s.B + GROUP - 1) / GROUP) * s.N * 4);
     A.inl = (decltype(A.inl))take((size_t)((s.B + INL_TILE - 1) / INL_TILE) * INL_TILE * s.N * 4);
-    A.stats = (decltype(A.stats))take(3 * 8);
+    A.stats = (decltype(A.stats))take(4 * 8);
     A.tr_alive = (decltype(A.tr_alive))take((size_t)MAX_ROUNDS * s.N * 4);
     A.tr_energy = (decltype(A.tr_energy))take((size_t)MAX_ROUNDS * s.N * 4);
     A.tr_n_alive = (decltype(A.tr_n_alive))take((size_t)MAX_ROUNDS * 4);
@@ -1779,6 +1981,9 @@ struct Stages {
     Stage pix, pb, att, hyp, wts;
     std::vector<Stage> score, refine, solve, cull, live;
 };
+
+// whether round r's cull and refinement also scores round r + 1
+static bool scores_next(const Plan *pl, int r) { return r >= pl->score_from && r + 1 < pl->rounds; }
 
 // host offsets of every stage for schedule `sc`: pix, pb, att, hyp, wts, then
 // per round (score, refine, solve, cull by ranks, live positions)
@@ -1815,7 +2020,10 @@ static std::vector<int32_t> offsets(const Plan *pl, const Sched &sc)
         fill(6 + 5 * r, [&](int a) { return r >= rounds_for(pl->shape[a].N) ? 0 : bound(a, r + 1); });
         fill(7 + 5 * r, [&](int a) { return r >= rounds_for(pl->shape[a].N) ? 0 : (bound(a, r + 1) + 63) / 64; });
         fill(8 + 5 * r, [&](int a) { return r >= rounds_for(pl->shape[a].N) ? 0 : (bound(a, r) + 63) / 64; });
-        fill(9 + 5 * r, [&](int a) { return r >= rounds_for(pl->shape[a].N) ? 0 : bound(a, r); });
+        fill(9 + 5 * r, [&](int a) {
+            if (r >= rounds_for(pl->shape[a].N)) return 0;
+            return bound(a, r) * (scores_next(pl, r) ? next_parts(pl->shape[a].B) : 1);
+        });
     }
     return off;
 }
@@ -1971,19 +2179,25 @@ static int enqueue(const Plan *pl, const Sched &sc, const Stages &st, hipStream_
     };
     bool finished = false;
     for (int r = 0; r < pl->rounds; ++r) {
-        if (tm) tm->begin(1 + r, s);
-        if (sc.su == 4)
-            RL_LAUNCH("k_b_score", k_b_score<4>, dim3(grid_of(st.score[r], sc.grid, sc.xcd)), dim3(64 * nw), smem,
-                      s, d, st.score[r], r, sc.dpu[r], tm4, lph_of(r));
-        else
-            RL_LAUNCH("k_b_score", k_b_score<1>, dim3(grid_of(st.score[r], sc.grid, sc.xcd)), dim3(64 * nw), smem,
-                      s, d, st.score[r], r, sc.dpu[r], tm4, lph_of(r));
-        if (tm) tm->end(1 + r, s);
+        if (r <= pl->score_from) {   // later ones are scored by the round before
+            if (tm) tm->begin(1 + r, s);
+            if (sc.su == 4)
+                RL_LAUNCH("k_b_score", k_b_score<4>, dim3(grid_of(st.score[r], sc.grid, sc.xcd)), dim3(64 * nw), smem,
+                          s, d, st.score[r], r, sc.dpu[r], tm4, lph_of(r));
+            else
+                RL_LAUNCH("k_b_score", k_b_score<1>, dim3(grid_of(st.score[r], sc.grid, sc.xcd)), dim3(64 * nw), smem,
+                          s, d, st.score[r], r, sc.dpu[r], tm4, lph_of(r));
+            if (tm) tm->end(1 + r, s);
+        }
         if (r >= pl->fused_from && st.refine[r].total <= FUSED_REFINE) {
             // a lone attempt's last round also writes its result
             const int fin = (pl->n == 1 && r == pl->rounds - 1) ? 1 : 0;
-            RL_LAUNCH("k_b_cull_refine", k_b_cull_refine, dim3(grid_of(st.live[r], 0, sc.xcd)), dim3(64), 0, s, d,
-                      st.live[r], r, fin);
+            if (scores_next(pl, r))
+                RL_LAUNCH("k_b_cull_refine", k_b_cull_refine<true>, dim3(grid_of(st.live[r], 0, sc.xcd)),
+                          dim3(64 * (2 + NEXT_GROUPS)), 0, s, d, st.live[r], r, 0, pl->score_from);
+            else
+                RL_LAUNCH("k_b_cull_refine", k_b_cull_refine<false>, dim3(grid_of(st.live[r], 0, sc.xcd)), dim3(128), 0,
+                          s, d, st.live[r], r, fin, pl->score_from);
             finished |= fin != 0;
             continue;
         }
@@ -2087,7 +2301,7 @@ static int time_rounds(Plan *pl, const Sched &sc, hipStream_t s, LaunchTimer &tm
         if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = RELOC_E_HIP;
     }
     for (int r = 0; r < pl->rounds && !rc; ++r) {
-        t_round[r] = tm.ms(1 + r);
+        t_round[r] = r <= pl->score_from ? tm.ms(1 + r) : 0.0f;   // later ones have no scoring launch
         if (t_round[r] < 0.0f) rc = RELOC_E_HIP;
     }
     (void)hipFree(d_off);
@@ -2250,6 +2464,16 @@ static Plan *find_or_make_plan(reloc_batch *b, const std::vector<Shape> &shape, 
             ++r;
         }
         pl->fused_from = std::max(pl->fused_from, r);
+    }
+    // the first fused round after round 0 whose units fit (bounds only fall)
+    for (int r = std::max(pl->fused_from, 1); r + 1 < pl->rounds && pl->score_from == NO_ROUND; ++r) {
+        int64_t units = 0, survivors = 0;
+        for (const Shape &s : shape) {
+            if (r >= rounds_for(s.N)) continue;
+            units += (int64_t)live_bound(s.N, r) * next_parts(s.B);
+            survivors += live_bound(s.N, r + 1);
+        }
+        if (units <= NEXT_UNITS && survivors <= FUSED_REFINE) pl->score_from = r;
     }
     size_t total = 0;
     pl->slices.resize(pl->n);
