@@ -1027,6 +1027,12 @@ struct Forest {
     uint64_t bytes = 0;
 };
 
+// device memory kept between objects (blocks.hip): hipMalloc's errors; a block
+// is returned with the size it was taken with, by a caller that has waited
+// for all work that used it
+hipError_t block_alloc(void **p, size_t bytes);
+void block_return(void *p, size_t bytes, int device);
+
 // ---------------------------------------------------------------------------
 // one relocalisation attempt as the device sees it (ragged batches)
 // ---------------------------------------------------------------------------

@@ -110,7 +110,7 @@ static int dalloc(Forest *f, T **ptr, size_t count, hipStream_t s)
     size_t bytes = count * sizeof(T);
     if (bytes == 0) bytes = sizeof(T);
     (void)s;
-    if (hipMalloc((void **)ptr, bytes) != hipSuccess) {
+    if (block_alloc((void **)ptr, bytes) != hipSuccess) {
         *ptr = nullptr;
         return RELOC_E_NOMEM;
     }
@@ -118,12 +118,17 @@ static int dalloc(Forest *f, T **ptr, size_t count, hipStream_t s)
     return RELOC_OK;
 }
 
+// keep: the block stays for the next forest (the device is idle)
 template <typename T>
-static void dfree(Forest *f, T **ptr, size_t count)
+static void dfree(Forest *f, T **ptr, size_t count, bool keep = false)
 {
     if (*ptr) {
-        (void)hipFree(*ptr);
-        f->bytes -= std::max<size_t>(count * sizeof(T), sizeof(T));
+        const size_t bytes = std::max<size_t>(count * sizeof(T), sizeof(T));
+        if (keep)
+            block_return(*ptr, bytes, f->device);
+        else
+            (void)hipFree(*ptr);
+        f->bytes -= bytes;
         *ptr = nullptr;
     }
 }
@@ -1071,20 +1076,20 @@ static ModeParams mode_params(const Forest *f)
 // workgroups of k_reservoir per tree
 static int64_t res_blocks(int64_t P) { return (P + RES_THREADS - 1) / RES_THREADS; }
 
-static void free_frame_scratch(Forest *f)
+static void free_frame_scratch(Forest *f, bool keep = false)
 {
-    dfree(f, &f->leaves, (size_t)f->T * f->cap_P);
-    dfree(f, &f->packed, (size_t)PACKED_WORDS * f->cap_P);
-    dfree(f, &f->rank, (size_t)f->T * f->cap_P);
-    dfree(f, &f->late, (size_t)f->T * res_blocks(f->cap_P) * RES_THREADS * sizeof(Late));
-    dfree(f, &f->n_late, (size_t)f->T * res_blocks(f->cap_P));
+    dfree(f, &f->leaves, (size_t)f->T * f->cap_P, keep);
+    dfree(f, &f->packed, (size_t)PACKED_WORDS * f->cap_P, keep);
+    dfree(f, &f->rank, (size_t)f->T * f->cap_P, keep);
+    dfree(f, &f->late, (size_t)f->T * res_blocks(f->cap_P) * RES_THREADS * sizeof(Late), keep);
+    dfree(f, &f->n_late, (size_t)f->T * res_blocks(f->cap_P), keep);
     f->cap_P = 0;
 }
 
-static void free_chunk_tables(Forest *f)
+static void free_chunk_tables(Forest *f, bool keep = false)
 {
-    dfree(f, &f->chunk_cnt, (size_t)f->T * f->cap_C * f->L);
-    dfree(f, &f->chunk_pref, (size_t)f->T * f->cap_C * f->L);
+    dfree(f, &f->chunk_cnt, (size_t)f->T * f->cap_C * f->L, keep);
+    dfree(f, &f->chunk_pref, (size_t)f->T * f->cap_C * f->L, keep);
     f->cap_C = 0;
 }
 
@@ -1203,25 +1208,25 @@ extern "C" const char *reloc_status_string(int code)
     }
 }
 
-static void forest_free(Forest *f)
+static void forest_free(Forest *f, bool keep = false)
 {
     size_t TL = (size_t)f->T * f->L;
-    dfree(f, &f->nodes, (size_t)f->T * (f->L - 1) + 8);
-    dfree(f, &f->deep, (size_t)f->T * (f->L - 1));
-    dfree(f, &f->counter, TL);
-    dfree(f, &f->base, TL);
-    dfree(f, &f->res, TL * f->R);
-    dfree(f, &f->stamp, TL * f->R);
-    dfree(f, &f->modes, TL * f->M);
-    dfree(f, &f->nmodes, TL);
-    dfree(f, &f->dirty, TL);
-    dfree(f, &f->dirty_list, TL);
-    dfree(f, &f->dirty_count, 2);
-    dfree(f, &f->total_samples, 1);
-    free_frame_scratch(f);
-    free_chunk_tables(f);
-    dfree(f, &f->mode_rgb, TL * rgb_stride(f->M));
-    dfree(f, &f->leaf_in, TL * 4);
+    dfree(f, &f->nodes, (size_t)f->T * (f->L - 1) + 8, keep);
+    dfree(f, &f->deep, (size_t)f->T * (f->L - 1), keep);
+    dfree(f, &f->counter, TL, keep);
+    dfree(f, &f->base, TL, keep);
+    dfree(f, &f->res, TL * f->R, keep);
+    dfree(f, &f->stamp, TL * f->R, keep);
+    dfree(f, &f->modes, TL * f->M, keep);
+    dfree(f, &f->nmodes, TL, keep);
+    dfree(f, &f->dirty, TL, keep);
+    dfree(f, &f->dirty_list, TL, keep);
+    dfree(f, &f->dirty_count, 2, keep);
+    dfree(f, &f->total_samples, 1, keep);
+    free_frame_scratch(f, keep);
+    free_chunk_tables(f, keep);
+    dfree(f, &f->mode_rgb, TL * rgb_stride(f->M), keep);
+    dfree(f, &f->leaf_in, TL * 4, keep);
 }
 
 extern "C" int reloc_forest_create(const reloc_params *p, void *stream, reloc_forest **out)
@@ -1285,9 +1290,10 @@ extern "C" int reloc_forest_create(const reloc_params *p, void *stream, reloc_fo
 extern "C" int reloc_forest_destroy(reloc_forest *f)
 {
     if (!f) return RELOC_E_ARG;
-    (void)hipDeviceSynchronize();
+    // (the wait fails while another thread captures a graph: nothing is kept then)
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
     rl_free_plain(f);
-    forest_free(f);
+    forest_free(f, idle);
     delete f;
     return RELOC_OK;
 }

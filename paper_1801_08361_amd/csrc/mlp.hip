@@ -840,7 +840,7 @@ extern "C" int reloc_valid_pixels(reloc_forest *f, const uint16_t *depth_dev, co
     hipStream_t s = (hipStream_t)stream;
     const int P = fr.W * fr.H, nb = (P + VP_BLOCK - 1) / VP_BLOCK;
     int32_t *cnt = nullptr;
-    if (hipMalloc((void **)&cnt, (size_t)(nb + 1) * 4) != hipSuccess) return RELOC_E_NOMEM;
+    if (block_alloc((void **)&cnt, (size_t)(nb + 1) * 4) != hipSuccess) return RELOC_E_NOMEM;
     RL_LAUNCH("k_valid_count", k_valid_count, dim3(nb), dim3(VP_THREADS), 0, s, fr, P, cnt);
     RL_LAUNCH("k_valid_scan", k_valid_scan, dim3(1), dim3(1024), 0, s, cnt, nb);
     RL_LAUNCH("k_valid_emit", k_valid_emit, dim3(nb), dim3(VP_THREADS), 0, s, fr, P, cnt, pix_dev);
@@ -848,8 +848,11 @@ extern "C" int reloc_valid_pixels(reloc_forest *f, const uint16_t *depth_dev, co
     if (hipGetLastError() != hipSuccess || hipMemcpyAsync(&n, cnt + nb, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         rc = RELOC_E_HIP;
-    (void)hipFree(cnt);
-    if (rc) return rc;
+    if (rc) {
+        (void)hipFree(cnt);
+        return rc;
+    }
+    block_return(cnt, (size_t)(nb + 1) * 4, f->device);   // (the stream is done with it)
     *n_out = n;
     return RELOC_OK;
 }
