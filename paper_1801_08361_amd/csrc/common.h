@@ -914,6 +914,17 @@ __device__ __forceinline__ bool pose_from_sums(const double s[NSUM], double R[9]
 // chains of a single wavefront
 // ---------------------------------------------------------------------------
 
+// Orders one wavefront's LDS writes before its later LDS reads of other
+// lanes' data, and its reads before its later writes: a wavefront's LDS
+// operations are performed in issue order, so only the compiler must keep
+// them in place.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // v of lane (lane ^ M), every lane active
 template <int M>
 __device__ __forceinline__ uint32_t xor_lane(uint32_t v)

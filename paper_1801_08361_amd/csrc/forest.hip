@@ -546,6 +546,7 @@ struct __align__(16) ModeLds {
     u32x4_t pt[MAX_R];
     int32_t par[MAX_R];      // sort exchange; then parent by original index, then root (-1: a root)
     uint4 box[MAX_R / 8];    // lo xy, hi xy, lo z, hi z (16-bit halves)
+    uint32_t first[MAX_R / 8];   // the lowest order in the group
     int32_t red[MODE_THREADS / 64][6];
     int32_t n_cand;
     uint32_t next;
@@ -570,6 +571,14 @@ __device__ __forceinline__ uint32_t near_d2(uint32_t axy, uint32_t az, uint32_t 
     const i16x2 d = as_i16x2(axy) - as_i16x2(bxy);
     const int32_t dz = (int32_t)(az - bz);
     return (uint32_t)__builtin_amdgcn_sdot2(d, d, __mul24(dz, dz), false);
+}
+
+// Where point b comes before point a: their squared distance << 10 | b's
+// index, so that the least is the nearest, then the lowest index
+__device__ __forceinline__ uint32_t link_key(u32x4_t a, u32x4_t b)
+{
+    const uint32_t c = __builtin_amdgcn_alignbit(min(near_d2(a.x, a.y, b.x, b.y), D2_CAP), b.z, 22);
+    return b.w < a.w ? c : 0xFFFFFFFFu;
 }
 
 // squared gap between two bounds (lo xy, hi xy, lo z, hi z)
@@ -650,10 +659,17 @@ __device__ __forceinline__ void mode_sort(uint32_t v[4], int len, int tid, uint3
 // of its own, whose points it reads from LDS at one address for all lanes. On
 // a full-size forest a third of all pairs is left (5 % are within 5 cm, 11 %
 // within 10 cm), at 6 (density) and 9 (parent) VALU instructions a pair
-// against about 33 for the branching plain search: k_modes of the 200-frame
-// full-size forest took 64.5 ms with that and takes 7.3 ms with this.
+// against about 33 for the branching plain search. The parent pass starts
+// with the tile itself and then skips every group of which no lane can use a
+// point: one that comes before its own and, by the group's bounds, within its
+// best distance so far (about half of the groups that come within the link
+// radius of the tile). k_modes of the 200-frame full-size forest took 64.5 ms
+// with the plain search, 7.3 ms without that skip and takes 6.5 ms.
 // Groups of 16 leave 6 % more pairs; tiles of 32 points would leave a quarter
-// but need two lists a wavefront. x0, y0, z0: the leaf's minimum; shift: cells
+// but need two lists a wavefront. Handing the (point, group) pairs that are
+// left, 9 lanes of 64 per group met, to a queue that refills the wavefront
+// met an eighth of the groups but spent as much on the queue (6.4 to 6.7 ms,
+// and small leaves 15 % slower). x0, y0, z0: the leaf's minimum; shift: cells
 // of 2^shift mm, 128 an axis at most.
 __device__ __forceinline__ void near_search(ModeLds &S, const Entry (&mine)[4], int n, const ModeParams mp, int x0, int y0, int z0,
                             int shift)
@@ -721,36 +737,46 @@ __device__ __forceinline__ void near_search(ModeLds &S, const Entry (&mine)[4], 
                 tb.w = as_u32(__builtin_elementwise_max(as_i16x2(tb.w), as_i16x2(o.w)));
             }
             const u32x4_t me = S.pt[b + lane];
-            uint32_t cnt = 0u, best = (rl2 + 1u) << 10;
-            for (int g = 0; g < nt; g += 64) {
-                uint64_t m = __ballot(g + lane < nt && box_gap2(tb, S.box[min(g + lane, nt - 1)]) <= r2);
-                while (m) {
-                    const u32x4_t *pp = S.pt + 8 * (g + __builtin_ctzll(m));
-                    m &= m - 1;
-                    if (!pass) {
+            const uint32_t i = me.z >> 22;
+            const int own = b >> 3;      // the tile's first group
+            if (!pass) {
+                uint32_t cnt = 0u;
+                for (int g = 0; g < nt; g += 64) {
+                    uint64_t m = __ballot(g + lane < nt && box_gap2(tb, S.box[min(g + lane, nt - 1)]) <= r2);
+                    while (m) {
+                        const u32x4_t *pp = S.pt + 8 * (g + __builtin_ctzll(m));
+                        m &= m - 1;
 #pragma unroll
                         for (int q = 0; q < 8; ++q) {
                             const u32x2_t w = *(const u32x2_t *)(pp + q);
                             cnt += near_d2(me.x, me.y, w.x, w.y) <= rd2 ? 1u : 0u;
                         }
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            const u32x4_t w = pp[q];
-                            // d2 << 10 | index: the nearest, then the lowest index
-                            const uint32_t c =
-                                __builtin_amdgcn_alignbit(min(near_d2(me.x, me.y, w.x, w.y), D2_CAP), w.z, 22);
-                            best = min(best, w.w < me.w ? c : 0xFFFFFFFFu);
-                        }
                     }
                 }
-            }
-            const uint32_t i = me.z >> 22;
-            if (!pass) {
                 // the padding comes before no point; other wavefronts only read x, y and z in this pass
-                ((uint32_t *)&S.pt[b + lane])[3] = b + lane < n ? ((2047u - cnt) << 10) | i : 0xFFFFFFFFu;
-            } else if (b + lane < n) {
-                S.par[i] = best < ((rl2 + 1u) << 10) ? (int32_t)(best & 1023u) : -1;
+                const uint32_t order = b + lane < n ? ((2047u - cnt) << 10) | i : 0xFFFFFFFFu;
+                ((uint32_t *)&S.pt[b + lane])[3] = order;
+                uint32_t lowest = min(order, xor_lane<1>(order));
+                lowest = min(lowest, xor_lane<2>(lowest));
+                lowest = min(lowest, xor_lane<4>(lowest));
+                if ((lane & 7) == 0) S.first[own + (lane >> 3)] = lowest;
+            } else {
+                uint32_t best = (rl2 + 1u) << 10;
+                auto meet = [&](int g) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) best = min(best, link_key(me, S.pt[8 * g + q]));
+                };
+                for (int g = own; g < min(own + 8, nt); ++g) meet(g);
+                const uint4 at = make_uint4(me.x, me.x, me.y, me.y);
+                for (int g = 0; g < nt; g += 64) {
+                    uint64_t m = __ballot(g + lane < nt && ((g + lane) ^ own) >> 3 != 0 &&
+                                          box_gap2(tb, S.box[min(g + lane, nt - 1)]) <= r2);
+                    for (; m; m &= m - 1) {
+                        const int o = g + __builtin_ctzll(m);
+                        if (__any(S.first[o] < me.w && box_gap2(at, S.box[o]) <= best >> 10)) meet(o);
+                    }
+                }
+                if (b + lane < n) S.par[i] = best < ((rl2 + 1u) << 10) ? (int32_t)(best & 1023u) : -1;
             }
         }
         __syncthreads();
@@ -844,6 +870,8 @@ __device__ __forceinline__ void leaf_modes(const Entry *__restrict__ pts, int n,
             lo[a] = min(lo[a], S.red[w][a]);
             hi[a] = max(hi[a], S.red[w][3 + a]);
         }
+        lo[a] = __builtin_amdgcn_readfirstlane(lo[a]);   // (the same in every thread)
+        hi[a] = __builtin_amdgcn_readfirstlane(hi[a]);
         ext = max(ext, (int64_t)hi[a] - (int64_t)lo[a]);
     }
     if (ext <= NEAR_EXTENT && mp.rd <= NEAR_RADIUS && mp.rl <= NEAR_RADIUS) {
@@ -895,6 +923,10 @@ __device__ __forceinline__ void leaf_modes(const Entry *__restrict__ pts, int n,
     }
     __syncthreads();
     const int nm = nc < mp.M ? nc : mp.M;
+    // (read again: held through the search, its registers would be spilled)
+    Entry again[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) again[e] = pts[min(4 * tid + e, n - 1)];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int i = 4 * tid + e;
@@ -902,9 +934,10 @@ __device__ __forceinline__ void leaf_modes(const Entry *__restrict__ pts, int n,
         const int r = S.par[i];
         const int m = -2 - (r < 0 ? r : S.par[r]);
         if (m < 0) continue;
-        const unsigned long long x = (uint32_t)mine[e].x - (uint32_t)lo[0], y = (uint32_t)mine[e].y - (uint32_t)lo[1],
-                                 z = (uint32_t)mine[e].z - (uint32_t)lo[2];
-        const uint32_t cl = mine[e].rgb;
+        const Entry pt = again[e];
+        const unsigned long long x = (uint32_t)pt.x - (uint32_t)lo[0], y = (uint32_t)pt.y - (uint32_t)lo[1],
+                                 z = (uint32_t)pt.z - (uint32_t)lo[2];
+        const uint32_t cl = pt.rgb;
         atomicAdd(&acc[m][0], x);
         atomicAdd(&acc[m][1], y);
         atomicAdd(&acc[m][2], z);

@@ -53,17 +53,6 @@ __device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << __lane_id())
     unit_range(S, u##0_, u##1_, u##s_); \
     for (int u = u##0_; u < u##1_; u += u##s_)
 
-// Orders one wavefront's LDS writes before its later LDS reads of other
-// lanes' data, and its reads before its later writes: a wavefront's LDS
-// operations are performed in issue order, so only the compiler must keep
-// them in place.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // round r of attempt A runs when at least one (r = 0) or more than one
 // (r > 0) hypothesis is live at its start
 __device__ __forceinline__ bool round_active(const Attempt &A, int r)
