@@ -277,24 +277,75 @@ __device__ __forceinline__ int32_t node_response_d(const Frame &fr, uint64_t w, 
     return (int32_t)fr.rgb[(qy * fr.W + qx) * 3 + c] - (int32_t)fr.rgb[(v * fr.W + u) * 3 + c];
 }
 
-// implicit heap: children of node i are 2i+1 (left) and 2i+2 (right); go
-// right iff response >= threshold; leaf = i - (L - 1)
-__device__ __forceinline__ int32_t traverse_d(const uint64_t *__restrict__ tree, int32_t L, const Frame &fr, int u,
-                                              int v, int32_t d, const PixelDen &pd)
+// Implicit heap: children of node i are 2i+1 (left) and 2i+2 (right); go right
+// iff response >= threshold; leaf = i - (L - 1). The leaves of pixel (u, v)
+// with valid depth d in trees t0 .. t0 + K - 1, straight from the frame: the
+// trees' walks are chains of two dependent loads a level, so K of them advance
+// together, each level's loads all issued before the first is waited for. Only
+// the lanes of a probe's kind take part in its depth or colour load: loading
+// both for every lane costs more gathers than the branches (640 x 480 labels
+// 142 us, 97 so).
+// own: the pixel's colour, channel c in byte c + 1. leaf[k * stride] receives
+// tree t0 + k's.
+template <int K>
+__device__ __forceinline__ void traverse_trees_k(const uint64_t *__restrict__ nodes, int t0, int32_t L, const Frame &fr,
+                                                 int u, int v, int32_t d, const PixelDen &pd, uint32_t own,
+                                                 int32_t *leaf, int stride)
 {
-    int32_t i = 0;
-    while (i < L - 1) {
-        int32_t thr;
-        int32_t r = node_response_d(fr, tree[i], u, v, d, pd, thr);
-        i = 2 * i + 1 + (r >= thr ? 1 : 0);
+    int32_t i[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) i[k] = 0;
+    while (i[0] < L - 1) {
+        uint64_t w[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) w[k] = nodes[(int64_t)(t0 + k) * (L - 1) + i[k]];
+        uint32_t z[K];   // the probed depth (0 outside the image) or colour
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            int32_t kind, dx, dy, thr;
+            unpack_node(w[k], kind, dx, dy, thr);
+            const int32_t qx = u + div_trunc(dx * fr.Fx, pd), qy = v + div_trunc(dy * fr.Fy, pd);
+            const int32_t x = min(max(qx, 0), fr.W - 1), y = min(max(qy, 0), fr.H - 1), p = y * fr.W + x;
+            z[k] = 0u;
+            if (kind) z[k] = fr.rgb[(int64_t)p * 3 + (kind - 1)];
+            else if (x == qx && y == qy) z[k] = fr.depth[p];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            int32_t kind, dx, dy, thr;
+            unpack_node(w[k], kind, dx, dy, thr);
+            const int32_t mine = (int32_t)((own >> (8 * kind)) & 255u);
+            const int32_t r = kind == 0 ? (valid_depth(fr, z[k]) ? (int32_t)z[k] : 65535) - d : (int32_t)z[k] - mine;
+            i[k] = 2 * i[k] + 1 + (r >= thr ? 1 : 0);
+        }
     }
-    return i - (L - 1);
+#pragma unroll
+    for (int k = 0; k < K; ++k) leaf[k * stride] = i[k] - (L - 1);
 }
 
-__device__ __forceinline__ int32_t traverse(const uint64_t *__restrict__ tree, int32_t L, const Frame &fr, int u,
-                                            int v, int32_t d)
+// all T trees' leaves, up to five trees at a time
+__device__ __forceinline__ void traverse_trees(const uint64_t *__restrict__ nodes, int T, int32_t L, const Frame &fr,
+                                               int u, int v, int32_t d, const PixelDen &pd, int32_t *leaf, int stride)
 {
-    return traverse_d(tree, L, fr, u, v, d, pixel_den(fr, d));
+    const uint8_t *rgb = fr.rgb + ((int64_t)v * fr.W + u) * 3;
+    const uint32_t own = ((uint32_t)rgb[0] << 8) | ((uint32_t)rgb[1] << 16) | ((uint32_t)rgb[2] << 24);
+    for (int t = 0; t < T;) {
+        int32_t *out = leaf + t * stride;
+        const int left = T - t;
+        if (left == 5) {
+            traverse_trees_k<5>(nodes, t, L, fr, u, v, d, pd, own, out, stride);
+            t += 5;
+        } else if (left >= 4) {
+            traverse_trees_k<4>(nodes, t, L, fr, u, v, d, pd, own, out, stride);
+            t += 4;
+        } else if (left >= 2) {
+            traverse_trees_k<2>(nodes, t, L, fr, u, v, d, pd, own, out, stride);
+            t += 2;
+        } else {
+            traverse_trees_k<1>(nodes, t, L, fr, u, v, d, pd, own, out, stride);
+            t += 1;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------

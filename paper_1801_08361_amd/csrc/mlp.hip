@@ -438,19 +438,42 @@ __global__ void __launch_bounds__(64) k_mlp_logits(const uint16_t *__restrict__ 
 // per-pixel inputs, labels, verification
 // ---------------------------------------------------------------------------
 
-__global__ void k_pixel_features(FeatArgs A, const int32_t *__restrict__ pix, int n, uint16_t *__restrict__ X,
-                                 float *__restrict__ XF)
+constexpr int PIX_THREADS = 128;
+constexpr int MAX_TREES = 16;   // (checked when a forest is created)
+
+// Bound by the chains and gathers of its walks (traverse_trees): 320 x 240,
+// depth 10, half of the pixels 51 to 31 us, 640 x 480, depth 15 116 to 78
+// against walking tree after tree.
+// VEC: X and XF are 16-byte aligned (as torch's tensors are); their rows of 64
+// and 96 bytes then go out in 16-byte stores, 10 where single values take 56
+template <bool VEC>
+__global__ void __launch_bounds__(PIX_THREADS) k_pixel_features(FeatArgs A, const int32_t *__restrict__ pix, int n,
+                                                                uint16_t *__restrict__ X, float *__restrict__ XF)
 {
+    __shared__ int32_t leaf[MAX_TREES][PIX_THREADS];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int p = pix[i];
     float x[24];
-    if (p >= 0 && p < A.fr.W * A.fr.H) pixel_features(A, p, x);
+    if (p >= 0 && p < A.fr.W * A.fr.H) pixel_features(A, p, &leaf[0][threadIdx.x], PIX_THREADS, x);
     else
         for (int k = 0; k < 24; ++k) x[k] = 0.0f;
-    for (int k = 0; k < 32; ++k) X[(int64_t)i * 32 + k] = k < 24 ? f2bf(x[k]) : (uint16_t)0;
-    if (XF)
-        for (int k = 0; k < 24; ++k) XF[(int64_t)i * 24 + k] = x[k];
+    if constexpr (VEC) {
+        uint4 *in = (uint4 *)(X + (int64_t)i * 32);
+        auto pair = [&](int k) { return (uint32_t)f2bf(x[k]) | ((uint32_t)f2bf(x[k + 1]) << 16); };
+#pragma unroll
+        for (int k = 0; k < 24; k += 8) in[k / 8] = make_uint4(pair(k), pair(k + 2), pair(k + 4), pair(k + 6));
+        in[3] = make_uint4(0u, 0u, 0u, 0u);
+        if (XF) {
+            float4 *row = (float4 *)(XF + (int64_t)i * 24);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) row[k] = make_float4(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
+        }
+    } else {
+        for (int k = 0; k < 32; ++k) X[(int64_t)i * 32 + k] = k < 24 ? f2bf(x[k]) : (uint16_t)0;
+        if (XF)
+            for (int k = 0; k < 24; ++k) XF[(int64_t)i * 24 + k] = x[k];
+    }
 }
 
 struct PoseF {
@@ -461,10 +484,13 @@ struct PoseF {
 // pose: among the modes of the pixel's leaves whose colour passes the pick's
 // colour test (|mode - pixel| <= rgb_tol in every channel), the fraction that
 // lie within 5 cm of y = R c + t (FP32, the scoring transform), as
-// round(255 good / candidates) (0 without candidates)
-__global__ void k_label(FeatArgs A, PoseF P, int rgb_tol, const int32_t *__restrict__ pix, int n,
+// round(255 good / candidates) (0 without candidates). The walks advance
+// together and a leaf's modes are loaded four at a time: 320 x 240, depth 10,
+// half of the pixels 57 to 32 us, 640 x 480, depth 15 121 to 97.
+__global__ void __launch_bounds__(PIX_THREADS) k_label(FeatArgs A, PoseF P, int rgb_tol, const int32_t *__restrict__ pix, int n,
                         uint8_t *__restrict__ lab)
 {
+    __shared__ int32_t leaves[MAX_TREES][PIX_THREADS];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int p = pix[i];
@@ -480,16 +506,29 @@ __global__ void k_label(FeatArgs A, PoseF P, int rgb_tol, const int32_t *__restr
                 y[k] = fmaf(P.R[k * 3 + 0], c[0], fmaf(P.R[k * 3 + 1], c[1], fmaf(P.R[k * 3 + 2], c[2], P.t[k])));
             const int pr = A.fr.rgb[(int64_t)p * 3], pg = A.fr.rgb[(int64_t)p * 3 + 1], pb = A.fr.rgb[(int64_t)p * 3 + 2];
             const float lim = 0.05f * 0.05f;
+            int32_t *leaf = &leaves[0][threadIdx.x];
+            traverse_trees(A.nodes, A.T, A.L, A.fr, u, v, (int32_t)d, pixel_den(A.fr, (int32_t)d), leaf, PIX_THREADS);
             for (int t = 0; t < A.T; ++t) {
-                const int32_t leaf = traverse(A.nodes + (int64_t)t * (A.L - 1), A.L, A.fr, u, v, (int32_t)d);
-                const int64_t li = (int64_t)t * A.L + leaf;
-                for (int m = 0; m < A.nmodes[li]; ++m) {
-                    const Mode &md = A.modes[li * A.M + m];
-                    const int mr = (int)(md.rgb & 255u), mg = (int)((md.rgb >> 8) & 255u), mb = (int)((md.rgb >> 16) & 255u);
-                    if (abs(mr - pr) > rgb_tol || abs(mg - pg) > rgb_tol || abs(mb - pb) > rgb_tol) continue;
-                    cand++;
-                    const float d0 = y[0] - md.mu[0], d1 = y[1] - md.mu[1], d2 = y[2] - md.mu[2];
-                    if ((d0 * d0 + d1 * d1) + d2 * d2 <= lim) good++;
+                const int64_t li = (int64_t)t * A.L + leaf[t * PIX_THREADS];
+                const int nm = A.nmodes[li];
+                // four modes' loads at a time; past the leaf's last they read it again
+                for (int m0 = 0; m0 < nm; m0 += 4) {
+                    float mu[4][3];
+                    uint32_t rgb[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const Mode &md = A.modes[li * A.M + min(m0 + e, nm - 1)];
+                        for (int k = 0; k < 3; ++k) mu[e][k] = md.mu[k];
+                        rgb[e] = md.rgb;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int mr = (int)(rgb[e] & 255u), mg = (int)((rgb[e] >> 8) & 255u), mb = (int)((rgb[e] >> 16) & 255u);
+                        const float d0 = y[0] - mu[e][0], d1 = y[1] - mu[e][1], d2 = y[2] - mu[e][2];
+                        const bool is = m0 + e < nm && abs(mr - pr) <= rgb_tol && abs(mg - pg) <= rgb_tol && abs(mb - pb) <= rgb_tol;
+                        cand += is ? 1u : 0u;
+                        good += is && (d0 * d0 + d1 * d1) + d2 * d2 <= lim ? 1u : 0u;
+                    }
                 }
             }
         }
@@ -504,11 +543,12 @@ __global__ void __launch_bounds__(64) k_mlp_pixels(FeatArgs A, const uint16_t *_
                                                    float *__restrict__ prob)
 {
     __shared__ InTile S;
+    __shared__ int32_t leaf[MAX_TREES][ROWS];
     const int P = A.fr.W * A.fr.H;
     const int l = __lane_id();
     const int p = blockIdx.x * ROWS + l;
     float x[24];
-    if (p < P) pixel_features(A, p, x);
+    if (p < P) pixel_features(A, p, &leaf[0][l], ROWS, x);
     else
         for (int k = 0; k < 24; ++k) x[k] = 0.0f;
     store_row(S.X, x);
@@ -824,8 +864,9 @@ extern "C" int reloc_pixel_features(reloc_forest *f, const uint16_t *depth_dev, 
     rc = update_modes(f, s);
     if (rc) return rc;
     if (n == 0) return RELOC_OK;
-    RL_LAUNCH("k_pixel_features", k_pixel_features, dim3((n + 127) / 128), dim3(128), 0, s, feat_args(f, fr), pix_dev,
-              n, x_dev, xf_dev);
+    auto kernel = (((uintptr_t)x_dev | (uintptr_t)xf_dev) & 15) ? k_pixel_features<false> : k_pixel_features<true>;
+    RL_LAUNCH("k_pixel_features", kernel, dim3((n + PIX_THREADS - 1) / PIX_THREADS), dim3(PIX_THREADS), 0, s, feat_args(f, fr),
+              pix_dev, n, x_dev, xf_dev);
     RL_HIP(hipGetLastError());
     return RELOC_OK;
 }
@@ -874,7 +915,7 @@ extern "C" int reloc_label_pixels(reloc_forest *f, const uint16_t *depth_dev, co
         for (int c = 0; c < 3; ++c) P.R[r * 3 + c] = (float)pose_c2w[r * 4 + c];
         P.t[r] = (float)pose_c2w[r * 4 + 3];
     }
-    RL_LAUNCH("k_label", k_label, dim3((n + 127) / 128), dim3(128), 0, s, feat_args(f, fr), P, f->p.rgb_tol, pix_dev,
+    RL_LAUNCH("k_label", k_label, dim3((n + PIX_THREADS - 1) / PIX_THREADS), dim3(PIX_THREADS), 0, s, feat_args(f, fr), P, f->p.rgb_tol, pix_dev,
               n, label_dev);
     RL_HIP(hipGetLastError());
     return RELOC_OK;

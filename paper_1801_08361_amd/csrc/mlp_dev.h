@@ -318,8 +318,9 @@ __device__ __forceinline__ void pixel_inputs(const FeatArgs &A, int u, int v, ui
     x[23] = (float)v / (float)A.fr.H;
 }
 
-// the same with the leaves found by traversal (zeros for an invalid pixel)
-__device__ __forceinline__ void pixel_features(const FeatArgs &A, int p, float x[24])
+// the same with the leaves found by traversal, kept in the thread's column of
+// `leaf` (T rows of `stride`; zeros for an invalid pixel)
+__device__ __forceinline__ void pixel_features(const FeatArgs &A, int p, int32_t *leaf, int stride, float x[24])
 {
     const uint32_t d = A.fr.depth[p];
     if (!valid_depth(A.fr, d)) {
@@ -327,10 +328,8 @@ __device__ __forceinline__ void pixel_features(const FeatArgs &A, int p, float x
         return;
     }
     const int u = p % A.fr.W, v = p / A.fr.W;
-    const PixelDen pd = pixel_den(A.fr, (int32_t)d);
-    pixel_inputs(A, u, v, d,
-                 [&](int t) { return traverse_d(A.nodes + (int64_t)t * (A.L - 1), A.L, A.fr, u, v, (int32_t)d, pd); },
-                 x);
+    traverse_trees(A.nodes, A.T, A.L, A.fr, u, v, (int32_t)d, pixel_den(A.fr, (int32_t)d), leaf, stride);
+    pixel_inputs(A, u, v, d, [&](int t) { return leaf[t * stride]; }, x);
 }
 
 // lane l's inputs as row l of a tile's inputs X (bfloat16, 8 zeros of
