@@ -1612,8 +1612,9 @@ __global__ void __launch_bounds__(64) k_b_finish(const Attempt *__restrict__ att
 // NEXT_GROUPS: the refinement's registers leave 8 wavefronts to a CU, that is
 // two workgroups of 4; with 4 groups (6 wavefronts, one workgroup) a round of 16
 // live took 12.2 us, with 6 groups 12.9, with 2 10.3. NEXT_UNITS: two turns
-// of the chip, where 32 live of 500 draws take 15.3 us against 9.4 + 6.7
-// and the gap apart; at 64 live four turns would cost more than two launches.
+// of the chip, where 32 positions of 500 draws take 15.3 us (half of them live)
+// to 20 (all live) against 8.8-9.4 + 6.2-7.4 and the gap apart, about the point
+// where both are equal; at 64 four turns would cost more than two launches.
 constexpr int FUSED_LIVE = 64;    // live hypotheses per attempt up to which a round culls in its refinement
 constexpr int NEXT_GROUPS = 2;    // draw groups per workgroup that scores the next round
 constexpr int NEXT_DRAWS = NEXT_GROUPS * GROUP;
