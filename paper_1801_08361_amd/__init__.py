@@ -115,6 +115,7 @@ _SIGS = {
     "reloc_debug_modes": [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p],
     "reloc_debug_modes_from_points": [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p],
     "reloc_debug_trace": [C.c_void_p, C.c_void_p],
+    "reloc_trim": [],
     "reloc_profile_enable": [C.c_int],
     "reloc_profile_reset": [],
     "reloc_profile_read": [C.c_char_p, C.c_void_p, C.c_void_p],
@@ -221,6 +222,11 @@ def _check(code: int, what: str) -> int:
     if code < 0:
         raise RelocError(code, what)
     return code
+
+
+def trim() -> None:
+    """Gives the device memory kept from destroyed forests back (reloc_trim)."""
+    _check(lib().reloc_trim(), "reloc_trim")
 
 
 def profile_enable(on: bool = True) -> None:

@@ -1089,11 +1089,11 @@ struct Forest {
     uint64_t bytes = 0;
 };
 
-// device memory kept between objects (blocks.hip): hipMalloc's errors; a block
-// is returned with the size it was taken with, by a caller that has waited
-// for all work that used it
-hipError_t block_alloc(void **p, size_t bytes);
-void block_return(void *p, size_t bytes, int device);
+// hipMalloc and hipMallocAsync for everything else that the library allocates:
+// before they fail, the memory kept from destroyed forests (forest.hip) goes
+// back to the device
+hipError_t device_malloc(void **p, size_t bytes);
+hipError_t device_malloc_async(void **p, size_t bytes, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // one relocalisation attempt as the device sees it (ragged batches)

@@ -15,12 +15,181 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
+#include <mutex>
 #include <new>
 #include <vector>
 
 #include "common.h"
 
 namespace rl {
+
+// ---------------------------------------------------------------------------
+// device memory
+// ---------------------------------------------------------------------------
+
+// A destroyed forest's tables are kept for the next forest of the same sizes:
+// giving 21 allocations to the driver and taking them back costs more than a
+// small room's frames (0.8 of 2.3 ms for 9 frames in a 267 MB forest), and
+// quick rebuilding brings the driver into a state where giving back and taking
+// 267 MB costs 5 ms, and the 3.5 GB of a full-size forest 60 to 90 ms.
+//
+// A kept block belongs to nobody: whoever returns one has waited for the
+// device, so that any stream or thread can take it, and its contents are as
+// undefined as new memory's. At most KEEP_BYTES are kept per process, the
+// oldest going first, and beyond KEEP_SMALL no more than a KEEP_SHARE-th of
+// what the device has free besides (asking takes 20 us). All of a device's go back to it before any allocation of this
+// library there fails; those not taken within KEEP_TIME at the next
+// allocation or return of a block (calls that other threads' graph captures
+// exclude in any case); and everything by reloc_trim.
+namespace {
+using Clock = std::chrono::steady_clock;
+constexpr size_t KEEP_BYTES = 4ull << 30;   // a full-size forest (3.5 GB), 1/64 of the device
+constexpr size_t KEEP_SMALL = 256ull << 20;
+constexpr size_t KEEP_SHARE = 8;
+constexpr std::chrono::seconds KEEP_TIME{10};
+
+struct Block {
+    void *p;
+    size_t bytes;
+    int device;
+    Clock::time_point since;
+};
+
+struct Kept {
+    std::mutex mu;
+    std::vector<Block> blocks;   // oldest first
+    size_t bytes = 0;
+};
+
+// never destroyed: objects may outlive static ones
+Kept &kept()
+{
+    static Kept *k = new Kept();
+    return *k;
+}
+
+size_t block_bytes(size_t bytes) { return ((bytes < 1 ? 1 : bytes) + 4095) & ~(size_t)4095; }
+
+// the oldest kept block that `which` accepts, no longer kept; p is null if there is none
+template <typename Which>
+Block kept_take(Which which)
+{
+    Kept &k = kept();
+    std::lock_guard<std::mutex> g(k.mu);
+    for (size_t i = 0; i < k.blocks.size(); ++i)
+        if (which(k.blocks[i], k.bytes)) {
+            const Block b = k.blocks[i];
+            k.bytes -= b.bytes;
+            k.blocks.erase(k.blocks.begin() + (std::ptrdiff_t)i);
+            return b;
+        }
+    return Block{};
+}
+
+bool kept_put(const Block &b)
+{
+    Kept &k = kept();
+    std::lock_guard<std::mutex> g(k.mu);
+    try {
+        size_t i = k.blocks.size();
+        while (i > 0 && k.blocks[i - 1].since > b.since) --i;
+        k.blocks.insert(k.blocks.begin() + (std::ptrdiff_t)i, b);
+    } catch (...) {
+        return false;
+    }
+    k.bytes += b.bytes;
+    return true;
+}
+
+// gives those blocks back to their devices; whether there was one
+template <typename Which>
+bool kept_release(Which which)
+{
+    bool any = false;
+    for (;;) {
+        const Block b = kept_take(which);
+        if (!b.p) return any;
+        if (hipFree(b.p) != hipSuccess) {   // (refused while another thread captures a graph)
+            (void)hipGetLastError();
+            (void)kept_put(b);
+            return any;
+        }
+        any = true;
+    }
+}
+
+// An allocation, tried once more without the device's kept blocks if it fails.
+// The error is the caller's alone: it is not left for the next launch's check.
+template <typename Alloc>
+hipError_t alloc_or_release(Alloc alloc)
+{
+    hipError_t e = alloc();
+    if (e == hipSuccess) return e;
+    int device = 0;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&device) == hipSuccess &&
+        kept_release([&](const Block &b, size_t) { return b.device == device; }))
+        e = alloc();
+    (void)hipGetLastError();
+    return e;
+}
+
+void kept_expire()
+{
+    const Clock::time_point now = Clock::now();
+    kept_release([&](const Block &b, size_t) { return now - b.since > KEEP_TIME; });
+}
+
+// bytes that may be kept at the moment, `more` of them wanted
+size_t kept_room(size_t more)
+{
+    {
+        Kept &k = kept();
+        std::lock_guard<std::mutex> g(k.mu);
+        if (k.bytes + more <= KEEP_SMALL) return KEEP_SMALL;
+    }
+    size_t free = 0, total = 0;
+    if (hipMemGetInfo(&free, &total) != hipSuccess) return KEEP_SMALL;
+    return std::max(KEEP_SMALL, std::min(KEEP_BYTES, free / KEEP_SHARE));
+}
+
+// a kept block of the size, or a new one
+hipError_t block_take(void **p, size_t bytes)
+{
+    const size_t n = block_bytes(bytes);
+    int device = 0;
+    const hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    *p = kept_take([&](const Block &b, size_t) { return b.bytes == n && b.device == device; }).p;
+    return *p ? hipSuccess : device_malloc(p, n);
+}
+
+// keeps a block while `room` allows it (0: not at all). The caller has waited
+// for all work on the current device, which has to be the block's.
+void block_return(void *p, size_t bytes, int device, size_t room)
+{
+    const size_t n = block_bytes(bytes);
+    int current = -1;
+    const bool keep = n <= room && hipGetDevice(&current) == hipSuccess && current == device &&
+                      kept_put(Block{p, n, device, Clock::now()});
+    if (keep)
+        kept_release([&](const Block &, size_t bytes_kept) { return bytes_kept > room; });
+    else
+        (void)hipFree(p);
+    kept_expire();
+}
+}  // namespace
+
+hipError_t device_malloc(void **p, size_t bytes)
+{
+    kept_expire();
+    return alloc_or_release([&] { return hipMalloc(p, bytes); });
+}
+
+hipError_t device_malloc_async(void **p, size_t bytes, hipStream_t s)
+{
+    return alloc_or_release([&] { return hipMallocAsync(p, bytes, s); });
+}
 
 // ---------------------------------------------------------------------------
 // parameters
@@ -110,7 +279,7 @@ static int dalloc(Forest *f, T **ptr, size_t count, hipStream_t s)
     size_t bytes = count * sizeof(T);
     if (bytes == 0) bytes = sizeof(T);
     (void)s;
-    if (block_alloc((void **)ptr, bytes) != hipSuccess) {
+    if (block_take((void **)ptr, bytes) != hipSuccess) {
         *ptr = nullptr;
         return RELOC_E_NOMEM;
     }
@@ -118,14 +287,14 @@ static int dalloc(Forest *f, T **ptr, size_t count, hipStream_t s)
     return RELOC_OK;
 }
 
-// keep: the block stays for the next forest (the device is idle)
+// room: kept for the next forest as block_return keeps it (the device is idle)
 template <typename T>
-static void dfree(Forest *f, T **ptr, size_t count, bool keep = false)
+static void dfree(Forest *f, T **ptr, size_t count, size_t room = 0)
 {
     if (*ptr) {
         const size_t bytes = std::max<size_t>(count * sizeof(T), sizeof(T));
-        if (keep)
-            block_return(*ptr, bytes, f->device);
+        if (room)
+            block_return(*ptr, bytes, f->device, room);
         else
             (void)hipFree(*ptr);
         f->bytes -= bytes;
@@ -1109,20 +1278,20 @@ static ModeParams mode_params(const Forest *f)
 // workgroups of k_reservoir per tree
 static int64_t res_blocks(int64_t P) { return (P + RES_THREADS - 1) / RES_THREADS; }
 
-static void free_frame_scratch(Forest *f, bool keep = false)
+static void free_frame_scratch(Forest *f, size_t room = 0)
 {
-    dfree(f, &f->leaves, (size_t)f->T * f->cap_P, keep);
-    dfree(f, &f->packed, (size_t)PACKED_WORDS * f->cap_P, keep);
-    dfree(f, &f->rank, (size_t)f->T * f->cap_P, keep);
-    dfree(f, &f->late, (size_t)f->T * res_blocks(f->cap_P) * RES_THREADS * sizeof(Late), keep);
-    dfree(f, &f->n_late, (size_t)f->T * res_blocks(f->cap_P), keep);
+    dfree(f, &f->leaves, (size_t)f->T * f->cap_P, room);
+    dfree(f, &f->packed, (size_t)PACKED_WORDS * f->cap_P, room);
+    dfree(f, &f->rank, (size_t)f->T * f->cap_P, room);
+    dfree(f, &f->late, (size_t)f->T * res_blocks(f->cap_P) * RES_THREADS * sizeof(Late), room);
+    dfree(f, &f->n_late, (size_t)f->T * res_blocks(f->cap_P), room);
     f->cap_P = 0;
 }
 
-static void free_chunk_tables(Forest *f, bool keep = false)
+static void free_chunk_tables(Forest *f, size_t room = 0)
 {
-    dfree(f, &f->chunk_cnt, (size_t)f->T * f->cap_C * f->L, keep);
-    dfree(f, &f->chunk_pref, (size_t)f->T * f->cap_C * f->L, keep);
+    dfree(f, &f->chunk_cnt, (size_t)f->T * f->cap_C * f->L, room);
+    dfree(f, &f->chunk_pref, (size_t)f->T * f->cap_C * f->L, room);
     f->cap_C = 0;
 }
 
@@ -1241,25 +1410,25 @@ extern "C" const char *reloc_status_string(int code)
     }
 }
 
-static void forest_free(Forest *f, bool keep = false)
+static void forest_free(Forest *f, size_t room = 0)
 {
     size_t TL = (size_t)f->T * f->L;
-    dfree(f, &f->nodes, (size_t)f->T * (f->L - 1) + 8, keep);
-    dfree(f, &f->deep, (size_t)f->T * (f->L - 1), keep);
-    dfree(f, &f->counter, TL, keep);
-    dfree(f, &f->base, TL, keep);
-    dfree(f, &f->res, TL * f->R, keep);
-    dfree(f, &f->stamp, TL * f->R, keep);
-    dfree(f, &f->modes, TL * f->M, keep);
-    dfree(f, &f->nmodes, TL, keep);
-    dfree(f, &f->dirty, TL, keep);
-    dfree(f, &f->dirty_list, TL, keep);
-    dfree(f, &f->dirty_count, 2, keep);
-    dfree(f, &f->total_samples, 1, keep);
-    free_frame_scratch(f, keep);
-    free_chunk_tables(f, keep);
-    dfree(f, &f->mode_rgb, TL * rgb_stride(f->M), keep);
-    dfree(f, &f->leaf_in, TL * 4, keep);
+    dfree(f, &f->nodes, (size_t)f->T * (f->L - 1) + 8, room);
+    dfree(f, &f->deep, (size_t)f->T * (f->L - 1), room);
+    dfree(f, &f->counter, TL, room);
+    dfree(f, &f->base, TL, room);
+    dfree(f, &f->res, TL * f->R, room);
+    dfree(f, &f->stamp, TL * f->R, room);
+    dfree(f, &f->modes, TL * f->M, room);
+    dfree(f, &f->nmodes, TL, room);
+    dfree(f, &f->dirty, TL, room);
+    dfree(f, &f->dirty_list, TL, room);
+    dfree(f, &f->dirty_count, 2, room);
+    dfree(f, &f->total_samples, 1, room);
+    free_frame_scratch(f, room);
+    free_chunk_tables(f, room);
+    dfree(f, &f->mode_rgb, TL * rgb_stride(f->M), room);
+    dfree(f, &f->leaf_in, TL * 4, room);
 }
 
 extern "C" int reloc_forest_create(const reloc_params *p, void *stream, reloc_forest **out)
@@ -1326,8 +1495,15 @@ extern "C" int reloc_forest_destroy(reloc_forest *f)
     // (the wait fails while another thread captures a graph: nothing is kept then)
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     rl_free_plain(f);
-    forest_free(f, idle);
+    forest_free(f, idle ? kept_room(f->bytes) : 0);
+    if (!idle) (void)hipGetLastError();   // (not left for the next launch's check)
     delete f;
+    return RELOC_OK;
+}
+
+extern "C" int reloc_trim(void)
+{
+    kept_release([](const Block &, size_t) { return true; });
     return RELOC_OK;
 }
 
@@ -1677,7 +1853,7 @@ extern "C" int reloc_debug_features8(reloc_forest *f, const uint16_t *depth_dev,
     hipStream_t s = (hipStream_t)stream;
     int64_t P = (int64_t)fr.W * fr.H;
     int32_t *d = nullptr;
-    RL_HIP(hipMallocAsync((void **)&d, (size_t)P * 8 * sizeof(int32_t), s));
+    RL_HIP(device_malloc_async((void **)&d, (size_t)P * 8 * sizeof(int32_t), s));
     RL_LAUNCH("k_features8", k_features8, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s,
                        f->nodes + (int64_t)f->T * (f->L - 1), fr, d);
     hipError_t e = hipMemcpyAsync(feat_host, d, (size_t)P * 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s);
@@ -1724,9 +1900,9 @@ extern "C" int reloc_debug_modes_from_points(reloc_forest *f, const void *entrie
     Mode *d_modes = nullptr;
     int32_t *d_n = nullptr;
     RL_HIP(hipDeviceSynchronize());
-    if (hipMalloc((void **)&d_pts, (size_t)std::max(n, 1) * sizeof(Entry)) != hipSuccess) return RELOC_E_NOMEM;
-    if (hipMalloc((void **)&d_modes, (size_t)f->M * sizeof(Mode)) != hipSuccess ||
-        hipMalloc((void **)&d_n, sizeof(int32_t)) != hipSuccess) {
+    if (device_malloc((void **)&d_pts, (size_t)std::max(n, 1) * sizeof(Entry)) != hipSuccess) return RELOC_E_NOMEM;
+    if (device_malloc((void **)&d_modes, (size_t)f->M * sizeof(Mode)) != hipSuccess ||
+        device_malloc((void **)&d_n, sizeof(int32_t)) != hipSuccess) {
         (void)hipFree(d_pts);
         (void)hipFree(d_modes);
         return RELOC_E_NOMEM;

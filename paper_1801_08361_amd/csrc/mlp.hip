@@ -584,7 +584,7 @@ static int ensure_tiles(reloc_mlp *m, int tiles)
     if (m->partial) (void)hipFree(m->partial);
     m->partial = nullptr;
     m->cap_tiles = 0;
-    RL_HIP(hipMalloc((void **)&m->partial, (size_t)tiles * (NP + 1) * sizeof(float)));
+    RL_HIP(device_malloc((void **)&m->partial, (size_t)tiles * (NP + 1) * sizeof(float)));
     m->cap_tiles = tiles;
     return RELOC_OK;
 }
@@ -595,7 +595,7 @@ static int ensure_loss(reloc_mlp *m, int n)
     if (m->loss) (void)hipFree(m->loss);
     m->loss = nullptr;
     m->cap_loss = 0;
-    RL_HIP(hipMalloc((void **)&m->loss, (size_t)n * sizeof(float)));
+    RL_HIP(device_malloc((void **)&m->loss, (size_t)n * sizeof(float)));
     m->cap_loss = n;
     return RELOC_OK;
 }
@@ -725,9 +725,9 @@ extern "C" int reloc_mlp_create(uint64_t seed, void *stream, reloc_mlp **out)
     hipStream_t s = (hipStream_t)stream;
     reloc_mlp *m = new (std::nothrow) reloc_mlp();
     if (!m) return RELOC_E_NOMEM;
-    if (hipMalloc((void **)&m->w, NP * 4) != hipSuccess || hipMalloc((void **)&m->m, NP * 4) != hipSuccess ||
-        hipMalloc((void **)&m->v, NP * 4) != hipSuccess || hipMalloc((void **)&m->grad, (NP + 1) * 4) != hipSuccess ||
-        hipMalloc((void **)&m->q, NQ * 2) != hipSuccess) {
+    if (device_malloc((void **)&m->w, NP * 4) != hipSuccess || device_malloc((void **)&m->m, NP * 4) != hipSuccess ||
+        device_malloc((void **)&m->v, NP * 4) != hipSuccess || device_malloc((void **)&m->grad, (NP + 1) * 4) != hipSuccess ||
+        device_malloc((void **)&m->q, NQ * 2) != hipSuccess) {
         mlp_free(m);
         delete m;
         return RELOC_E_NOMEM;
@@ -881,19 +881,15 @@ extern "C" int reloc_valid_pixels(reloc_forest *f, const uint16_t *depth_dev, co
     hipStream_t s = (hipStream_t)stream;
     const int P = fr.W * fr.H, nb = (P + VP_BLOCK - 1) / VP_BLOCK;
     int32_t *cnt = nullptr;
-    if (block_alloc((void **)&cnt, (size_t)(nb + 1) * 4) != hipSuccess) return RELOC_E_NOMEM;
+    if (device_malloc_async((void **)&cnt, (size_t)(nb + 1) * 4, s) != hipSuccess) return RELOC_E_NOMEM;
     RL_LAUNCH("k_valid_count", k_valid_count, dim3(nb), dim3(VP_THREADS), 0, s, fr, P, cnt);
     RL_LAUNCH("k_valid_scan", k_valid_scan, dim3(1), dim3(1024), 0, s, cnt, nb);
     RL_LAUNCH("k_valid_emit", k_valid_emit, dim3(nb), dim3(VP_THREADS), 0, s, fr, P, cnt, pix_dev);
     int32_t n = 0;
-    if (hipGetLastError() != hipSuccess || hipMemcpyAsync(&n, cnt + nb, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+    if (hipGetLastError() != hipSuccess || hipMemcpyAsync(&n, cnt + nb, 4, hipMemcpyDeviceToHost, s) != hipSuccess)
         rc = RELOC_E_HIP;
-    if (rc) {
-        (void)hipFree(cnt);
-        return rc;
-    }
-    block_return(cnt, (size_t)(nb + 1) * 4, f->device);   // (the stream is done with it)
+    if (hipFreeAsync(cnt, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) rc = RELOC_E_HIP;
+    if (rc) return rc;
     *n_out = n;
     return RELOC_OK;
 }
@@ -940,8 +936,8 @@ extern "C" int reloc_debug_bf16(const float *x_host, int32_t n, uint16_t *y_host
     if (n == 0) return RELOC_OK;
     float *x = nullptr;
     uint16_t *y = nullptr;
-    if (hipMalloc((void **)&x, (size_t)n * 4) != hipSuccess) return RELOC_E_NOMEM;
-    if (hipMalloc((void **)&y, (size_t)n * 2) != hipSuccess) {
+    if (device_malloc((void **)&x, (size_t)n * 4) != hipSuccess) return RELOC_E_NOMEM;
+    if (device_malloc((void **)&y, (size_t)n * 2) != hipSuccess) {
         (void)hipFree(x);
         return RELOC_E_NOMEM;
     }
@@ -963,8 +959,8 @@ extern "C" int reloc_debug_mfma_probe(const uint16_t *a_host, const uint16_t *bt
     if (!a_host || !bt_host || !c_host) return RELOC_E_ARG;
     uint16_t *a = nullptr, *b = nullptr;
     float *c = nullptr;
-    if (hipMalloc((void **)&a, 16 * 32 * 2) != hipSuccess) return RELOC_E_NOMEM;
-    if (hipMalloc((void **)&b, 16 * 32 * 2) != hipSuccess || hipMalloc((void **)&c, 256 * 4) != hipSuccess) {
+    if (device_malloc((void **)&a, 16 * 32 * 2) != hipSuccess) return RELOC_E_NOMEM;
+    if (device_malloc((void **)&b, 16 * 32 * 2) != hipSuccess || device_malloc((void **)&c, 256 * 4) != hipSuccess) {
         (void)hipFree(a);
         (void)hipFree(b);
         return RELOC_E_NOMEM;

@@ -2222,7 +2222,7 @@ static int capture(reloc_batch *b, const Plan *pl, const Sched &sc, int32_t **d_
 {
     const std::vector<int32_t> off = offsets(pl, sc);
     int32_t *d_off = nullptr;
-    RL_HIP(hipMalloc((void **)&d_off, off.size() * 4));
+    RL_HIP(device_malloc((void **)&d_off, off.size() * 4));
     if (hipMemcpy(d_off, off.data(), off.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(d_off);
         return RELOC_E_HIP;
@@ -2287,7 +2287,7 @@ static int time_rounds(Plan *pl, const Sched &sc, hipStream_t s, LaunchTimer &tm
 {
     const std::vector<int32_t> off = offsets(pl, sc);
     int32_t *d_off = nullptr;
-    RL_HIP(hipMalloc((void **)&d_off, off.size() * 4));
+    RL_HIP(device_malloc((void **)&d_off, off.size() * 4));
     int rc = RELOC_OK;
     if (hipMemcpy(d_off, off.data(), off.size() * 4, hipMemcpyHostToDevice) != hipSuccess) rc = RELOC_E_HIP;
     const Stages st = stages_of(pl, sc, d_off, off);
@@ -2479,8 +2479,8 @@ static Plan *find_or_make_plan(reloc_batch *b, const std::vector<Shape> &shape, 
         total += carve(shape[a], nullptr, pl->slices[a]);
     }
     pl->arena_bytes = total;
-    if (hipMalloc((void **)&pl->arena, total) != hipSuccess ||
-        hipMalloc((void **)&pl->d_att, sizeof(Attempt) * pl->n) != hipSuccess ||
+    if (device_malloc((void **)&pl->arena, total) != hipSuccess ||
+        device_malloc((void **)&pl->d_att, sizeof(Attempt) * pl->n) != hipSuccess ||
         hipHostMalloc((void **)&pl->h_att, sizeof(Attempt) * pl->n, hipHostMallocCoherent) != hipSuccess ||
         hipHostMalloc((void **)&pl->h_res, sizeof(Result) * pl->n, hipHostMallocCoherent) != hipSuccess) {
         pl->arena_bytes = 0;
@@ -2744,7 +2744,7 @@ extern "C" int reloc_debug_lane_probe(uint32_t *out_host)
 {
     if (!out_host) return RELOC_E_ARG;
     uint32_t *d = nullptr;
-    if (hipMalloc((void **)&d, 12 * 64 * 4) != hipSuccess) return RELOC_E_NOMEM;
+    if (device_malloc((void **)&d, 12 * 64 * 4) != hipSuccess) return RELOC_E_NOMEM;
     int rc = RELOC_OK;
     hipLaunchKernelGGL(k_lane_probe, dim3(1), dim3(64), 0, 0, d);
     if (hipDeviceSynchronize() != hipSuccess || hipMemcpy(out_host, d, 12 * 64 * 4, hipMemcpyDeviceToHost) != hipSuccess)

@@ -666,7 +666,7 @@ struct Scratch {
     bool get(X **p, size_t count)
     {
         *p = nullptr;
-        if (hipMallocAsync((void **)p, std::max<size_t>(count, 1) * sizeof(X), s) != hipSuccess) return false;
+        if (device_malloc_async((void **)p, std::max<size_t>(count, 1) * sizeof(X), s) != hipSuccess) return false;
         ptrs.push_back((void *)*p);
         return true;
     }

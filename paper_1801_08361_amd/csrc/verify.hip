@@ -169,7 +169,7 @@ extern "C" int reloc_verify(const uint16_t *da_dev, const uint16_t *db_dev, int3
     if (!verify_args_ok(da_dev, db_dev, W, H, valid_frac, mu_m, accept)) return RELOC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     unsigned long long *work = nullptr;
-    RL_HIP(hipMallocAsync((void **)&work, (3 * VERIFY_MAX_PARTS + 3) * sizeof(unsigned long long), s));
+    RL_HIP(device_malloc_async((void **)&work, (3 * VERIFY_MAX_PARTS + 3) * sizeof(unsigned long long), s));
     const int rc = verify_run(da_dev, db_dev, W, H, work, valid_frac, mu_m, accept, s);
     const hipError_t e = hipFreeAsync(work, s);
     if (rc) return rc;
