@@ -1297,27 +1297,35 @@ static void free_chunk_tables(Forest *f, size_t room = 0)
 
 static int ensure_frame_scratch(Forest *f, int64_t P, hipStream_t s)
 {
+    // (the capacities are set first: what a failure has to give back has their sizes)
     if (P > f->cap_P) {
         free_frame_scratch(f);
+        f->cap_P = P;
         int rc = RELOC_OK;
         rc |= dalloc(f, &f->leaves, (size_t)f->T * P, s);
         rc |= dalloc(f, &f->packed, (size_t)PACKED_WORDS * P, s);
         rc |= dalloc(f, &f->rank, (size_t)f->T * P, s);
         rc |= dalloc(f, &f->late, (size_t)f->T * res_blocks(P) * RES_THREADS * sizeof(Late), s);
         rc |= dalloc(f, &f->n_late, (size_t)f->T * res_blocks(P), s);
-        if (rc) return RELOC_E_NOMEM;
-        f->cap_P = P;
+        if (rc) {
+            free_frame_scratch(f);
+            return RELOC_E_NOMEM;
+        }
     }
     const int chunk = chunk_pixels(P, f->T, f->L);
     const int64_t C = (P + chunk - 1) / chunk;
     if (C > f->cap_C) {
         free_chunk_tables(f);
+        f->cap_C = C;
         int rc = RELOC_OK;
         rc |= dalloc(f, &f->chunk_cnt, (size_t)f->T * C * f->L, s);
         rc |= dalloc(f, &f->chunk_pref, (size_t)f->T * C * f->L, s);
-        if (rc) return RELOC_E_NOMEM;
-        RL_HIP(hipMemsetAsync(f->chunk_cnt, 0, (size_t)f->T * C * f->L * sizeof(uint16_t), s));
-        f->cap_C = C;
+        if (!rc && hipMemsetAsync(f->chunk_cnt, 0, (size_t)f->T * C * f->L * sizeof(uint16_t), s) != hipSuccess)
+            rc = RELOC_E_HIP;
+        if (rc) {
+            free_chunk_tables(f);
+            return rc == RELOC_E_HIP ? RELOC_E_HIP : RELOC_E_NOMEM;
+        }
     }
     return RELOC_OK;
 }

@@ -203,9 +203,50 @@ def case_busy():
     assert D.L.reloc_trim() == 0 and D.used == 0
 
 
+def case_no_scratch():
+    """a frame whose scratch does not fit, whichever of its allocations is the
+    first that fails: nothing of it stays, the forest's memory is what it was,
+    and the frame is accepted once there is room"""
+    D = Dev()
+
+    def memory(f):
+        b = C.c_uint64()
+        assert D.L.reloc_forest_memory(f, C.byref(b)) == 0
+        return b.value
+
+    fr, small = D.frame(), D.frame(64, 48)
+    f = D.forest(**OTHER)
+    own = memory(f)
+    assert D.adapt(f, fr) == 0
+    need, own_after = memory(f) - own, memory(f)
+    D.destroy(f)
+    for first in (0, 1):            # a forest without scratch, and one with a smaller frame's
+        for k in range(24):
+            assert D.L.reloc_trim() == 0
+            f = D.forest(**OTHER)
+            if first:
+                assert D.adapt(f, small) == 0
+            had, used = memory(f), D.used
+            D.d.dev_limit(used + need * k // 24)
+            rc = D.adapt(f, fr)
+            assert rc == D.rl.E_NOMEM or (first and k == 23), (k, rc)
+            if rc:
+                assert own <= memory(f) <= had, (k, own, memory(f), had)
+                assert D.used - used <= 8192 * 24 and D.used >= memory(f), (k, D.used - used)
+            D.d.dev_limit(288 * GB)
+            assert D.adapt(f, fr) == 0 and memory(f) == own_after, k
+            before = D.used
+            D.destroy(f)
+            assert D.used == before, "all of it is kept, at its size"
+    assert D.L.reloc_trim() == 0
+    for p in fr[:2] + small[:2]:
+        D.d.hipFree(p)
+    assert D.used == 0
+
+
 # -- the tests ---------------------------------------------------------------------
 
-@pytest.mark.parametrize("case", ["full_device", "bounds", "time", "busy"])
+@pytest.mark.parametrize("case", ["full_device", "bounds", "time", "busy", "no_scratch"])
 def test_kept_memory(device, case):
     run(device, case)
 
