@@ -1,9 +1,12 @@
 """Device memory kept from destroyed forests goes back to the device on request,
 so that any other allocator of the process can have it, and the next forest
-takes it back in time."""
+takes it back in time; a new forest in another's memory shows nothing of it, in
+its mode slots and in its checkpoint."""
+import numpy as np
 import pytest
 
-from tests.gpu_util import banner, need_gpu
+import synthroom as sr
+from tests.gpu_util import banner, need_gpu, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +38,37 @@ def test_trim_gives_everything_back(dev):
     f.close()
     rl.trim()
     assert torch.cuda.mem_get_info()[0] >= free0 - (64 << 20)
+
+
+def test_new_forest_is_empty_where_another_was(dev, tmp_path):
+    import paper_1801_08361_amd as rl
+    sc = sr.small_scene(107, 200, 150)
+    # a table of modes of 2 MB and one of 40 KB
+    for kw in (dict(n_trees=4, depth=10, reservoir_size=32), dict(n_trees=2, depth=4, reservoir_size=64)):
+        banner(f"forest after another {kw}")
+        p = rl.params_default(max_modes=10, min_cluster=1, **kw)
+        files = []
+        for k in range(2):
+            f = rl.Forest(p)
+            for t in range(f.T):
+                m, n = f.modes(t, 0, f.L)
+                assert not n.any() and not m.view(np.uint8).any()
+            d, c = sc.render_adapt(5)
+            g = to_dev(d, c, dev)
+            # the second one has a tenth of the frame
+            h = 150 if k == 0 else 15
+            f.adapt_frame(g[0][:h].contiguous(), g[1][:h].contiguous(), sc.K, sc.adapt_poses[5])
+            for t in range(f.T):
+                m, n = f.modes(t, 0, f.L)
+                assert n.any()
+                past = np.arange(f.M)[None, :] >= n[:, None]
+                assert not m[past].view(np.uint8).any()
+            f.save(str(tmp_path / f"{k}"))
+            files.append((tmp_path / f"{k}").read_bytes())
+            f.close()
+        # the same frame into a forest that follows another: the same file
+        f = rl.Forest(p)
+        f.adapt_frame(g[0][:15].contiguous(), g[1][:15].contiguous(), sc.K, sc.adapt_poses[5])
+        f.save(str(tmp_path / "again"))
+        assert (tmp_path / "again").read_bytes() == files[1]
+        f.close()
