@@ -801,7 +801,8 @@ extern "C" int reloc_mlp_train(reloc_mlp *m, const uint16_t *x_dev, const uint8_
         ((uintptr_t)x_dev & 15))
         return RELOC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
-    int rc = ensure_loss(m, std::max(epochs, 1));
+    // (without losses nothing is allocated but the minibatch's tiles, once)
+    int rc = epoch_loss_host ? ensure_loss(m, epochs) : RELOC_OK;
     if (rc) return rc;
     const int steps = std::max(1, n_rows / batch_rows);
     for (int e = 0; e < epochs; ++e) {
@@ -812,15 +813,14 @@ extern "C" int reloc_mlp_train(reloc_mlp *m, const uint16_t *x_dev, const uint8_
             m->step++;
             const float c1 = 1.0f - powf(0.9f, (float)m->step), c2 = 1.0f - powf(0.999f, (float)m->step);
             RL_LAUNCH("k_mlp_update", k_mlp_update, dim3((NP + 1 + 63) / 64), dim3(64), 0, s, m->partial, tiles, m->w, m->m,
-                      m->v, m->q, lr, c1, c2, st == steps - 1 ? m->loss + e : nullptr);
+                      m->v, m->q, lr, c1, c2, epoch_loss_host && st == steps - 1 ? m->loss + e : nullptr);
         }
     }
     RL_HIP(hipGetLastError());
     if (epoch_loss_host && epochs > 0) {
-        std::vector<float> g(epochs);
-        RL_HIP(hipMemcpyAsync(g.data(), m->loss, epochs * sizeof(float), hipMemcpyDeviceToHost, s));
+        RL_HIP(hipMemcpyAsync(epoch_loss_host, m->loss, (size_t)epochs * sizeof(float), hipMemcpyDeviceToHost, s));
         RL_HIP(hipStreamSynchronize(s));
-        for (int e = 0; e < epochs; ++e) epoch_loss_host[e] = (float)(g[e] / (double)batch_rows);
+        for (int e = 0; e < epochs; ++e) epoch_loss_host[e] = (float)(epoch_loss_host[e] / (double)batch_rows);
     }
     return RELOC_OK;
 }

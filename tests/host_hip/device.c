@@ -31,6 +31,15 @@ void dev_total(uint64_t bytes) { total = bytes; }
 void dev_refuse(int what) { refuse = what; }
 void dev_skip(long seconds) { skip_s += seconds; }
 
+/* the last copy to the device */
+static unsigned char *upload;
+static uint64_t n_upload;
+uint64_t dev_upload(void *out, uint64_t cap)
+{
+    memcpy(out, upload, cap < n_upload ? cap : n_upload);
+    return n_upload;
+}
+
 int clock_gettime(clockid_t id, struct timespec *t)
 {
     const int rc = (int)syscall(SYS_clock_gettime, id, t);
@@ -108,8 +117,10 @@ int hipMemcpy(void *d, const void *q, size_t n, int kind)
 {
     (void)kind;
     if (on_device(q)) check(q, n);
-    if (on_device(d)) check(d, n);
-    else if (on_device(q)) memset(d, 0, n);
+    if (on_device(d)) {
+        check(d, n);
+        if (!on_device(q) && n && (upload = realloc(upload, n))) memcpy(upload, q, n_upload = n);
+    } else if (on_device(q)) memset(d, 0, n);
     else memcpy(d, q, n);
     return OK;
 }

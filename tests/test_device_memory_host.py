@@ -244,9 +244,35 @@ def case_no_scratch():
     assert D.used == 0
 
 
+def case_network_training():
+    """training that asks for no losses allocates nothing once its minibatch
+    has run, however many epochs follow, so that a capture can hold it; the
+    losses go straight to the caller's array"""
+    D = Dev()
+    x, y, h = D.malloc(64 * 8192), D.malloc(8192), C.c_void_p()
+    assert D.L.reloc_mlp_create(1, None, C.byref(h)) == 0
+
+    def train(epochs, loss=None):
+        return D.L.reloc_mlp_train(h, x, y, 8192, epochs, 512, C.c_float(1e-3), 0, loss, None)
+
+    assert train(1) == 0
+    used = D.used
+    D.d.dev_refuse(2)
+    assert train(64) == 0
+    D.d.dev_refuse(0)
+    assert D.used == used
+    loss = np.full(10, -1.0, np.float32)
+    assert train(8, loss.ctypes.data) == 0
+    assert not loss[:8].any() and (loss[8:] == -1.0).all()
+    assert D.L.reloc_mlp_destroy(h) == 0
+    D.d.hipFree(x)
+    D.d.hipFree(y)
+    assert D.used == 0
+
+
 # -- the tests ---------------------------------------------------------------------
 
-@pytest.mark.parametrize("case", ["full_device", "bounds", "time", "busy", "no_scratch"])
+@pytest.mark.parametrize("case", ["full_device", "bounds", "time", "busy", "no_scratch", "network_training"])
 def test_kept_memory(device, case):
     run(device, case)
 
