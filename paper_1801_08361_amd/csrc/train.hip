@@ -106,11 +106,12 @@ struct TrainFrame {
 };
 
 // A frame as its probes read it: a plane of 16-bit depths (65535 - z, 0 outside
-// the valid range) and three of 8-bit colours (255 - r, g, b), each rounded up
-// to words: 5 bytes a pixel, and 64 or 128 neighbours of a row in a cache
-// line, where the traversal's 8-byte words would hold 16.
-__host__ __device__ __forceinline__ int plane_words(int P) { return (P + 3) & ~3; }
-__host__ __device__ __forceinline__ int plane_bytes(int P) { return 5 * plane_words(P); }
+// the valid range) and three of 8-bit colours (255 - r, g, b): 5 bytes a pixel,
+// and 64 or 128 neighbours of a row in a cache line, where the traversal's
+// 8-byte words would hold 16. Planes have a multiple of 8 pixels, so that the
+// next frame's begin where its depths' 8-byte stores may.
+__host__ __device__ __forceinline__ int plane_pixels(int P) { return (P + 7) & ~7; }
+__host__ __device__ __forceinline__ int plane_bytes(int P) { return 5 * plane_pixels(P); }
 
 struct TrainArgs {
     const TrainFrame *frames;     // [n_frames]
@@ -170,7 +171,7 @@ __global__ void __launch_bounds__(256) k_tr_pack(TrainArgs A, uint8_t *__restric
     for (int fi = blockIdx.y; fi < A.n_frames; fi += gridDim.y) {
         const Frame fr = scalar_read(&A.frames[fi].fr);
         uint8_t *base = planes + scalar_read(&A.frames[fi].poff);
-        const int P = fr.W * fr.H, n = plane_words(P);
+        const int P = fr.W * fr.H, n = plane_pixels(P);
         for (int p = 4 * (blockIdx.x * 256 + threadIdx.x); p < P; p += 4 * 256 * gridDim.x) {
             uint64_t z = 0;
             uint32_t c[3] = {0u, 0u, 0u};
@@ -403,7 +404,7 @@ __device__ __forceinline__ PlaneNode plane_node(uint64_t w, const Frame &fr)
     q.ax = n.ax;
     q.ay = n.ay;
     q.sxy = n.sxy;
-    q.base = kind ? (uint32_t)((1 + kind) * plane_words(fr.W * fr.H)) : 0u;
+    q.base = kind ? (uint32_t)((1 + kind) * plane_pixels(fr.W * fr.H)) : 0u;
     q.lg = kind ? 0u : 1u;
     q.bits = kind ? 8u : 16u;
     q.wout = kind ? 8u : 0u;
@@ -488,7 +489,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_tr_eval(TrainArgs A)
                     img = A.planes + scalar_read(&A.frames[fi].poff);
                     node.ax = (uint32_t)abs(dx * fr.Fx) << 1;
                     node.ay = (uint32_t)abs(dy * fr.Fy) << 1;
-                    node.base = kind ? (uint32_t)((1 + kind) * plane_words(W * H)) : 0u;
+                    node.base = kind ? (uint32_t)((1 + kind) * plane_pixels(W * H)) : 0u;
                 }
                 const __amdgpu_buffer_rsrc_t rs =
                     __builtin_amdgcn_make_buffer_rsrc((void *)img, (short)0, plane_bytes(W * H), 0x00020000);

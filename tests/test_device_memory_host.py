@@ -270,9 +270,31 @@ def case_network_training():
     assert D.used == 0
 
 
+def case_train_planes():
+    """every training frame's planes begin where its 8-byte stores may, whatever
+    the sizes of the frames before"""
+    D = Dev()
+    f, sizes = D.forest(**OTHER), [(163, 121), (4, 1), (1, 1), (65, 3), (640, 480), (7, 5), (5, 4)]
+    frames = [D.frame(*s) for s in sizes]
+    tr = (D.rl.reloc_train_frame * len(sizes))()
+    for x, fr in zip(tr, frames):
+        x.depth_dev, x.rgb_dev, x.K = fr
+        x.pose_c2w[:] = [float(v) for v in np.eye(4).ravel()]
+    assert D.L.reloc_forest_train(f, tr, len(sizes), 1, 8, None) == 0
+    got = np.zeros(4096, np.uint8)
+    D.d.dev_upload.restype = C.c_uint64
+    n = D.d.dev_upload(C.c_void_p(got.ctypes.data), C.c_uint64(got.size))
+    size = n // len(sizes)      # the frames' descriptors; the last word of each is its planes' offset
+    assert n == size * len(sizes) and n <= got.size
+    at = [int(got[(i + 1) * size - 8: (i + 1) * size].view(np.int64)[0]) for i in range(len(sizes))]
+    assert at[0] == 0 and all(a % 8 == 0 for a in at), at
+    # 5 bytes a pixel: 16-bit depths and three planes of colours, none over the next frame's
+    assert all(b - a >= 5 * w * h for a, b, (w, h) in zip(at, at[1:], sizes)), at
+
+
 # -- the tests ---------------------------------------------------------------------
 
-@pytest.mark.parametrize("case", ["full_device", "bounds", "time", "busy", "no_scratch", "network_training"])
+@pytest.mark.parametrize("case", ["full_device", "bounds", "time", "busy", "no_scratch", "network_training", "train_planes"])
 def test_kept_memory(device, case):
     run(device, case)
 
