@@ -1095,6 +1095,14 @@ struct Forest {
 hipError_t device_malloc(void **p, size_t bytes);
 hipError_t device_malloc_async(void **p, size_t bytes, hipStream_t s);
 
+// a kept block of the size, or a new one
+hipError_t block_take(void **p, size_t bytes);
+// Keeps a block for the next block_take while at most `room` bytes are kept (0:
+// gives it back), the oldest going first. The caller has waited for all work
+// that used it; it is kept only if its device is the current one.
+constexpr size_t KEEP_BYTES = 4ull << 30;   // a full-size forest (3.5 GB), 1/64 of the device
+void block_return(void *p, size_t bytes, int device, size_t room);
+
 // ---------------------------------------------------------------------------
 // one relocalisation attempt as the device sees it (ragged batches)
 // ---------------------------------------------------------------------------

@@ -38,13 +38,13 @@ namespace rl {
 // device, so that any stream or thread can take it, and its contents are as
 // undefined as new memory's. At most KEEP_BYTES are kept per process, the
 // oldest going first, and beyond KEEP_SMALL no more than a KEEP_SHARE-th of
-// what the device has free besides (asking takes 20 us). All of a device's go back to it before any allocation of this
-// library there fails; those not taken within KEEP_TIME at the next
-// allocation or return of a block (calls that other threads' graph captures
-// exclude in any case); and everything by reloc_trim.
+// what the device has free besides (asking takes 20 us). All of a device's go
+// back to it before any allocation of this library there fails; those not
+// taken within KEEP_TIME at the next allocation or return of a block (calls
+// that other threads' graph captures exclude in any case); and everything by
+// reloc_trim.
 namespace {
 using Clock = std::chrono::steady_clock;
-constexpr size_t KEEP_BYTES = 4ull << 30;   // a full-size forest (3.5 GB), 1/64 of the device
 constexpr size_t KEEP_SMALL = 256ull << 20;
 constexpr size_t KEEP_SHARE = 8;
 constexpr std::chrono::seconds KEEP_TIME{10};
@@ -153,7 +153,8 @@ size_t kept_room(size_t more)
     return std::max(KEEP_SMALL, std::min(KEEP_BYTES, free / KEEP_SHARE));
 }
 
-// a kept block of the size, or a new one
+}  // namespace
+
 hipError_t block_take(void **p, size_t bytes)
 {
     const size_t n = block_bytes(bytes);
@@ -164,8 +165,6 @@ hipError_t block_take(void **p, size_t bytes)
     return *p ? hipSuccess : device_malloc(p, n);
 }
 
-// keeps a block while `room` allows it (0: not at all). The caller has waited
-// for all work on the current device, which has to be the block's.
 void block_return(void *p, size_t bytes, int device, size_t room)
 {
     const size_t n = block_bytes(bytes);
@@ -178,7 +177,6 @@ void block_return(void *p, size_t bytes, int device, size_t room)
         (void)hipFree(p);
     kept_expire();
 }
-}  // namespace
 
 hipError_t device_malloc(void **p, size_t bytes)
 {

@@ -881,14 +881,18 @@ extern "C" int reloc_valid_pixels(reloc_forest *f, const uint16_t *depth_dev, co
     hipStream_t s = (hipStream_t)stream;
     const int P = fr.W * fr.H, nb = (P + VP_BLOCK - 1) / VP_BLOCK;
     int32_t *cnt = nullptr;
-    if (device_malloc_async((void **)&cnt, (size_t)(nb + 1) * 4, s) != hipSuccess) return RELOC_E_NOMEM;
+    const size_t bytes = (size_t)(nb + 1) * 4;
+    // (a kept block: 37 us a call, 62 with an allocation in stream order)
+    if (block_take((void **)&cnt, bytes) != hipSuccess) return RELOC_E_NOMEM;
     RL_LAUNCH("k_valid_count", k_valid_count, dim3(nb), dim3(VP_THREADS), 0, s, fr, P, cnt);
     RL_LAUNCH("k_valid_scan", k_valid_scan, dim3(1), dim3(1024), 0, s, cnt, nb);
     RL_LAUNCH("k_valid_emit", k_valid_emit, dim3(nb), dim3(VP_THREADS), 0, s, fr, P, cnt, pix_dev);
     int32_t n = 0;
-    if (hipGetLastError() != hipSuccess || hipMemcpyAsync(&n, cnt + nb, 4, hipMemcpyDeviceToHost, s) != hipSuccess)
+    if (hipGetLastError() != hipSuccess || hipMemcpyAsync(&n, cnt + nb, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
         rc = RELOC_E_HIP;
-    if (hipFreeAsync(cnt, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) rc = RELOC_E_HIP;
+    // (the stream is done with it; if the wait failed, hipFree's own is left)
+    block_return(cnt, bytes, f->device, rc ? 0 : KEEP_BYTES);
     if (rc) return rc;
     *n_out = n;
     return RELOC_OK;
