@@ -66,6 +66,7 @@ FLOP_PER_PAIR = 18                # y = R c + t: 9 fma
 # (22 doubles) read and written, live slot (hypothesis, position) read, pose
 # written (rotation and translation as doubles and floats, live FP32 copy)
 REFINE_BYTES_PER_SURVIVOR = 2 * 22 * 8 + 8 + 12 * 8 + 12 * 4 + 12 * 4
+MODE_BYTES = 48                   # one leaf mode
 FUSED_LIVE = 64                   # planned live hypotheses from which a round culls inside its refinement
 FUSED_REFINE = 1024               # planned survivors of a batch up to which a round refines in one kernel
 NEXT_DRAWS = 16                   # draws per workgroup of a cull and refinement that scores the next round
@@ -229,7 +230,11 @@ def rooflines(kernels, res, attempts, batch_pixels=500, batched=False):
     its re-solved pose written; the gathers of its inliers' points and modes
     are not counted, so the figure is a lower bound; the late rounds' kernel
     also reads each live hypothesis's list entry, energy and group sums once
-    and writes the next list). `attempts` are (pixels, trees, learned,
+    and writes the next list). Where that kernel scores the next round too, its
+    share of the scoring is its own term, `next_scoring`: the FLOPs that
+    k_b_score's entry leaves out, and the draws, mode ranges and modes read and
+    group sums and inlier ids written for them; `achieved` does not count
+    it. `attempts` are (pixels, trees, learned,
     hypotheses) per attempt, `batch_pixels` the draws per round (B),
     `batched` whether they ran as one batch; `dominant` is the kernel with the
     largest total time."""
@@ -288,15 +293,19 @@ def rooflines(kernels, res, attempts, batch_pixels=500, batched=False):
     plan_b = plan([a[3] for a in attempts]) if batched else None
     surv = {"one": 0, "split": 0, "fused": 0}
     cull_fused = 0
-    flops = 0.0
-    for r, (_, _, _, n_hyp) in zip(res, attempts):
+    flops = next_flops = next_bytes = 0.0
+    for r, (_, trees, _, n_hyp) in zip(res, attempts):
         kinds, scored = plan_b if batched else plan([n_hyp])
         na = r["n_valid"]
         # k_b_score's part of the attempt's work: its rounds' live
         # hypotheses (a round's draws have the same number of modes, nearly)
         lives = [(na + (1 << k) - 1) >> k for k in range(r["n_rounds"])]
-        flops += ((r["mode_evals"] * FLOP_PER_MODE_TERM + r["pair_evals"] * FLOP_PER_PAIR)
-                  * sum(lives[:scored]) / max(sum(lives), 1))
+        total = r["mode_evals"] * FLOP_PER_MODE_TERM + r["pair_evals"] * FLOP_PER_PAIR
+        share = sum(lives[:scored]) / max(sum(lives), 1)
+        flops += total * share
+        next_flops += total * (1.0 - share)
+        next_bytes += (r["mode_evals"] * (1.0 - share) * MODE_BYTES
+                       + sum(lives[scored:]) * (batch_pixels * (16 + 8 * trees + 4) + 4 * groups))
         for k in range(r["n_rounds"]):
             keep = (na + 1) // 2
             surv[kinds[k]] += keep
@@ -310,6 +319,11 @@ def rooflines(kernels, res, attempts, batch_pixels=500, batched=False):
     out["k_b_refine"] = entry("k_b_refine", "hbm", surv["one"] * per_survivor, HBM_PEAK_GBS, "GB/s")
     out["k_b_cull_refine"] = entry("k_b_cull_refine", "hbm", cull_fused + surv["fused"] * per_survivor,
                                    HBM_PEAK_GBS, "GB/s")
+    fused = out["k_b_cull_refine"]
+    if fused and next_flops > 0:
+        n, sec = fused["launches"], fused["avg_launch_us"] * fused["launches"] * 1e-6
+        fused["next_scoring"] = {"flops_per_launch": next_flops / n, "tflops": next_flops / sec / 1e12,
+                                 "bytes_per_launch": next_bytes / n, "gbs": next_bytes / sec / 1e9}
     mlp = sum(P * MLP_FLOP_PER_PIXEL for P, _, learned, _ in attempts if learned)
     if mlp:
         out["k_b_weights"] = entry("k_b_weights", "mfma", mlp, BF16_PEAK_TFLOPS, "TFLOP/s")

@@ -1,0 +1,34 @@
+"""Host-side check of the bench's roofline accounting (no GPU): every scored
+round is counted once, in the scoring kernel's entry or as the next-round
+scoring of the kernel that culls and refines."""
+import pytest
+
+import bench
+
+
+@pytest.mark.parametrize("n_hyp,n_valid,batch_pixels,scored", [
+    (1024, 1000, 500, 6),       # rounds 6-9 are scored by the round before
+    (256, 256, 64, 3),
+    (64, 40, 2000, 4),          # 8 positions are the first with few enough workgroups
+    (2, 2, 64, 1)])             # one round: no next one
+def test_scoring_is_counted_once(n_hyp, n_valid, batch_pixels, scored):
+    rounds = max(1, (n_hyp - 1).bit_length())
+    n_rounds = max(1, (n_valid - 1).bit_length())
+    res = [dict(mode_evals=12345, pair_evals=678, n_valid=n_valid, n_rounds=n_rounds)]
+    kernels = {"k_b_score": (2.0, min(scored, rounds)), "k_b_cull_refine": (3.0, 6)}
+    r = bench.rooflines(kernels, res, [(100, 5, False, n_hyp)], batch_pixels=batch_pixels)
+    total = 12345 * bench.FLOP_PER_MODE_TERM + 678 * bench.FLOP_PER_PAIR
+    lives = [n_valid]
+    while len(lives) < n_rounds:
+        lives.append((lives[-1] + 1) // 2)
+    by_score = r["k_b_score"]["work_per_launch"] * min(scored, rounds)
+    assert by_score == pytest.approx(total * sum(lives[:scored]) / sum(lives))
+    nxt = r["k_b_cull_refine"].get("next_scoring")
+    if sum(lives[scored:]) == 0:
+        assert nxt is None
+        return
+    assert by_score + nxt["flops_per_launch"] * 6 == pytest.approx(total)
+    assert nxt["tflops"] == pytest.approx(nxt["flops_per_launch"] * 6 / 3.0e-3 / 1e12)
+    share = sum(lives[scored:]) / sum(lives)
+    ids = sum(lives[scored:]) * (batch_pixels * (16 + 8 * 5 + 4) + 4 * ((batch_pixels + 7) // 8))
+    assert nxt["bytes_per_launch"] * 6 == pytest.approx(12345 * share * 48 + ids)
