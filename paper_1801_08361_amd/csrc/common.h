@@ -1078,7 +1078,7 @@ struct Forest {
     int64_t cap_P = 0;             // pixels the frame scratch holds
     int64_t cap_C = 0;             // chunks per tree the chunk tables hold
     int32_t *leaves = nullptr;     // [T][P]
-    uint64_t *packed = nullptr;    // [P] the frame packed for probing
+    uint64_t *packed = nullptr;    // [PACKED_WORDS P] the frame packed for probing: words, then row planes
     uint16_t *rank = nullptr;      // [T][P]
     uint8_t *late = nullptr;       // per workgroup of the reservoir kernel: pixels that met a taken slot
     uint32_t *n_late = nullptr;    // their numbers
@@ -1126,7 +1126,7 @@ struct Attempt {
     uint64_t seed;
     // scratch owned by the batch
     int32_t RL_GLOBAL *leaves;              // [T][P] leaf of each pixel in each tree (-1: invalid pixel)
-    uint64_t RL_GLOBAL *packed;             // [P] the frame packed for probing
+    uint64_t RL_GLOBAL *packed;             // [PACKED_WORDS P] the frame packed for probing
     int32_t RL_GLOBAL *pool;                // [P]
     int32_t RL_GLOBAL *blockcnt;            // [nb]
     unsigned long long RL_GLOBAL *blockw;   // [nb] weight sums per pixel block

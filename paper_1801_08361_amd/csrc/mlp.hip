@@ -45,12 +45,13 @@ struct reloc_mlp {
 
 namespace rl {
 
-// one 16x32 by 32x16 product of host-given tiles (checks the lane layout)
+// one 16x32 by 32x16 product of host-given tiles, with the operand loads and the
+// result's places of the training and inference kernels (checks the lane layout)
 __global__ void __launch_bounds__(64) k_mfma_probe(const uint16_t *__restrict__ A, const uint16_t *__restrict__ Bt,
                                                    float *__restrict__ C)
 {
     floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    acc = mfma_tile(A, 32, Bt, 32, 32, acc);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_operand(A, 32), tile_operand(Bt, 32), acc, 0, 0, 0);
     const int l = __lane_id();
     for (int i = 0; i < 4; ++i) C[(4 * (l >> 4) + i) * 16 + (l & 15)] = acc[i];
 }
@@ -98,15 +99,6 @@ __global__ void k_mlp_pack(const float *__restrict__ w, uint16_t *__restrict__ q
 // ---------------------------------------------------------------------------
 // training: one 64-row tile per workgroup
 // ---------------------------------------------------------------------------
-
-// Orders one wavefront's LDS writes before its later reads of other lanes'
-// data (its LDS operations are performed in issue order).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 constexpr int TS = 72;   // row stride of a tile's arrays: 16-byte rows, off the banks' period
 
@@ -183,11 +175,11 @@ __global__ void __launch_bounds__(320) k_mlp_fwd_bwd(const uint16_t *__restrict_
             const int32_t row = __shfl(src, 16 * ti + col, 64);
             xa[ti] = row >= 0 ? load8(X + (int64_t)row * 32 + kb) : zero8;
         }
-        w1b = load8(q + QW1 + c * 32 + kb);
+        w1b = tile_operand(q + QW1 + 16 * wave * 32, 32);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            w2b[k] = load8(q + QW2 + c * 64 + 32 * k + kb);
-            w2tb[k] = load8(q + QW2T + c * 64 + 32 * k + kb);
+            w2b[k] = tile_operand(q + QW2 + 16 * wave * 64 + 32 * k, 64);
+            w2tb[k] = tile_operand(q + QW2T + 16 * wave * 64 + 32 * k, 64);
         }
         b1c = w[OB1 + c];
         b2c = w[OB2 + c];
@@ -235,7 +227,7 @@ __global__ void __launch_bounds__(320) k_mlp_fwd_bwd(const uint16_t *__restrict_
             floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int k = 0; k < 2; ++k)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load8(S.H1 + (16 * ti + col) * TS + 32 * k + kb), w2b[k], acc,
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_operand(S.H1 + 16 * ti * TS + 32 * k, TS), w2b[k], acc,
                                                               0, 0, 0);
             float hv[4];
 #pragma unroll
@@ -268,7 +260,7 @@ __global__ void __launch_bounds__(320) k_mlp_fwd_bwd(const uint16_t *__restrict_
     const bool valid = tile * ROWS + l < n;
     const float y = (float)label / 255.0f;
     S.dz[wave][l] = valid ? (1.0f / (1.0f + expf(-z)) - y) * inv_n : 0.0f;
-    wave_sync();
+    wave_lds_sync();
     const float *dz = S.dz[wave];
     if (wave == 4) {
         float loss = valid ? fmaxf(z, 0.0f) - z * y + log1pf(expf(-fabsf(z))) : 0.0f;
@@ -303,17 +295,17 @@ __global__ void __launch_bounds__(320) k_mlp_fwd_bwd(const uint16_t *__restrict_
         }
         bs = col_sum(bs);
         if (l < 16) out[OB2 + c] = bs;
-        wave_sync();
+        wave_lds_sync();
         // dW2 = dH2^T H1: this wavefront's units (its own rows of D2T) by all of layer 1's
         bf16x8 a[2];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) a[k] = load8(S.D2T + c * TS + 32 * k + kb);
+        for (int k = 0; k < 2; ++k) a[k] = tile_operand(S.D2T + 16 * wave * TS + 32 * k, TS);
 #pragma unroll
         for (int tj = 0; tj < 4; ++tj) {
             floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int k = 0; k < 2; ++k)
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[k], load8(S.H1T + (16 * tj + col) * TS + 32 * k + kb), acc, 0,
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[k], tile_operand(S.H1T + 16 * tj * TS + 32 * k, TS), acc, 0,
                                                               0, 0);
 #pragma unroll
             for (int i = 0; i < 4; ++i) out[OW2 + (16 * wave + r0 + i) * 64 + 16 * tj + col] = acc[i];
@@ -328,7 +320,7 @@ __global__ void __launch_bounds__(320) k_mlp_fwd_bwd(const uint16_t *__restrict_
         floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int k = 0; k < 2; ++k)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load8(S.D2 + (16 * ti + col) * TS + 32 * k + kb), w2tb[k], acc, 0, 0,
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_operand(S.D2 + 16 * ti * TS + 32 * k, TS), w2tb[k], acc, 0, 0,
                                                           0);
         float d[4];
 #pragma unroll
@@ -340,17 +332,17 @@ __global__ void __launch_bounds__(320) k_mlp_fwd_bwd(const uint16_t *__restrict_
     }
     bs = col_sum(bs);
     if (l < 16) out[OB1 + c] = bs;
-    wave_sync();
+    wave_lds_sync();
     // dW1 = dH1^T X (input columns 24..31 are padding)
     bf16x8 a[2];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) a[k] = load8(S.D1T + c * TS + 32 * k + kb);
+    for (int k = 0; k < 2; ++k) a[k] = tile_operand(S.D1T + 16 * wave * TS + 32 * k, TS);
 #pragma unroll
     for (int tj = 0; tj < 2; ++tj) {
         floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int k = 0; k < 2; ++k)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[k], load8(S.XT + (16 * tj + col) * TS + 32 * k + kb), acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[k], tile_operand(S.XT + 16 * tj * TS + 32 * k, TS), acc, 0, 0, 0);
         const int x = 16 * tj + col;
         if (x < 24)
 #pragma unroll

@@ -47,20 +47,14 @@ __device__ __forceinline__ bf16x8 load8(const uint16_t *p)
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// 16x16 tile of A (16 rows, K-contiguous, stride lda) times B given as B^T
-// (16 columns, K-contiguous, stride ldb), K a multiple of 32, accumulated into
-// acc. Lane l supplies row / column (l & 15) and the k-block 8 (l >> 4) .. +7;
-// the result holds column (l & 15), rows 4 (l >> 4) + i, i < 4.
-__device__ __forceinline__ floatx4 mfma_tile(const uint16_t *A, int lda, const uint16_t *Bt, int ldb, int K,
-                                             floatx4 acc)
+// What the lane supplies of a 16x32 operand tile, A's rows or B's columns, each
+// K-contiguous at the stride: row (column) lane & 15, k-block 8 (lane >> 4) .. +7.
+// The 16x16 result holds, per lane, column lane & 15 and rows
+// 4 (lane >> 4) + i, i < 4.
+__device__ __forceinline__ bf16x8 tile_operand(const uint16_t *tile, int stride)
 {
-    const int l = __lane_id(), r = l & 15, kb = (l >> 4) * 8;
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        const bf16x8 a = load8(A + r * lda + k0 + kb);
-        const bf16x8 b = load8(Bt + r * ldb + k0 + kb);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-    }
-    return acc;
+    const int l = __lane_id();
+    return load8(tile + (l & 15) * stride + 8 * (l >> 4));
 }
 
 // LDS of an inference tile: the rows' inputs (the activations stay in

@@ -1612,9 +1612,12 @@ __global__ void __launch_bounds__(64) k_b_finish(const Attempt *__restrict__ att
 // NEXT_GROUPS: the refinement's registers leave 8 wavefronts to a CU, that is
 // two workgroups of 4; with 4 groups (6 wavefronts, one workgroup) a round of 16
 // live took 12.2 us, with 6 groups 12.9, with 2 10.3. NEXT_UNITS: two turns
-// of the chip, where 32 positions of 500 draws take 15.3 us (half of them live)
-// to 20 (all live) against 8.8-9.4 + 6.2-7.4 and the gap apart, about the point
-// where both are equal; at 64 four turns would cost more than two launches.
+// of the chip, about the point where one launch and two are equal. Whole
+// calls whose round of 32 positions of 500 draws is the one at the limit,
+// with that round in one launch and in two: 222 against 226.6 us with a tenth
+// of the hypotheses valid, 266.7 and 266.4 with 58 %, 360.4 and 358.6 with all
+// (250 draws, 64 positions: 331 and 328; 1000 draws, 16 positions, 58 %: 323
+// and 320). At 64 positions of 500 draws four turns would cost more.
 constexpr int FUSED_LIVE = 64;    // live hypotheses per attempt up to which a round culls in its refinement
 constexpr int NEXT_GROUPS = 2;    // draw groups per workgroup that scores the next round
 constexpr int NEXT_DRAWS = NEXT_GROUPS * GROUP;
@@ -1635,10 +1638,12 @@ __device__ __forceinline__ int score_col(const Attempt &A, int r, int from)
     return r > from && ((r - from) & 1) ? live_bound(A.N, from) : 0;
 }
 
-struct NextLds {
-    int2 tree[NEXT_GROUPS][GROUP][16];   // per draw and tree: modes up to its last; first global index less those before
+// what the wavefronts of a workgroup pass on (tree and pose: NEXT only)
+template <bool NEXT>
+struct CullLds {
+    int2 tree[NEXT ? NEXT_GROUPS : 1][NEXT ? GROUP : 1][16];   // per draw and tree: modes up to its last; first global index less those before
     float pose[12];
-    int32_t slot;                        // the survivor's, or -1
+    int32_t slot;                                              // the survivor's, or -1
 };
 
 template <bool NEXT>
@@ -1646,7 +1651,7 @@ __global__ void __launch_bounds__(64 * (NEXT ? 2 + NEXT_GROUPS : 2))
     k_b_cull_refine(const Attempt *__restrict__ att, Stage S, int r, int fin, int from)
 {
     static_assert(GROUP == 8, "8 lanes per draw of a group of 8");
-    __shared__ NextLds nx;
+    __shared__ CullLds<NEXT> nx;
     FOR_UNITS(S, u) {
         const int a = attempt_of(S, u);
         const Attempt &A = att[a];
