@@ -1188,9 +1188,13 @@ __global__ void __launch_bounds__(256) k_dirty_list(const uint32_t *__restrict__
     }
 }
 
-// Leaves of the dirty list, handed out by a ticket (work[1]) since their
-// point counts differ by three orders of magnitude; work[0] is the list's
-// length. Clears each leaf's dirty flag and refreshes its summary for the
+// Leaves of the dirty list; work[0] is the list's length. They are handed out
+// by a ticket (work[1]) since their point counts differ by three orders of
+// magnitude, unless reservoirs hold no more than a tile's points: such leaves
+// take about 2 us each whatever they hold, and the tickets' additions to one
+// address cost as much (20 480 leaves of 1 point 31 us, with tickets 100; of 16
+// 97 and 117, of 64 118 and 124; leaves of 128 points 142 and 139, of 1024 in a
+// deep forest's first frame 582 and 496). Clears each leaf's dirty flag and refreshes its summary for the
 // learned proposal's inputs: {min(k, R), number of modes kept (<= 3)} and, for
 // its first three modes (the heaviest: modes are ranked by size),
 // {pi = n / min(k, R), -log(Sigma^-1_xx) / 10, -log(Sigma^-1_yy) / 10,
@@ -1207,10 +1211,11 @@ __global__ void __launch_bounds__(MODE_THREADS, 6) k_modes(const uint32_t *__res
     __shared__ ModeLds S;
     const int tid = (int)threadIdx.x;
     const uint32_t n_list = work[0];
+    const bool tickets = mp.R > 64;
     uint32_t it = blockIdx.x;
     while (it < n_list) {
-        uint32_t ahead = 0u;   // the next ticket, asked for before this leaf's work
-        if (tid == 0) ahead = atomicAdd(&work[1], 1u);
+        uint32_t ahead = 0u;   // the next leaf, asked for before this one's work
+        if (tid == 0) ahead = tickets ? atomicAdd(&work[1], 1u) : it;
         const uint32_t li = list[it];
         const uint32_t k = counter[li];
         const int n = k < (uint32_t)mp.R ? (int)k : mp.R;
