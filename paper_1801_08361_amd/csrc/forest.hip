@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -1379,7 +1380,6 @@ int forest_empty_leaves(Forest *f, hipStream_t s)
         hipMemsetAsync(f->stamp, 0, TL * f->R * sizeof(uint32_t), s) != hipSuccess ||
         hipMemsetAsync(f->res, 0, TL * f->R * sizeof(Entry), s) != hipSuccess ||
         hipMemsetAsync(f->nmodes, 0, TL * sizeof(int32_t), s) != hipSuccess ||
-        hipMemsetAsync(f->modes, 0, TL * f->M * sizeof(Mode), s) != hipSuccess ||
         hipMemsetAsync(f->mode_rgb, 0xFF, TL * rgb_stride(f->M) * sizeof(uint32_t), s) != hipSuccess ||
         hipMemsetAsync(f->leaf_in, 0, TL * 4 * sizeof(float4), s) != hipSuccess ||
         hipMemsetAsync(f->dirty, 0, TL * sizeof(uint32_t), s) != hipSuccess ||
@@ -1480,7 +1480,6 @@ extern "C" int reloc_forest_create(const reloc_params *p, void *stream, reloc_fo
         hipMemsetAsync(f->stamp, 0, TL * f->R * sizeof(uint32_t), s) != hipSuccess ||
         hipMemsetAsync(f->res, 0, TL * f->R * sizeof(Entry), s) != hipSuccess ||
         hipMemsetAsync(f->nmodes, 0, TL * sizeof(int32_t), s) != hipSuccess ||
-        hipMemsetAsync(f->modes, 0, TL * f->M * sizeof(Mode), s) != hipSuccess ||
         hipMemsetAsync(f->mode_rgb, 0xFF, TL * rgb_stride(f->M) * sizeof(uint32_t), s) != hipSuccess ||
         hipMemsetAsync(f->leaf_in, 0, TL * 4 * sizeof(float4), s) != hipSuccess ||
         hipMemsetAsync(f->dirty, 0, TL * sizeof(uint32_t), s) != hipSuccess ||
@@ -1617,6 +1616,14 @@ constexpr char FILE_MAGIC[8] = {'R', 'L', 'F', 'O', 'R', 'E', 'S', 'T'};
 constexpr uint32_t FILE_VERSION = 1;
 constexpr size_t STAGE_BYTES = (size_t)64 << 20;
 
+void clear_unused_modes(Mode *modes, const int32_t *count, size_t leaves, int M)
+{
+    for (size_t i = 0; i < leaves; ++i) {
+        const int n = std::min(std::max(count[i], 0), M);
+        memset((void *)(modes + i * M + n), 0, (size_t)(M - n) * sizeof(Mode));
+    }
+}
+
 struct Staging {
     void *buf = nullptr;
     ~Staging()
@@ -1625,24 +1632,30 @@ struct Staging {
     }
 };
 
-// device -> file in chunks through pinned host memory, every 32-bit word
-// passed through `word` on the way where it is given
-int save_section(FILE *fp, const void *dev, size_t bytes, Staging &st, hipStream_t s,
-                 uint32_t (*word)(uint32_t) = nullptr)
+// device -> file in chunks of whole units through pinned host memory, each
+// handed to pass(buffer, offset, bytes) on the way
+template <typename Pass>
+int save_section(FILE *fp, const void *dev, size_t bytes, Staging &st, hipStream_t s, Pass pass, size_t unit = 4)
 {
     const char *src = (const char *)dev;
-    for (size_t off = 0; off < bytes; off += STAGE_BYTES) {
-        const size_t n = std::min(STAGE_BYTES, bytes - off);
+    const size_t chunk = STAGE_BYTES / unit * unit;
+    for (size_t off = 0; off < bytes; off += chunk) {
+        const size_t n = std::min(chunk, bytes - off);
         RL_HIP(hipMemcpyAsync(st.buf, src + off, n, hipMemcpyDeviceToHost, s));
         RL_HIP(hipStreamSynchronize(s));
-        if (word)
-            for (size_t i = 0; i < n / 4; ++i) ((uint32_t *)st.buf)[i] = word(((uint32_t *)st.buf)[i]);
+        pass(st.buf, off, n);
         if (fwrite(st.buf, 1, n, fp) != n) return RELOC_E_IO;
     }
     return RELOC_OK;
 }
 
-// file -> device in chunks through pinned host memory, with `word` as above
+int save_section(FILE *fp, const void *dev, size_t bytes, Staging &st, hipStream_t s)
+{
+    return save_section(fp, dev, bytes, st, s, [](void *, size_t, size_t) {});
+}
+
+// file -> device in chunks through pinned host memory, every 32-bit word passed
+// through `word` on the way where it is given
 int load_section(FILE *fp, void *dev, size_t bytes, Staging &st, hipStream_t s,
                  uint32_t (*word)(uint32_t) = nullptr)
 {
@@ -1689,8 +1702,21 @@ int save_forest(Forest *f, FILE *fp, hipStream_t s)
     if ((rc = save_section(fp, f->nodes, h.n_nodes * sizeof(uint64_t), st, s))) return rc;
     if ((rc = save_section(fp, f->counter, h.n_leaves * sizeof(uint32_t), st, s))) return rc;
     if ((rc = save_section(fp, f->nmodes, h.n_leaves * sizeof(int32_t), st, s))) return rc;
-    if ((rc = save_section(fp, f->modes, h.n_mode_slots * sizeof(Mode), st, s))) return rc;
-    if ((rc = save_section(fp, f->mode_rgb, h.n_rgb * sizeof(uint32_t), st, s, rgb_of_code))) return rc;
+    // (a leaf's unused mode slots hold whatever was there before: zeros in the file)
+    std::unique_ptr<int32_t[]> count(new (std::nothrow) int32_t[h.n_leaves]);
+    if (!count) return RELOC_E_NOMEM;
+    RL_HIP(hipMemcpyAsync(count.get(), f->nmodes, h.n_leaves * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    const size_t leaf = f->M * sizeof(Mode);
+    if ((rc = save_section(fp, f->modes, h.n_mode_slots * sizeof(Mode), st, s,
+                           [&](void *buf, size_t off, size_t n) {
+                               clear_unused_modes((Mode *)buf, count.get() + off / leaf, n / leaf, f->M);
+                           },
+                           leaf)))
+        return rc;
+    if ((rc = save_section(fp, f->mode_rgb, h.n_rgb * sizeof(uint32_t), st, s, [](void *buf, size_t, size_t n) {
+             for (size_t i = 0; i < n / 4; ++i) ((uint32_t *)buf)[i] = rgb_of_code(((uint32_t *)buf)[i]);
+         })))
+        return rc;
     if ((rc = save_section(fp, f->leaf_in, h.n_leaves * 4 * sizeof(float4), st, s))) return rc;
     if (!f->dropped && (rc = save_section(fp, f->res, h.n_res * sizeof(Entry), st, s))) return rc;
     return RELOC_OK;
@@ -1898,10 +1924,14 @@ extern "C" int reloc_debug_modes(reloc_forest *f, int32_t t, int32_t leaf0, int3
     if (rc) return rc;
     RL_HIP(hipDeviceSynchronize());
     int64_t li = (int64_t)t * f->L + leaf0;
-    if (modes_host)
+    std::unique_ptr<int32_t[]> count(new (std::nothrow) int32_t[std::max(n, 1)]);
+    if (!count) return RELOC_E_NOMEM;
+    RL_HIP(hipMemcpy(count.get(), f->nmodes + li, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost));
+    if (modes_host) {
         RL_HIP(hipMemcpy(modes_host, f->modes + li * f->M, (size_t)n * f->M * sizeof(Mode), hipMemcpyDeviceToHost));
-    if (n_modes_host)
-        RL_HIP(hipMemcpy(n_modes_host, f->nmodes + li, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost));
+        clear_unused_modes((Mode *)modes_host, count.get(), (size_t)n, f->M);
+    }
+    if (n_modes_host) memcpy(n_modes_host, count.get(), (size_t)n * sizeof(int32_t));
     return RELOC_OK;
 }
 
