@@ -106,10 +106,10 @@ int reloc_forest_create(const reloc_params *p, void *stream, reloc_forest **out)
 
 /* Frees the forest after the work queued on its streams has finished. Device
  * memory of it may stay with the process for the next forest of the same
- * sizes: at most 4 GiB over all destroyed forests, and beyond 256 MiB no more
+ * sizes: at most 4 GiB over all destroyed forests, and beyond 1 GiB no more
  * than an eighth of what the device has free. It goes back before a device
- * allocation of this library fails, when the library allocates or frees
- * forest memory more than 10 s later, and with reloc_trim. */
+ * allocation of this library fails, when the library allocates device memory
+ * or destroys a forest more than 10 s later, and with reloc_trim. */
 int reloc_forest_destroy(reloc_forest *f);
 
 /* Gives the device memory kept from destroyed forests back, on every device

@@ -41,12 +41,12 @@ namespace rl {
 // oldest going first, and beyond KEEP_SMALL no more than a KEEP_SHARE-th of
 // what the device has free besides (asking takes 20 us). All of a device's go
 // back to it before any allocation of this library there fails; those not
-// taken within KEEP_TIME at the next allocation or return of a block (calls
-// that other threads' graph captures exclude in any case); and everything by
+// taken within KEEP_TIME at the next allocation or destruction (calls that
+// other threads' graph captures exclude in any case); and everything by
 // reloc_trim.
 namespace {
 using Clock = std::chrono::steady_clock;
-constexpr size_t KEEP_SMALL = 256ull << 20;
+constexpr size_t KEEP_SMALL = 1ull << 30;
 constexpr size_t KEEP_SHARE = 8;
 constexpr std::chrono::seconds KEEP_TIME{10};
 
@@ -88,7 +88,8 @@ Block kept_take(Which which)
     return Block{};
 }
 
-bool kept_put(const Block &b)
+// keeps the block; the bytes kept with it, 0 if it is not
+size_t kept_put(const Block &b)
 {
     Kept &k = kept();
     std::lock_guard<std::mutex> g(k.mu);
@@ -97,10 +98,10 @@ bool kept_put(const Block &b)
         while (i > 0 && k.blocks[i - 1].since > b.since) --i;
         k.blocks.insert(k.blocks.begin() + (std::ptrdiff_t)i, b);
     } catch (...) {
-        return false;
+        return 0;
     }
     k.bytes += b.bytes;
-    return true;
+    return k.bytes;
 }
 
 // gives those blocks back to their devices; whether there was one
@@ -170,13 +171,13 @@ void block_return(void *p, size_t bytes, int device, size_t room)
 {
     const size_t n = block_bytes(bytes);
     int current = -1;
-    const bool keep = n <= room && hipGetDevice(&current) == hipSuccess && current == device &&
-                      kept_put(Block{p, n, device, Clock::now()});
-    if (keep)
-        kept_release([&](const Block &, size_t bytes_kept) { return bytes_kept > room; });
-    else
+    size_t all = 0;
+    if (n <= room && hipGetDevice(&current) == hipSuccess && current == device)
+        all = kept_put(Block{p, n, device, Clock::now()});
+    if (!all)
         (void)hipFree(p);
-    kept_expire();
+    else if (all > room)
+        kept_release([&](const Block &, size_t bytes_kept) { return bytes_kept > room; });
 }
 
 hipError_t device_malloc(void **p, size_t bytes)
@@ -1509,6 +1510,7 @@ extern "C" int reloc_forest_destroy(reloc_forest *f)
     rl_free_plain(f);
     forest_free(f, idle ? kept_room(f->bytes) : 0);
     if (!idle) (void)hipGetLastError();   // (not left for the next launch's check)
+    kept_expire();
     delete f;
     return RELOC_OK;
 }

@@ -152,7 +152,7 @@ def case_full_device():
 
 
 def case_bounds():
-    """at most 4 GiB, and past 256 MiB an eighth of what the device has free"""
+    """at most 4 GiB, and past 1 GiB an eighth of what the device has free"""
     D = Dev()
     fs = [D.forest(**LARGE) for _ in range(8)]
     for f in fs:
@@ -160,10 +160,13 @@ def case_bounds():
         assert D.used <= sum(1 for g in fs[fs.index(f) + 1:]) * GB + 4 * GB
     assert 3 * GB < D.used <= 4 * GB
     assert D.L.reloc_trim() == 0 and D.used == 0
-    for total in (6 * GB, 2 * GB):
+    for total in (22 * GB, 14 * GB, 6 * GB):
         D.d.dev_total(total)
-        D.destroy(D.forest(**LARGE))
-        assert D.used <= max((total - D.used) // 8, GB // 4) + GB // 16
+        for f in [D.forest(**LARGE) for _ in range(5)]:
+            D.destroy(f)
+        assert D.used <= max((total - D.used) // 8 + GB // 8, GB)
+        assert D.used > GB // 2
+        assert D.L.reloc_trim() == 0
     assert D.L.reloc_trim() == 0 and D.used == 0
 
 
