@@ -611,7 +611,7 @@ struct Late {
 // of larger k goes to its workgroup's list for k_late (a later one of smaller k
 // has lost). (Slots, then a second pass that compared every pixel's k with its
 // slot's stamp and wrote the winners: 22.7 + 16.9 us for a 640 x 480 frame
-// in 5 trees; this and k_late: 27 + 5, mostly the
+// in 5 trees; this and k_late: 26 + 5, mostly the
 // chain of loads and the atomic's return. With one list for the frame its
 // counter's atomics alone made it 58.)
 constexpr int RES_THREADS = 256;

@@ -376,7 +376,7 @@ __global__ void __launch_bounds__(64) k_mlp_reduce(const float *__restrict__ par
 // One Adam step from the tiles' partials: the entry's sum, its moments, the
 // FP32 weight and its bfloat16 copies; the thread past the parameters writes
 // the minibatch's loss sum to *loss where one is wanted. (Sum, Adam and copies
-// as three kernels took 16.0 + 4.7 + 4.6 us a step of 64 tiles; this takes 4.7.)
+// as three kernels took 16.0 + 4.7 + 4.6 us a step of 64 tiles; this takes 3.8.)
 __global__ void __launch_bounds__(64) k_mlp_update(const float *__restrict__ partial, int tiles, float *__restrict__ w,
                                                    float *__restrict__ m, float *__restrict__ v, uint16_t *__restrict__ q,
                                                    float lr, float c1, float c2, float *__restrict__ loss)

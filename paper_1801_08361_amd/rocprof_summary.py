@@ -19,6 +19,11 @@
   python -m paper_1801_08361_amd.rocprof_summary mfma PMC_DIR STATS_DIR
       per-kernel BF16 matrix FLOPs, rate and matrix-core busy
       (rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_INSTS_VALU_MFMA_MOPS_BF16 ...)
+  python -m paper_1801_08361_amd.rocprof_summary rates SQ_DIR TCP_DIR STATS_DIR
+      per-kernel instruction and cache rates (rocprofv3 --pmc SQ_INSTS_VALU
+      SQ_INSTS_VMEM_RD SQ_INSTS_LDS SQ_LDS_BANK_CONFLICT SQ_WAVES ..., then
+      --pmc TCP_TOTAL_CACHE_ACCESSES_sum TCP_TCC_READ_REQ_sum ..., durations
+      from a kernel trace of the same command)
 
 Library kernels are those in namespace rl; parameter lists are dropped from
 the names (template arguments are kept: k_b_score<4> and k_b_score<1> are
@@ -43,7 +48,7 @@ def _one(d: str, pattern: str) -> str:
 
 
 def _short(name: str) -> str:
-    name = name.replace("void ", "")
+    name = name.replace("void ", "").replace("(anonymous namespace)::", "")
     name = name.split("(")[0]
     return name.replace("rl::", "")
 
@@ -165,6 +170,42 @@ def mfma(pmc_dir: str, stats_dir: str) -> str:
     return "\n".join(out)
 
 
+def _means(d: str):
+    vals = defaultdict(lambda: defaultdict(list))
+    for r in csv.DictReader(open(_one(d, "*counter_collection.csv"))):
+        if _is_lib(r["Kernel_Name"]):
+            vals[_short(r["Kernel_Name"])][r["Counter_Name"]].append(float(r["Counter_Value"]))
+    return {k: {c: sum(v) / len(v) for c, v in cs.items()} for k, cs in vals.items()}
+
+
+def rates(sq_dir: str, tcp_dir: str, stats_dir: str) -> str:
+    """Rates per kernel, from means per dispatch and the average duration in
+    the kernel trace of stats_dir at 2.4 GHz: VALU busy (4 SQ_INSTS_VALU over
+    1024 SIMDs), a CU's cycles per vector load (256 CUs over
+    SQ_INSTS_VMEM_RD), L1 accesses a cycle and CU
+    (TCP_TOTAL_CACHE_ACCESSES), L2 reads per L1 access (TCP_TCC_READ_REQ),
+    LDS instructions per wavefront and bank conflict cycles per LDS
+    instruction."""
+    sq, tcp = _means(sq_dir), _means(tcp_dir)
+    out = ["| kernel | avg us | waves | VALU busy | CU cycles per vector load | L1 accesses per cycle and CU | "
+           "L2 reads per L1 access | LDS instr. per wave | conflict cycles per LDS instr. |",
+           "|---|---:|---:|---:|---:|---:|---:|---:|---:|"]
+    for r in csv.DictReader(open(_one(stats_dir, "*kernel_stats.csv"))):
+        k = _short(r["Name"])
+        if not _is_lib(r["Name"]) or k not in sq:
+            continue
+        cycles = float(r["AverageNs"]) * 2.4
+        c, t = defaultdict(float, sq[k]), defaultdict(float, tcp.get(k, {}))
+        over = lambda a, b, f: f"{a / b:{f}}" if b else "-"
+        acc, lds = t["TCP_TOTAL_CACHE_ACCESSES_sum"], c["SQ_INSTS_LDS"]
+        out.append(f"| {k} | {cycles / 2400:.2f} | {c['SQ_WAVES']:,.0f} | "
+                   f"{100 * 4 * c['SQ_INSTS_VALU'] / (1024 * cycles):.1f} % | "
+                   f"{over(256 * cycles, c['SQ_INSTS_VMEM_RD'], '.1f')} | {acc / (256 * cycles):.3f} | "
+                   f"{over(t['TCP_TCC_READ_REQ_sum'], acc, '.3f')} | {over(lds, c['SQ_WAVES'], ',.0f')} | "
+                   f"{over(c['SQ_LDS_BANK_CONFLICT'], lds, '.2f')} |")
+    return "\n".join(out)
+
+
 def main(argv) -> None:
     if len(argv) == 2 and argv[0] == "stats":
         print(stats(argv[1]))
@@ -174,6 +215,8 @@ def main(argv) -> None:
         print(valu(argv[1], argv[2]))
     elif len(argv) == 3 and argv[0] == "mfma":
         print(mfma(argv[1], argv[2]))
+    elif len(argv) == 4 and argv[0] == "rates":
+        print(rates(argv[1], argv[2], argv[3]))
     else:
         raise SystemExit(__doc__)
 

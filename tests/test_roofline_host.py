@@ -1,9 +1,12 @@
-"""Host-side check of the bench's roofline accounting (no GPU): every scored
-round is counted once, in the scoring kernel's entry or as the next-round
-scoring of the kernel that culls and refines."""
+"""Host-side checks of the measurement code (no GPU): the bench counts every
+scored round once, in the scoring kernel's entry or as the next-round scoring
+of the kernel that culls and refines; the counter summary's rates."""
+import csv
+
 import pytest
 
 import bench
+from paper_1801_08361_amd import rocprof_summary as rs
 
 
 @pytest.mark.parametrize("n_hyp,n_valid,batch_pixels,scored", [
@@ -32,3 +35,22 @@ def test_scoring_is_counted_once(n_hyp, n_valid, batch_pixels, scored):
     share = sum(lives[scored:]) / sum(lives)
     ids = sum(lives[scored:]) * (batch_pixels * (16 + 8 * 5 + 4) + 4 * ((batch_pixels + 7) // 8))
     assert nxt["bytes_per_launch"] * 6 == pytest.approx(12345 * share * 48 + ids)
+
+
+def test_rates(tmp_path):
+    def put(d, name, header, rows):
+        (tmp_path / d).mkdir()
+        with open(tmp_path / d / name, "w", newline="") as f:
+            csv.writer(f).writerows([header] + rows)
+    hdr = ["Kernel_Name", "Counter_Name", "Counter_Value"]
+    k = "void rl::(anonymous namespace)::k_x<8>(rl::A)"
+    put("sq", "s_counter_collection.csv", hdr, [[k, "SQ_INSTS_VALU", 1024 * 600], [k, "SQ_INSTS_VMEM_RD", 256 * 120],
+                                                [k, "SQ_INSTS_LDS", 3000], [k, "SQ_LDS_BANK_CONFLICT", 1500],
+                                                [k, "SQ_WAVES", 1000], ["at::other", "SQ_WAVES", 7]])
+    put("tcp", "t_counter_collection.csv", hdr, [[k, "TCP_TOTAL_CACHE_ACCESSES_sum", 256 * 4800],
+                                                 [k, "TCP_TCC_READ_REQ_sum", 256 * 1200]])
+    put("st", "p_kernel_stats.csv", ["Name", "Calls", "TotalDurationNs", "AverageNs", "MinNs", "MaxNs"],
+        [[k, 2, 2000, 1000, 1, 1], ["at::other", 1, 1, 1, 1, 1]])
+    text = rs.rates(str(tmp_path / "sq"), str(tmp_path / "tcp"), str(tmp_path / "st"))
+    # 2400 cycles: 4 x 600 of them busy a SIMD, 20 per load, 2 L1 accesses a cycle
+    assert text.splitlines()[2:] == ["| k_x<8> | 1.00 | 1,000 | 100.0 % | 20.0 | 2.000 | 0.250 | 3 | 0.50 |"]
