@@ -66,7 +66,8 @@ struct Kept {
 // never destroyed: objects may outlive static ones
 Kept &kept()
 {
-    static Kept *k = new Kept();
+    alignas(Kept) static unsigned char place[sizeof(Kept)];
+    static Kept *k = new (place) Kept();
     return *k;
 }
 
@@ -278,8 +279,13 @@ static int dalloc(Forest *f, T **ptr, size_t count, hipStream_t s)
 {
     size_t bytes = count * sizeof(T);
     if (bytes == 0) bytes = sizeof(T);
-    (void)s;
-    if (block_take((void **)ptr, bytes) != hipSuccess) {
+    // (no block while the stream records a graph, kept or new: hipMalloc refuses there)
+    hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &recording) != hipSuccess) {   // (the null stream beside one that records)
+        (void)hipGetLastError();
+        recording = hipStreamCaptureStatusNone;
+    }
+    if (recording != hipStreamCaptureStatusNone || block_take((void **)ptr, bytes) != hipSuccess) {
         *ptr = nullptr;
         return RELOC_E_NOMEM;
     }

@@ -19,7 +19,7 @@ static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
 static struct { uint64_t p, n; } block[MAX_BLOCKS];
 static int n_blocks;
 static uint64_t next = 0x100000000000ull, used, limit = 288ull << 30, total = 288ull << 30;
-static int last, refuse;
+static int last, refuse, capturing;
 static long skip_s;
 
 /* what a test sees and sets */
@@ -29,6 +29,9 @@ void dev_limit(uint64_t bytes) { limit = bytes; }
 void dev_total(uint64_t bytes) { total = bytes; }
 /* as while another thread captures: 1 the waits for the device, 2 allocation and release too */
 void dev_refuse(int what) { refuse = what; }
+/* the caller's stream records a graph: allocation is refused and ends the recording, as the runtime has it */
+void dev_capture(int on) { capturing = on; }
+int dev_capturing(void) { return capturing; }
 void dev_skip(long seconds) { skip_s += seconds; }
 
 /* the last copy to the device */
@@ -61,7 +64,10 @@ static void wrong(const char *what, const void *p, uint64_t n)
 
 int hipMalloc(void **p, size_t n)
 {
-    if (refuse > 1) return set(REFUSED);
+    if (refuse > 1 || capturing) {
+        capturing = 0;
+        return set(REFUSED);
+    }
     pthread_mutex_lock(&mu);
     if (used + n > limit || n_blocks == MAX_BLOCKS) {
         pthread_mutex_unlock(&mu);
@@ -136,6 +142,7 @@ int hipDeviceSynchronize(void) { return refuse ? set(REFUSED) : OK; }
 int hipStreamSynchronize(void *s) { (void)s; return OK; }
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = malloc(1); return OK; }
 int hipStreamDestroy(void *s) { free(s); return OK; }
+int hipStreamIsCapturing(void *s, int *on) { (void)s; *on = capturing; return OK; }
 int hipStreamBeginCapture(void *s, int m) { (void)s; (void)m; return OK; }
 int hipStreamEndCapture(void *s, void **g) { (void)s; *g = malloc(1); return OK; }
 int hipGraphInstantiate(void **e, void *g, void *n, char *b, size_t l) { (void)g; (void)n; (void)b; (void)l; *e = malloc(1); return OK; }

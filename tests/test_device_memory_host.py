@@ -295,9 +295,35 @@ def case_train_planes():
     assert all(b - a >= 5 * w * h for a, b, (w, h) in zip(at, at[1:], sizes)), at
 
 
+def case_capture():
+    """what needs new memory while its stream records a graph is refused, as
+    without kept memory, and the recording goes on"""
+    D = Dev()
+    fr = D.frame()
+    f = D.forest(**OTHER)
+    assert D.adapt(f, fr) == 0
+    D.destroy(f)
+    f = D.forest(**OTHER)
+    h = C.c_void_p()
+    D.d.dev_capture(1)
+    assert D.adapt(f, fr) == D.rl.E_NOMEM
+    assert D.L.reloc_forest_create(C.byref(D.rl.params_default(**OTHER)), None, C.byref(h)) == D.rl.E_NOMEM
+    assert D.d.dev_capturing() == 1
+    D.d.dev_capture(0)
+    assert D.adapt(f, fr) == 0
+    D.d.dev_capture(1)
+    assert D.adapt(f, fr) == 0     # its scratch is there
+    D.d.dev_capture(0)
+    D.destroy(f)
+    assert D.L.reloc_trim() == 0
+    for p in fr[:2]:
+        D.d.hipFree(p)
+    assert D.used == 0
+
+
 # -- the tests ---------------------------------------------------------------------
 
-@pytest.mark.parametrize("case", ["full_device", "bounds", "time", "busy", "no_scratch", "network_training", "train_planes"])
+@pytest.mark.parametrize("case", ["full_device", "bounds", "time", "busy", "no_scratch", "network_training", "train_planes", "capture"])
 def test_kept_memory(device, case):
     run(device, case)
 
