@@ -39,16 +39,17 @@ namespace rl {
 // device, so that any stream or thread can take it, and its contents are as
 // undefined as new memory's. At most KEEP_BYTES are kept per process, the
 // oldest going first, and beyond KEEP_SMALL no more than a KEEP_SHARE-th of
-// what the device has free besides (asking takes 20 us). All of a device's go
-// back to it before any allocation of this library there fails; those not
-// taken within KEEP_TIME at the next allocation or destruction (calls that
-// other threads' graph captures exclude in any case); and everything by
-// reloc_trim.
+// what the device has free besides (asked once a second at most, since asking
+// takes 15 us: 6 frames into a 450 MB forest 783 us with a question each, 770
+// so). All of a device's go back to it before any allocation of this library
+// there fails; those not taken within KEEP_TIME at the next allocation or
+// destruction (calls that other threads' graph captures exclude in any case);
+// and everything by reloc_trim.
 namespace {
 using Clock = std::chrono::steady_clock;
 constexpr size_t KEEP_SMALL = 1ull << 30;
 constexpr size_t KEEP_SHARE = 8;
-constexpr std::chrono::seconds KEEP_TIME{10};
+constexpr std::chrono::seconds KEEP_TIME{10}, ROOM_TIME{1};
 
 struct Block {
     void *p;
@@ -61,6 +62,9 @@ struct Kept {
     std::mutex mu;
     std::vector<Block> blocks;   // oldest first
     size_t bytes = 0;
+    size_t room = 0;             // what may be kept, as of room_since, on room_device
+    int room_device = -1;
+    Clock::time_point room_since;
 };
 
 // never destroyed: objects may outlive static ones
@@ -73,19 +77,23 @@ Kept &kept()
 
 size_t block_bytes(size_t bytes) { return ((bytes < 1 ? 1 : bytes) + 4095) & ~(size_t)4095; }
 
-// the oldest kept block that `which` accepts, no longer kept; p is null if there is none
+// the oldest (or newest) kept block that `which` accepts, no longer kept; p is
+// null if there is none
 template <typename Which>
-Block kept_take(Which which)
+Block kept_take(Which which, bool newest = false)
 {
     Kept &k = kept();
     std::lock_guard<std::mutex> g(k.mu);
-    for (size_t i = 0; i < k.blocks.size(); ++i)
+    const size_t n = k.blocks.size();
+    for (size_t j = 0; j < n; ++j) {
+        const size_t i = newest ? n - 1 - j : j;
         if (which(k.blocks[i], k.bytes)) {
             const Block b = k.blocks[i];
             k.bytes -= b.bytes;
             k.blocks.erase(k.blocks.begin() + (std::ptrdiff_t)i);
             return b;
         }
+    }
     return Block{};
 }
 
@@ -143,19 +151,25 @@ void kept_expire()
     kept_release([&](const Block &b, size_t) { return now - b.since > KEEP_TIME; });
 }
 
-// bytes that may be kept at the moment, `more` of them wanted
-size_t kept_room(size_t more)
+// bytes that may be kept on the current device at the moment, `more` of them wanted
+size_t kept_room(size_t more, int device)
 {
+    Kept &k = kept();
+    const Clock::time_point now = Clock::now();
     {
-        Kept &k = kept();
         std::lock_guard<std::mutex> g(k.mu);
         if (k.bytes + more <= KEEP_SMALL) return KEEP_SMALL;
+        if (k.room_device == device && now - k.room_since < ROOM_TIME) return k.room;
     }
     size_t free = 0, total = 0;
     if (hipMemGetInfo(&free, &total) != hipSuccess) return KEEP_SMALL;
-    return std::max(KEEP_SMALL, std::min(KEEP_BYTES, free / KEEP_SHARE));
+    const size_t room = std::max(KEEP_SMALL, std::min(KEEP_BYTES, free / KEEP_SHARE));
+    std::lock_guard<std::mutex> g(k.mu);
+    k.room = room;
+    k.room_device = device;
+    k.room_since = now;
+    return room;
 }
-
 }  // namespace
 
 hipError_t block_take(void **p, size_t bytes)
@@ -164,7 +178,8 @@ hipError_t block_take(void **p, size_t bytes)
     int device = 0;
     const hipError_t e = hipGetDevice(&device);
     if (e != hipSuccess) return e;
-    *p = kept_take([&](const Block &b, size_t) { return b.bytes == n && b.device == device; }).p;
+    // (the newest one: more of it is in the caches still)
+    *p = kept_take([&](const Block &b, size_t) { return b.bytes == n && b.device == device; }, true).p;
     return *p ? hipSuccess : device_malloc(p, n);
 }
 
@@ -1514,7 +1529,7 @@ extern "C" int reloc_forest_destroy(reloc_forest *f)
     // (the wait fails while another thread captures a graph: nothing is kept then)
     const bool idle = hipDeviceSynchronize() == hipSuccess;
     rl_free_plain(f);
-    forest_free(f, idle ? kept_room(f->bytes) : 0);
+    forest_free(f, idle ? kept_room(f->bytes, f->device) : 0);
     if (!idle) (void)hipGetLastError();   // (not left for the next launch's check)
     kept_expire();
     delete f;
